@@ -4,12 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpic_mi355x.so")
-SOURCES = ["pic_push.hip", "pic_field.hip", "pic_sort.hip", "pic_compact.hip", "pic_api.hip", "mlp.hip"]
+SOURCES = ["pic_push_vm0.hip", "pic_push_vm1.hip", "pic_push_vm2.hip", "pic_push_vm3.hip", "pic_push.hip", "pic_field.hip", "pic_sort.hip", "pic_compact.hip", "pic_api.hip", "mlp.hip"]
 EXPORTING = ("pic_api.hip", "mlp.hip")     # define the extern "C" boundary
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result",
@@ -18,9 +19,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 
 
 def build(verbose=False):
-    objs = []
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
-    for src in SOURCES:
+
+    def compile_one(src):
         obj = os.path.join(HERE, "_build", src.replace(".hip", ".o"))
         cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
         if src in EXPORTING:
@@ -29,7 +30,10 @@ def build(verbose=False):
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
-        objs.append(obj)
+        return obj
+
+    with ThreadPoolExecutor(max_workers=4) as pool:
+        objs = list(pool.map(compile_one, SOURCES))
     tmp = LIB + ".tmp"
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, LIB)

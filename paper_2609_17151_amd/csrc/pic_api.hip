@@ -218,6 +218,11 @@ void fill_push_consts(const pic_config& c, int s, SegConst& sc)
         sc.eext[k] = (float)c.e_ext[k];
     }
     sc.dtdx = (float)(c.dt / dx);
+    // by the constants as the kernel holds them
+    const bool bx = sc.tv[0] != 0.0f || sc.sv[0] != 0.0f, by = sc.tv[1] != 0.0f || sc.sv[1] != 0.0f,
+               bz = sc.tv[2] != 0.0f || sc.sv[2] != 0.0f;
+    sc.vuse = ((sc.eext[1] != 0.0f || bx || bz) ? kUseY : 0) |
+              ((sc.eext[2] != 0.0f || bx || by || c.renew_lz > 0.0) ? kUseZ : 0);
     sc.mw_half = 0.5 * sp.mass * sp.weight;
     sc.q = sp.charge;
     sc.w = sp.weight;
@@ -786,6 +791,7 @@ struct StepPlan {
     int ppt = 4, threads = 256;
     bool general = false;
     bool fuse = false;                   // the push does the events (no events launch)
+    int vm = kUseY | kUseZ;              // transverse velocity components the push carries
     int64_t grid = 1;
     EvArgs ea{};
     int64_t ev_grid = 1;
@@ -808,8 +814,10 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     p.ppt = ctx->ppt;
     p.threads = ctx->threads;
     p.general = false;
+    p.vm = 0;
     for (int g = 0; g < B * S; ++g) {
         const SegConst& sc = ctx->segc[g];
+        p.vm |= sc.vuse;
         if (sc.compacts || sc.nch > 0 || sc.emits || sc.renew_lz > 0.0) p.general = true;
     }
     push_shape(p.ppt, p.threads, p.general);
@@ -817,7 +825,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     const int T = p.threads * p.ppt;
     int64_t tiles = 0;
     for (int g = 0; g < B * S; ++g) tiles += (pad_cap(ctx->segc[g].cap) + T - 1) / T;
-    const int64_t resident = (int64_t)push_occupancy(p.ppt, p.threads, p.general, p.fuse, lds) * ctx->n_cu;
+    const int64_t resident = (int64_t)push_occupancy(p.ppt, p.threads, p.general, p.fuse, p.vm, lds) * ctx->n_cu;
     p.grid = std::max<int64_t>(1, std::min(std::min(tiles, resident), (int64_t)kMaxPushGrid));
     PushArgs& pa = p.pa;
     pa.d = ctx->d;
@@ -849,6 +857,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     p.ea.births_per_tile = T / kBirthsDiv;
     p.ea.diag = ctx->diag;
     p.ea.eepf_inv_bin = pa.eepf_inv_bin;
+    p.ea.vm = ctx->diag ? (kUseY | kUseZ) : p.vm;
     p.ev_grid = std::max<int64_t>(1, std::min(tiles, (int64_t)events_occupancy() * ctx->n_cu));
     mix((uint64_t)p.ev_grid);
     p.fa.eepf_inv_bin = pa.eepf_inv_bin;
@@ -870,7 +879,7 @@ pic_status enqueue_steps(pic_ctx* ctx, const StepPlan& p, int n, hipStream_t st,
                     return PIC_EHIP;
         }
         const int pp = prof ? prof_begin(ctx) : -1;
-        if (launch_push(p.pa, p.ppt, p.threads, p.general, p.fuse, p.grid, st) != hipSuccess) return PIC_EHIP;
+        if (launch_push(p.pa, p.ppt, p.threads, p.general, p.fuse, p.vm, p.grid, st) != hipSuccess) return PIC_EHIP;
         prof_end(ctx, pp, 0);
         if (p.general && !p.fuse) {
             const int pv = prof ? prof_begin(ctx) : -1;

@@ -28,6 +28,18 @@ constexpr int kBirthsPerTileMin = kTileMin / kBirthsDiv;
 constexpr int kMaxPushGrid = 4096;                          // workgroups of a push launch
 constexpr int kPow = 5;                                     // power time sums per species and node
 
+// Velocity components besides x that a step of a segment changes or needs.
+// Without an imposed magnetic field or a transverse electric one neither vy
+// nor vz changes; with B along y, vy does not, and with B along z, vz.  The
+// push then neither reads nor writes them (the events pass reads those of the
+// few particles that collide): 24 bytes per particle-step instead of 40
+// without a magnetic field, 32 with one along an axis, 4 more with draws.
+// The large pushes are bound by these bytes.  Measured with the packed
+// deposit word (pic_push_kernel.h), per step: 64 argon discharges, 4.9e7
+// particles, 760 -> 602 us; E x B box of 6.4e7 particles 553 -> 438 us, of
+// 8e6 (in the Infinity Cache) 66.2 -> 54.5 us; with axial renewal 111 -> 95 us.
+constexpr int kUseY = 1, kUseZ = 2;
+
 // latched device flags
 constexpr uint32_t kFlagCapacity = 1u << 0;
 constexpr uint32_t kFlagNumeric = 1u << 1;
@@ -72,6 +84,7 @@ struct SegConst {
     float qmh;              // (q/m) dt/2
     float tv[3], sv[3];     // Boris rotation vectors t and s = 2t/(1+t^2)
     float dtdx;             // dt/dx
+    int32_t vuse;           // kUseY, kUseZ: the transverse components the step changes or reads
     float eext[3];          // imposed field
     double mw_half;         // m w / 2 (kinetic energy per unit area)
     double q, w, qm;

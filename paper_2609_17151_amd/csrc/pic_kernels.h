@@ -23,6 +23,7 @@ struct EvArgs {
     int32_t births_per_tile;      // staging slots of a tile
     int32_t diag;
     float eepf_inv_bin;
+    int32_t vm;                   // velocity components the push's records hold
 };
 
 // finalize modes
@@ -64,8 +65,14 @@ struct ProfileArgs {
 };
 
 hipError_t launch_profile_load(const ProfileArgs& a, hipStream_t st);
-hipError_t launch_push(const PushArgs& a, int ppt, int threads, bool general, bool fuse, int64_t grid,
+hipError_t launch_push(const PushArgs& a, int ppt, int threads, bool general, bool fuse, int vm, int64_t grid,
                        hipStream_t st);
+// the same for one set of velocity components (one source file each)
+template <int VM>
+hipError_t launch_push_vm(const PushArgs& a, int ppt, int threads, bool general, bool fuse, int64_t grid,
+                          hipStream_t st);
+template <int VM>
+int push_occupancy_vm(int ppt, int threads, bool general, bool fuse, size_t lds);
 // whether a push of this shape can do its workgroups' own events
 bool push_fusable(int ppt, int threads, bool general);
 void push_shape(int& ppt, int& threads, bool general);
@@ -85,6 +92,6 @@ int64_t compact_tiles_for(int64_t padded_count);
 size_t sort_scratch_bytes(int64_t max_tiles, int B, int cells_max);
 int64_t sort_tiles_for(int64_t padded_count);
 size_t push_lds_bytes(int n_nodes, int n_cells, int diag);
-int push_occupancy(int ppt, int threads, bool general, bool fuse, size_t lds);
+int push_occupancy(int ppt, int threads, bool general, bool fuse, int vm, size_t lds);
 
 }  // namespace pic
