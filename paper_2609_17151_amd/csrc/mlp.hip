@@ -1,21 +1,38 @@
 // Warm-start network on the matrix cores: every layer, forward and backward,
-// is one BF16 product with FP32 accumulation (v_mfma_f32_16x16x32_bf16) whose
-// epilogue applies the elementwise work of the layer, so no activation makes
-// an extra round trip to memory.
+// is a BF16 product with FP32 accumulation (v_mfma_f32_16x16x32_bf16) whose
+// epilogue applies the elementwise work of the layer.
 //
 // A layer's parameters are the matrix [n_out][n_in + 1] with the bias as the
 // last column; the products see the layer input extended by a column of ones,
 // so the bias rides in the product both forward (z = [a 1] Wa^T) and backward
 // (dWa = dz^T [a 1], whose last column is the bias gradient).
 //
-// Product C[M][N] = sum_k A(m, k) B(k, n), operands read through strides from
-// FP32 or BF16 memory and rounded to BF16 into LDS.  Tile 64 x 64 x 32, four
-// waves in a 2 x 2 arrangement, each wave a 32 x 32 block of four 16 x 16
-// matrix-core tiles.  Epilogues:
-//   STORE  C = acc
-//   GELU   C = acc (pre-activation), C2 = acc Phi(acc)
-//   LOSS   d = acc - T, C = scale d (the output gradient), sum of d^2 per workgroup
-//   DGELU  C = acc * g'(Z) with g' the derivative of z Phi(z)
+// Every product reads both operands along k in fragments of 16 rows by 32: lane
+// l of a wave holds k = 8 (l / 16) .. + 7 of row l % 16.  All operands in memory
+// are kept fragment by fragment, 64 lanes of 16 bytes (frag_at), so a load is
+// 1 KB of whole cache lines, with zeros in the padding of k: the weights as Wa
+// (forward) and W^T (backward), the layer inputs and the output gradients of a
+// batch by feature, along the samples, for the weight gradients.  The
+// writer of an activation or of an output gradient rounds it to BF16 once;
+// its only readers are these products, which take BF16 operands.  Sums run
+// over k in ascending blocks of 32, so a result does not depend on the tiling
+// or on which of the kernels below formed it.
+//
+// A training step is two launches.  chain_kernel takes 16 (or 32) samples per
+// workgroup through all layers and back, the activations in LDS: the layers
+// of one sample depend on each other only, so nothing waits on another
+// workgroup, and the 1.3 MB of weights come from L2.  grad_kernel forms the
+// weight gradients of all layers (a 16 x 16 tile per wave) and applies Adam
+// in the epilogue, so the gradient makes no trip through memory.  What bounds
+// them for the 5-256-256-256-768 network on batches of 64: the dependent
+// chain of seven products through one compute unit's L2 port (64 bytes per
+// cycle), and the launch of two kernels.  Measured there: 33 us per training
+// step (chain 25, gradients and Adam 9), 313 us with one tiled kernel per
+// product that gathered its operands element by element; prediction of 4096
+// samples 15 us instead of 122.  Networks whose layers do not fit the chain's
+// LDS take one layer_kernel per product (operands straight from the cache);
+// for the others that is slower at every batch above a few rows (training,
+// batch 64: 41 us and five times the host's launches; 4096: 110 against 60).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,31 +45,39 @@
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBM = 64, kBN = 64, kBK = 32;
-constexpr int kPad = 8;                    // LDS row = 40 BF16 = 80 B: rows land on different banks
-constexpr int kThreads = 256;
+constexpr int kMaxL = PIC_MLP_MAX_LAYERS;
+constexpr int kChainThreads = 1024;
+constexpr int kChainWaves = kChainThreads / 64;
+constexpr int kChainLds = 64 * 1024;       // activations of the chain's rows
+constexpr int kPad = 8;                    // LDS row padding: rows land on different banks
+constexpr int kAhead = 12;                 // weight fragments in flight per wave
 
-enum { EPI_STORE = 0, EPI_GELU = 1, EPI_LOSS = 2, EPI_DGELU = 3 };
+__host__ __device__ constexpr int pad16(int n) { return (n + 15) & ~15; }
+__host__ __device__ constexpr int pad32(int n) { return (n + 31) & ~31; }
 
-struct Operand {
-    const void* p;
-    int64_t s0, s1;        // A: element (m, k) at m*s0 + k*s1;  B: element (k, n) at k*s0 + n*s1
-    int32_t bf16;          // storage type: 1 = BF16, 0 = FP32
-    int32_t one;           // A: k index that reads as 1; B: n index that reads as 1; -1: none
+// element (row, k) of an operand whose rows have `ks` blocks of 32 k
+__host__ __device__ __forceinline__ int64_t frag_at(int row, int k, int ks)
+{
+    return (((int64_t)(row >> 4) * ks + (k >> 5)) * 64 + (row & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
+
+struct Layer {
+    int32_t ni, no;        // inputs, outputs
+    int32_t kf, kb;        // padded lengths of k: forward (ni + 1), backward (no)
+    int64_t off;           // first parameter
+    __bf16* wf;            // [pad16(no)][kf] Wa, in fragments
+    __bf16* wt;            // [pad16(ni)][kb] W^T, in fragments
+    __bf16* at;            // [pad32(ni + 1)][ldb] layer input with its ones by feature, in fragments
+    __bf16* dzt;           // [pad16(no)][ldb] output gradient by feature, in fragments
+    float* z;              // [batch][no] pre-activation (hidden layers)
 };
 
-struct GemmArgs {
-    int32_t M, N, K, epi;
-    Operand a, b;
-    float* c;
-    float* c2;
-    int64_t ldc;
-    const float* aux;      // LOSS: targets, DGELU: pre-activation of the layer below
-    int64_t ldaux;
-    float scale;
-    float* loss_part;      // LOSS: one partial sum per workgroup
+struct Net {
+    int32_t L;
+    Layer l[kMaxL];
 };
 
 __device__ __forceinline__ float gelu(float z)
@@ -65,146 +90,465 @@ __device__ __forceinline__ float gelu_grad(float z)
     return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-__device__ __forceinline__ float ld(const Operand& o, int64_t idx)
+__device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
 {
-    return o.bf16 ? (float)reinterpret_cast<const __bf16*>(o.p)[idx] : reinterpret_cast<const float*>(o.p)[idx];
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-__global__ __launch_bounds__(kThreads) void gemm_kernel(GemmArgs g)
+// acc[i] += A_i B over KS blocks of 32: A_i from LDS (`a` at the lane's row and
+// k, blocks of 16 rows lda apart), B from memory (`b` at the lane's part of its
+// first fragment), every load issued before the first product.
+template <int MT, int KS>
+__device__ __forceinline__ void product_blocks(const __bf16* a, int lda, const __bf16* __restrict__ b, f32x4* acc)
 {
-    __shared__ __align__(16) __bf16 As[kBM][kBK + kPad];
-    __shared__ __align__(16) __bf16 Bs[kBN][kBK + kPad];   // [n][k]
-    __shared__ float s_red[kThreads / 64];
+    bf16x8 f[KS];
+#pragma unroll
+    for (int u = 0; u < KS; ++u) f[u] = *reinterpret_cast<const bf16x8*>(b + 512 * u);
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+            acc[i] = mfma(*reinterpret_cast<const bf16x8*>(a + (size_t)i * 16 * lda + 32 * u), f[u], acc[i]);
+}
 
+// ... over ks blocks, kAhead at a time
+template <int MT>
+__device__ __forceinline__ void product(const __bf16* a, int lda, const __bf16* __restrict__ b, int ks, f32x4* acc)
+{
+    for (; ks >= kAhead; ks -= kAhead, a += 32 * kAhead, b += 512 * kAhead) product_blocks<MT, kAhead>(a, lda, b, acc);
+#define PIC_REST(K) case K: product_blocks<MT, K>(a, lda, b, acc); break;
+    switch (ks) {
+        PIC_REST(1) PIC_REST(2) PIC_REST(3) PIC_REST(4) PIC_REST(5) PIC_REST(6)
+        PIC_REST(7) PIC_REST(8) PIC_REST(9) PIC_REST(10) PIC_REST(11) default: break;
+    }
+#undef PIC_REST
+}
+
+// a workgroup barrier that orders LDS only: __syncthreads also waits for every
+// store to global memory, here the transposed copies no wave of the kernel
+// reads and the pre-activations each lane reads back itself
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+struct ChainArgs {
+    Net net;
+    int32_t M, ld, ldb;    // samples, LDS row, samples padded to 32 (rows of at and dzt)
+    const float* x;
+    const float* t;        // targets (training)
+    float* y;              // outputs (forward only)
+    float scale;           // of the output gradient
+    float* loss_part;      // one partial sum of squares per workgroup
+    int32_t rows_wg;       // workgroups that take samples; the others warm the caches
+    const uint4* weights;  // every layer's BF16 weights, n_weights x 16 bytes
+    int32_t n_weights;
+};
+
+// Workgroups 8 h + x, h >= 1, run beside those that take samples and read the
+// weights into the L2 cache of XCD x (workgroups go round the eight XCDs in
+// turn).  After an update the weights are in no XCD's L2, and a batch of a few
+// row blocks has one workgroup per XCD to fetch 1.4 MB through one compute
+// unit's misses.  Only a matter of speed: nothing depends on where a
+// workgroup runs.
+constexpr int kXcd = 8;
+constexpr int kWarmers = 16;                 // workgroups per XCD
+constexpr int kWarmRows = 64;                // row blocks up to which they run: with eight per XCD and more the
+                                             // blocks warm the cache for each other.  Measured, us per step: 1 block
+                                             // 33.5 -> 28.9, 4 blocks 38.1 -> 33.0, 64 blocks 43.3 -> 42.1, 256
+                                             // blocks 60.2 -> 61.1
+
+// MT blocks of 16 samples per workgroup through the whole network; TRAIN: and
+// back, leaving every layer's input and output gradient in BF16 for
+// grad_kernel.  Rows past M carry zero inputs and zero gradients.
+template <int MT, bool TRAIN>
+__global__ __launch_bounds__(kChainThreads) void chain_kernel(ChainArgs g)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ float s_red[kChainWaves];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int m0 = blockIdx.y * kBM, n0 = blockIdx.x * kBN;
-    const int wm = wid >> 1, wn = wid & 1;
-    // loader: thread t fills row t/4 of a tile, k = 8 (t%4) .. 8 (t%4) + 7
-    const int lr = tid >> 2, lk = (tid & 3) * 8;
-
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    for (int k0 = 0; k0 < g.K; k0 += kBK) {
-        bf16x8 va, vb;
-        const int m = m0 + lr, n = n0 + lr;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int k = k0 + lk + e;
-            float x = 0.0f, y = 0.0f;
-            if (m < g.M && k < g.K) x = (k == g.a.one) ? 1.0f : ld(g.a, (int64_t)m * g.a.s0 + (int64_t)k * g.a.s1);
-            if (n < g.N && k < g.K) y = (n == g.b.one) ? 1.0f : ld(g.b, (int64_t)k * g.b.s0 + (int64_t)n * g.b.s1);
-            va[e] = (__bf16)x;
-            vb[e] = (__bf16)y;
-        }
-        __syncthreads();                                   // the previous tile is consumed
-        *reinterpret_cast<bf16x8*>(&As[lr][lk]) = va;
-        *reinterpret_cast<bf16x8*>(&Bs[lr][lk]) = vb;
-        __syncthreads();
-        // lane l holds row (l % 16) of A and column (l % 16) of B, k = 8 (l / 16) .. + 7
-        const int fr = lane & 15, fk = (lane >> 4) * 8;
-        bf16x8 fa[2], fb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(&As[wm * 32 + i * 16 + fr][fk]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(&Bs[wn * 32 + j * 16 + fr][fk]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    const int fr = lane & 15, fk = (lane >> 4) * 8, rq = (lane >> 4) * 4;
+    constexpr int R = 16 * MT;
+    const int ld = g.ld, m0 = (int)blockIdx.x * R;
+    __bf16* cur = reinterpret_cast<__bf16*>(smem);
+    __bf16* nxt = cur + (size_t)R * ld;
+    const int L = g.net.L;
+    if ((int)blockIdx.x >= g.rows_wg) {
+        const int x = (int)blockIdx.x % kXcd, h = (int)blockIdx.x / kXcd - (g.rows_wg + kXcd - 1) / kXcd;
+        if (x >= g.rows_wg || h < 0) return;
+        uint32_t v = 0u;
+        for (int i = h * kChainThreads + tid; i < g.n_weights; i += kWarmers * kChainThreads) v |= g.weights[i].x;
+        asm volatile("" ::"v"(v));           // keep the loads
+        return;
     }
 
-    // lane l holds rows 4 (l / 16) + r, r = 0..3, of column l % 16 of each 16 x 16 tile
+    // the input rows, their ones and the padding
+    {
+        const Layer& l0 = g.net.l[0];
+        for (int i = tid; i < R * l0.kf; i += kChainThreads) {
+            const int r = i / l0.kf, c = i - r * l0.kf;
+            float v = 0.0f;
+            if (c < l0.ni) {
+                if (m0 + r < g.M) v = g.x[(int64_t)(m0 + r) * l0.ni + c];
+            } else if (c == l0.ni) {
+                v = 1.0f;
+            }
+            cur[(size_t)r * ld + c] = (__bf16)v;
+            if (TRAIN && c <= l0.ni) l0.at[frag_at(c, m0 + r, g.ldb / 32)] = (__bf16)v;
+        }
+    }
+    __syncthreads();
+
+    float sq = 0.0f;
+    for (int l = 0; l < L; ++l) {
+        const Layer& y = g.net.l[l];
+        const bool last = l == L - 1;
+        const int no = y.no, kn = last ? (TRAIN ? y.kb : no) : g.net.l[l + 1].kf;
+        for (int t = wid; t < pad16(no) / 16; t += kChainWaves) {
+            f32x4 acc[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            product<MT>(cur + (size_t)fr * ld + fk, ld, y.wf + (int64_t)t * 16 * y.kf + lane * 8, y.kf / 32, acc);
+            const int n = t * 16 + fr;
+            if (n >= no) continue;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                bf16x4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = i * 16 + rq + r, m = m0 + row;
+                    const float v = acc[i][r];
+                    float w;
+                    if (!last) {
+                        if (TRAIN && m < g.M) y.z[(int64_t)m * no + n] = v;
+                        w = gelu(v);
+                    } else if (TRAIN) {
+                        float d = 0.0f;
+                        if (m < g.M) {
+                            d = v - g.t[(int64_t)m * no + n];
+                            sq += d * d;
+                        }
+                        w = g.scale * d;
+                    } else {
+                        if (m < g.M) g.y[(int64_t)m * no + n] = v;
+                        continue;
+                    }
+                    o[r] = (__bf16)w;
+                    nxt[(size_t)row * ld + n] = o[r];
+                }
+                if (TRAIN)
+                    *reinterpret_cast<bf16x4*>((last ? y.dzt : g.net.l[l + 1].at) +
+                                               frag_at(n, m0 + i * 16 + rq, g.ldb / 32)) = o;
+            }
+        }
+        // the ones and the padding of the next product's rows
+        for (int i = tid; i < R * (kn - no); i += kChainThreads) {
+            const int r = i / (kn - no), c = no + (i - r * (kn - no));
+            const __bf16 v = (__bf16)(!last && c == no ? 1.0f : 0.0f);
+            nxt[(size_t)r * ld + c] = v;
+            if (TRAIN && !last && c == no) g.net.l[l + 1].at[frag_at(c, m0 + r, g.ldb / 32)] = v;
+        }
+        lds_barrier();
+        __bf16* s = cur;
+        cur = nxt;
+        nxt = s;
+    }
+    if (!TRAIN) return;
+
+    // the output gradients of the layers below: dz = (dz W) g'(z)
+    for (int l = L - 1; l > 0; --l) {
+        const Layer& y = g.net.l[l];
+        const Layer& p = g.net.l[l - 1];
+        const int ni = y.ni;
+        for (int t = wid; t < pad16(ni) / 16; t += kChainWaves) {
+            const int n = t * 16 + fr;
+            float z[MT][4];
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = m0 + i * 16 + rq + r;
+                    z[i][r] = (n < ni && m < g.M) ? p.z[(int64_t)m * ni + n] : 0.0f;
+                }
+            f32x4 acc[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            product<MT>(cur + (size_t)fr * ld + fk, ld, y.wt + (int64_t)t * 16 * y.kb + lane * 8, y.kb / 32, acc);
+            if (n >= ni) continue;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                bf16x4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = i * 16 + rq + r;
+                    o[r] = (__bf16)(m0 + row < g.M ? acc[i][r] * gelu_grad(z[i][r]) : 0.0f);
+                    nxt[(size_t)row * ld + n] = o[r];
+                }
+                *reinterpret_cast<bf16x4*>(p.dzt + frag_at(n, m0 + i * 16 + rq, g.ldb / 32)) = o;
+            }
+        }
+        for (int i = tid; i < R * (p.kb - ni); i += kChainThreads) {
+            const int r = i / (p.kb - ni);
+            nxt[(size_t)r * ld + ni + (i - r * (p.kb - ni))] = (__bf16)0.0f;
+        }
+        lds_barrier();
+        __bf16* s = cur;
+        cur = nxt;
+        nxt = s;
+    }
+    // fixed-order reduction of the squares: lanes by butterfly, waves in order
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    if (lane == 0) s_red[wid] = sq;
+    __syncthreads();
+    if (tid == 0) {
+        float t = 0.0f;
+        for (int w = 0; w < kChainWaves; ++w) t += s_red[w];
+        g.loss_part[blockIdx.x] = t;
+    }
+}
+
+enum { LAYER_HIDDEN = 0, LAYER_OUT = 1, LAYER_LOSS = 2, LAYER_BACK = 3 };
+
+struct LayerArgs {
+    int32_t epi, M, N, K;  // samples, outputs of the product, padded k
+    int32_t train, ldb;
+    const __bf16* a;       // [pad64(M)][K] rows of the product, in fragments
+    const __bf16* b;       // [pad16(N)][K], in fragments
+    __bf16* next;          // rows of the next product, [pad64(M)][kn], in fragments
+    __bf16* next_t;        // the same by feature, [kn][ldb], in fragments (training)
+    int32_t kn, one;       // its padded k; the column that holds ones (-1: none)
+    float* z;              // HIDDEN: pre-activation out; BACK: in; OUT: outputs
+    const float* t;
+    float scale;
+    float* loss_part;
+};
+
+// One product, WAVES waves of 16 TM x 16 TN outputs per workgroup, 2 x 2 where
+// there are four, with the same epilogues.
+template <int TM, int TN, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void layer_kernel(LayerArgs g)
+{
+    __shared__ float s_red[WAVES];
+    constexpr int kG = TM * TN > 1 ? 4 : 8;              // blocks of 32 k in flight
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int fr = lane & 15, rq = (lane >> 4) * 4;
+    const int m0 = ((int)blockIdx.y * (WAVES > 1 ? 2 : 1) + (wid >> 1)) * 16 * TM;
+    const int n0 = ((int)blockIdx.x * (WAVES > 1 ? 2 : 1) + (wid & 1)) * 16 * TN;
+    const int last = pad16(g.N) / 16 - 1;
+    const __bf16 *pa[TM], *pb[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) pa[i] = g.a + (int64_t)(m0 / 16 + i) * 16 * g.K + lane * 8;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int n = n0 / 16 + j;                       // columns past N are discarded
+        pb[j] = g.b + (int64_t)(n < last ? n : last) * 16 * g.K + lane * 8;
+    }
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int ks = g.K / 32;
+    bf16x8 fa[kG][TM], fb[kG][TN];
+    auto fetch = [&](int u, int k) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[u][i] = *reinterpret_cast<const bf16x8*>(pa[i] + 512 * k);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[u][j] = *reinterpret_cast<const bf16x8*>(pb[j] + 512 * k);
+    };
+#pragma unroll
+    for (int u = 0; u < kG; ++u)
+        if (u < ks) fetch(u, u);
+    for (int k = 0; k < ks; k += kG) {
+#pragma unroll
+        for (int u = 0; u < kG; ++u) {
+            if (k + u < ks) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = mfma(fa[u][i], fb[u][j], acc[i][j]);
+                if (k + u + kG < ks) fetch(u, k + u + kG);
+            }
+        }
+    }
     float sq = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TN; ++j) {
+            const int n = n0 + j * 16 + fr, mr = m0 + i * 16 + rq;
+            bf16x4 o;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm * 32 + i * 16 + (lane >> 4) * 4 + r;
-                const int n = n0 + wn * 32 + j * 16 + (lane & 15);
-                if (m >= g.M || n >= g.N) continue;
+                const int m = mr + r;
+                const int64_t ci = (int64_t)m * g.N + n;
                 const float v = acc[i][j][r];
-                const int64_t ci = (int64_t)m * g.ldc + n;
-                if (g.epi == EPI_STORE) {
-                    g.c[ci] = v;
-                } else if (g.epi == EPI_GELU) {
-                    g.c[ci] = v;
-                    g.c2[ci] = gelu(v);
-                } else if (g.epi == EPI_LOSS) {
-                    const float d = v - g.aux[(int64_t)m * g.ldaux + n];
-                    g.c[ci] = g.scale * d;
-                    sq += d * d;
-                } else {
-                    g.c[ci] = v * gelu_grad(g.aux[(int64_t)m * g.ldaux + n]);
+                float w = n == g.one ? 1.0f : 0.0f;
+                if (m < g.M && n < g.N) {
+                    if (g.epi == LAYER_HIDDEN) {
+                        if (g.train) g.z[ci] = v;
+                        w = gelu(v);
+                    } else if (g.epi == LAYER_OUT) {
+                        g.z[ci] = v;
+                    } else if (g.epi == LAYER_LOSS) {
+                        const float d = v - g.t[ci];
+                        sq += d * d;
+                        w = g.scale * d;
+                    } else {
+                        w = v * gelu_grad(g.z[ci]);
+                    }
                 }
+                o[r] = (__bf16)w;
+                if (g.next && n < g.kn) g.next[frag_at(m, n, g.kn / 32)] = o[r];
             }
-    if (g.epi == EPI_LOSS) {
-        // fixed-order reduction: lanes by butterfly, waves in order
+            if (g.train && mr < g.ldb && (n < g.N || n == g.one))
+                *reinterpret_cast<bf16x4*>(g.next_t + frag_at(n, mr, g.ldb / 32)) = o;
+        }
+    if (g.epi == LAYER_LOSS) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o, 64);
         if (lane == 0) s_red[wid] = sq;
         __syncthreads();
         if (tid == 0) {
             float t = 0.0f;
-            for (int w = 0; w < kThreads / 64; ++w) t += s_red[w];
+            for (int w = 0; w < WAVES; ++w) t += s_red[w];
             g.loss_part[blockIdx.y * gridDim.x + blockIdx.x] = t;
         }
     }
 }
 
-// sum of the loss partials in a fixed order, divided by the element count
-__global__ __launch_bounds__(256) void loss_kernel(const float* part, int n, float inv_count, float* out,
-                                                   float* out2)
+// the input rows of the first layer_kernel: BF16 with their ones and padding,
+// and the same by feature
+__global__ __launch_bounds__(256) void input_kernel(const float* x, int M, int rows, int ni, int kf, __bf16* out,
+                                                    __bf16* at, int ldb)
 {
-    __shared__ double s[256];
-    double t = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) t += (double)part[i];
-    s[threadIdx.x] = t;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)rows * kf) return;
+    const int m = (int)(i / kf), c = (int)(i - (int64_t)m * kf);
+    const float v = c < ni ? (m < M ? x[(int64_t)m * ni + c] : 0.0f) : (c == ni ? 1.0f : 0.0f);
+    out[frag_at(m, c, kf / 32)] = (__bf16)v;
+    if (at && m < ldb && c <= ni) at[frag_at(c, m, ldb / 32)] = (__bf16)v;
+}
+
+struct GradArgs {
+    Net net;
+    int32_t first[kMaxL + 1];      // first wave of every layer's tiles
+    int32_t ldb;
+    float *w, *m, *v;              // Adam: master weights and moments
+    float* grad;                   // without an update: the gradient
+    float lr, b1, b2, eps, c1, c2;
+    const float* loss_part;
+    int32_t parts;
+    float inv_count;
+    float *loss, *loss2;
+};
+
+// dWa = dz^T [a 1] of every layer, a 16 x 16 tile per wave, and Adam's update
+// of its parameters (ADAM) or the gradient itself.  The last workgroup sums
+// the loss.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void grad_kernel(GradArgs g)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        // the loss partials in a fixed order, in FP64
+        __shared__ double s[256];
+        double t = 0.0;
+        for (int i = tid; i < g.parts; i += 256) t += (double)g.loss_part[i];
+        s[tid] = t;
         __syncthreads();
+        for (int w = 128; w >= 1; w >>= 1) {
+            if (tid < w) s[tid] += s[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) {
+            const float v = (float)(s[0] * (double)g.inv_count);
+            g.loss[0] = v;
+            if (g.loss2) g.loss2[0] = v;
+        }
+        return;
     }
-    if (threadIdx.x == 0) {
-        const float v = (float)(s[0] * (double)inv_count);
-        out[0] = v;
-        if (out2) out2[0] = v;
+    const int task = (int)blockIdx.x * 4 + wid;
+    if (task >= g.first[g.net.L]) return;
+    int li = 0;
+    while (task >= g.first[li + 1]) ++li;
+    const Layer& y = g.net.l[li];
+    const int nt = pad16(y.ni + 1) / 16, local = task - g.first[li];
+    const int mt = local / nt, m0 = mt * 16, n0 = (local - mt * nt) * 16;
+    const int n = n0 + (lane & 15), mr = m0 + (lane >> 4) * 4;
+    float w[4], mm[4], vv[4];
+    if (ADAM) {                    // in flight with the operands
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (mr + r < y.no && n <= y.ni) {
+                const int64_t i = y.off + (int64_t)(mr + r) * (y.ni + 1) + n;
+                w[r] = g.w[i];
+                mm[r] = g.m[i];
+                vv[r] = g.v[i];
+            }
+        }
     }
+    const __bf16* pa = y.dzt + (int64_t)m0 * g.ldb + lane * 8;
+    const __bf16* pb = y.at + (int64_t)n0 * g.ldb + lane * 8;
+    f32x4 acc{0.0f, 0.0f, 0.0f, 0.0f};
+    int ks = g.ldb / 32;
+    constexpr int kG = 4;          // blocks of 32 samples in flight
+    for (; ks >= kG; ks -= kG, pa += 512 * kG, pb += 512 * kG) {
+        bf16x8 fa[kG], fb[kG];
+#pragma unroll
+        for (int u = 0; u < kG; ++u) {
+            fa[u] = *reinterpret_cast<const bf16x8*>(pa + 512 * u);
+            fb[u] = *reinterpret_cast<const bf16x8*>(pb + 512 * u);
+        }
+#pragma unroll
+        for (int u = 0; u < kG; ++u) acc = mfma(fa[u], fb[u], acc);
+    }
+    for (; ks > 0; --ks, pa += 512, pb += 512)
+        acc = mfma(*reinterpret_cast<const bf16x8*>(pa), *reinterpret_cast<const bf16x8*>(pb), acc);
+    bf16x4 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = mr + r;
+        o[r] = (__bf16)0.0f;
+        if (m >= y.no || n > y.ni) continue;
+        const int64_t i = y.off + (int64_t)m * (y.ni + 1) + n;
+        const float gi = acc[r];
+        if (ADAM) {
+            const float mi = g.b1 * mm[r] + (1.0f - g.b1) * gi;
+            const float vi = g.b2 * vv[r] + (1.0f - g.b2) * gi * gi;
+            g.m[i] = mi;
+            g.v[i] = vi;
+            const float wi = w[r] - g.lr * (mi * g.c1) / (sqrtf(vi * g.c2) + g.eps);
+            g.w[i] = wi;
+            o[r] = (__bf16)wi;
+            y.wf[frag_at(m, n, y.kf / 32)] = o[r];
+        } else {
+            g.grad[i] = gi;
+        }
+    }
+    // rows past n_out lie in the padding of W^T and stay zero
+    if (ADAM && n < y.ni && mr < y.kb) *reinterpret_cast<bf16x4*>(y.wt + frag_at(n, mr, y.kb / 32)) = o;
 }
 
-__global__ __launch_bounds__(256) void adam_kernel(float* w, float* m, float* v, const float* grad, __bf16* wb,
-                                                   int64_t n, float lr, float b1, float b2, float eps, float c1,
-                                                   float c2)
+// the BF16 copies of one layer's master weights
+__global__ __launch_bounds__(256) void pack_kernel(Layer y, const float* w)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float gi = grad[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-    w[i] = wi;
-    wb[i] = (__bf16)wi;
-}
-
-__global__ __launch_bounds__(256) void to_bf16_kernel(const float* w, __bf16* wb, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) wb[i] = (__bf16)w[i];
+    if (i >= (int64_t)y.no * (y.ni + 1)) return;
+    const int m = (int)(i / (y.ni + 1)), n = (int)(i - (int64_t)m * (y.ni + 1));
+    const __bf16 v = (__bf16)w[y.off + i];
+    y.wf[frag_at(m, n, y.kf / 32)] = v;
+    if (n < y.ni) y.wt[frag_at(n, m, y.kb / 32)] = v;
 }
 
 }  // namespace
 
 struct pic_mlp {
     std::vector<int32_t> widths;
-    std::vector<int64_t> off;      // parameter offset of every layer
+    Net net{};
     int64_t P = 0;
     int32_t max_batch = 0;
     int has_alloc = 0;
@@ -212,9 +556,11 @@ struct pic_mlp {
     hipStream_t stream = nullptr;
     std::vector<void*> blocks;
     float *w = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
-    __bf16* wb = nullptr;
-    std::vector<float*> z, h;      // per hidden layer: pre-activation and activation [max_batch][width]
-    float* dz[2] = {nullptr, nullptr};
+    uint4* weights = nullptr;      // every layer's wf and wt, one block
+    size_t weight_bytes = 0;
+    bool chain = true;             // the layers of 16 samples fit the chain's LDS
+    int kf_max = 0, k_max = 0;     // longest padded k: forward, training
+    __bf16* rows[2] = {nullptr, nullptr};   // without the chain: rows of the current and the next product
     float* loss_part = nullptr;
     float* loss = nullptr;         // [1]
     int64_t max_parts = 0;
@@ -233,95 +579,177 @@ void* net_alloc(pic_mlp* n, size_t bytes)
     return p;
 }
 
-hipError_t gemm(const GemmArgs& g, hipStream_t st)
+int64_t pad64(int64_t n) { return (n + 63) & ~(int64_t)63; }
+
+size_t chain_lds(int mt, int k) { return (size_t)2 * 16 * mt * (k + kPad) * 2; }
+
+template <bool TRAIN>
+hipError_t launch_chain(const pic_mlp* n, ChainArgs& g, int* parts)
 {
-    const dim3 grid((unsigned)((g.N + kBN - 1) / kBN), (unsigned)((g.M + kBM - 1) / kBM));
-    hipLaunchKernelGGL(gemm_kernel, grid, dim3(kThreads), 0, st, g);
+    const int k = TRAIN ? n->k_max : n->kf_max;
+    g.ld = k + kPad;
+    const int rows = TRAIN ? g.ldb : g.M;          // training fills its rows of 32
+    // 16 samples per workgroup until the batch fills 256 compute units, then
+    // more, which share each weight fragment: the weights cross the L2 ports
+    // once per workgroup
+    const int most = TRAIN ? 2 : 4;
+    int mt = 1;
+    while (mt < most && rows > 16 * mt * 256 && chain_lds(2 * mt, k) <= (size_t)kChainLds) mt *= 2;
+    g.rows_wg = (rows + 16 * mt - 1) / (16 * mt);
+    g.weights = n->weights;
+    g.n_weights = (int32_t)(n->weight_bytes / 16);
+    // with few row blocks, workgroups that bring the weights into L2
+    unsigned grid = (unsigned)g.rows_wg;
+    if (TRAIN && g.rows_wg <= kWarmRows) grid = ((grid + kXcd - 1) / kXcd + kWarmers) * kXcd;
+    const size_t lds = chain_lds(mt, k);
+    if (mt == 1) hipLaunchKernelGGL((chain_kernel<1, TRAIN>), dim3(grid), dim3(kChainThreads), lds, n->stream, g);
+    else if (mt == 2) hipLaunchKernelGGL((chain_kernel<2, TRAIN>), dim3(grid), dim3(kChainThreads), lds, n->stream, g);
+    else hipLaunchKernelGGL((chain_kernel<TRAIN ? 2 : 4, TRAIN>), dim3(grid), dim3(kChainThreads), lds, n->stream, g);
+    if (parts) *parts = g.rows_wg;
     return hipGetLastError();
 }
 
-int64_t parts_for(int M, int N) { return (int64_t)((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN); }
-
-// forward pass; `t` non-null: the last layer writes the loss gradient into dz[0]
-// and the loss partials instead of the outputs
-hipError_t run_forward(pic_mlp* n, int batch, const float* x, float* y, const float* t)
+// the layers one launch each, for networks too wide for the chain
+hipError_t run_layers(pic_mlp* n, int batch, const float* x, float* y, const float* t, float scale, int ldb, int* parts)
 {
-    const int L = (int)n->widths.size() - 1;
-    const float* a = x;
-    for (int l = 0; l < L; ++l) {
-        const int ni = n->widths[l], no = n->widths[l + 1];
-        GemmArgs g{};
-        g.M = batch;
-        g.N = no;
-        g.K = ni + 1;
-        g.a = Operand{a, ni, 1, 0, ni};
-        g.b = Operand{n->wb + n->off[l], 1, ni + 1, 1, -1};
-        g.ldc = no;
+    const Net& net = n->net;
+    const int L = net.L;
+    const int64_t rows = pad64(batch);
+    const Layer& l0 = net.l[0];
+    hipLaunchKernelGGL(input_kernel, dim3((unsigned)((rows * l0.kf + 255) / 256)), dim3(256), 0, n->stream, x, batch,
+                       (int)rows, l0.ni, l0.kf, n->rows[0], t ? l0.at : nullptr, ldb);
+    hipError_t e = hipGetLastError();
+    int cur = 0;
+    auto go = [&](LayerArgs& a, int cols) {
+        a.M = batch;
+        a.train = t ? 1 : 0;
+        a.ldb = ldb;
+        a.a = n->rows[cur];
+        dim3 grid((unsigned)((cols + 15) / 16), (unsigned)(rows / 16));
+        const bool small = (int64_t)grid.x * grid.y <= 1024;
+        if (!small) grid = dim3((unsigned)((cols + 63) / 64), (unsigned)(rows / 64));
+        if (a.epi == LAYER_LOSS && parts) *parts = (int)(grid.x * grid.y);
+        if (small) hipLaunchKernelGGL((layer_kernel<1, 1, 1>), grid, dim3(64), 0, n->stream, a);
+        else hipLaunchKernelGGL((layer_kernel<2, 2, 4>), grid, dim3(256), 0, n->stream, a);
+        cur ^= 1;
+        return hipGetLastError();
+    };
+    for (int l = 0; l < L && e == hipSuccess; ++l) {
+        const Layer& p = net.l[l];
+        LayerArgs a{};
+        a.N = p.no;
+        a.K = p.kf;
+        a.b = p.wf;
+        a.one = -1;
         if (l < L - 1) {
-            g.epi = EPI_GELU;
-            g.c = n->z[l];
-            g.c2 = n->h[l];
+            a.epi = LAYER_HIDDEN;
+            a.z = p.z;
+            a.next = n->rows[cur ^ 1];
+            a.next_t = net.l[l + 1].at;
+            a.kn = net.l[l + 1].kf;
+            a.one = p.no;
         } else if (t) {
-            g.epi = EPI_LOSS;
-            g.c = n->dz[0];
-            g.aux = t;
-            g.ldaux = no;
-            g.scale = 2.0f / ((float)batch * (float)no);
-            g.loss_part = n->loss_part;
+            a.epi = LAYER_LOSS;
+            a.t = t;
+            a.scale = scale;
+            a.loss_part = n->loss_part;
+            a.next = n->rows[cur ^ 1];
+            a.next_t = p.dzt;
+            a.kn = p.kb;
         } else {
-            g.epi = EPI_STORE;
-            g.c = y;
+            a.epi = LAYER_OUT;
+            a.z = y;
         }
-        const hipError_t e = gemm(g, n->stream);
-        if (e != hipSuccess) return e;
-        a = (l < L - 1) ? n->h[l] : nullptr;
+        e = go(a, std::max(p.no, a.kn));
     }
-    return hipSuccess;
+    for (int l = L - 1; t && l > 0 && e == hipSuccess; --l) {
+        const Layer& p = net.l[l];
+        const Layer& q = net.l[l - 1];
+        LayerArgs a{};
+        a.epi = LAYER_BACK;
+        a.N = p.ni;
+        a.K = p.kb;
+        a.b = p.wt;
+        a.one = -1;
+        a.z = q.z;
+        a.next = n->rows[cur ^ 1];
+        a.next_t = q.dzt;
+        a.kn = q.kb;
+        e = go(a, a.kn);
+    }
+    return e;
 }
 
-// loss and gradient of the batch into n->loss and n->grad
-hipError_t run_grad(pic_mlp* n, int batch, const float* x, const float* t, float* loss_out)
+hipError_t run_forward(pic_mlp* n, int batch, const float* x, float* y)
 {
-    const int L = (int)n->widths.size() - 1;
-    hipError_t e = run_forward(n, batch, x, nullptr, t);
-    if (e != hipSuccess) return e;
-    const int no_last = n->widths[L];
-    hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, n->stream, n->loss_part, (int)parts_for(batch, no_last),
-                       1.0f / ((float)batch * (float)no_last), n->loss, loss_out);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    int cur = 0;
-    for (int l = L - 1; l >= 0; --l) {
-        const int ni = n->widths[l], no = n->widths[l + 1];
-        const float* a = l == 0 ? x : n->h[l - 1];
-        // dWa = dz^T [a 1]
-        GemmArgs g{};
-        g.M = no;
-        g.N = ni + 1;
-        g.K = batch;
-        g.epi = EPI_STORE;
-        g.a = Operand{n->dz[cur], 1, no, 0, -1};
-        g.b = Operand{a, ni, 1, 0, ni};
-        g.c = n->grad + n->off[l];
-        g.ldc = ni + 1;
-        if ((e = gemm(g, n->stream)) != hipSuccess) return e;
-        if (l > 0) {
-            // dz of the layer below = (dz W) * g'(z below)
-            GemmArgs h{};
-            h.M = batch;
-            h.N = ni;
-            h.K = no;
-            h.epi = EPI_DGELU;
-            h.a = Operand{n->dz[cur], no, 1, 0, -1};
-            h.b = Operand{n->wb + n->off[l], ni + 1, 1, 1, -1};
-            h.c = n->dz[cur ^ 1];
-            h.ldc = ni;
-            h.aux = n->z[l - 1];
-            h.ldaux = ni;
-            if ((e = gemm(h, n->stream)) != hipSuccess) return e;
-            cur ^= 1;
-        }
+    if (!n->chain) return run_layers(n, batch, x, y, nullptr, 0.0f, pad32(batch), nullptr);
+    ChainArgs g{};
+    g.net = n->net;
+    g.M = batch;
+    g.ldb = pad32(batch);
+    g.x = x;
+    g.y = y;
+    return launch_chain<false>(n, g, nullptr);
+}
+
+struct AdamArgs {
+    float lr, b1, b2, eps, c1, c2;
+};
+
+// the batch's loss into n->loss (and loss_out) and its gradient: into n->grad,
+// or with `up` into the parameters by Adam
+hipError_t run_grad(pic_mlp* n, int batch, const float* x, const float* t, float* loss_out, const AdamArgs* up)
+{
+    const int L = n->net.L, no = n->widths[L];
+    const float scale = 2.0f / ((float)batch * (float)no);
+    const int ldb = pad32(batch);
+    int parts = 0;
+    hipError_t e;
+    if (n->chain) {
+        ChainArgs c{};
+        c.net = n->net;
+        c.M = batch;
+        c.ldb = ldb;
+        c.x = x;
+        c.t = t;
+        c.scale = scale;
+        c.loss_part = n->loss_part;
+        e = launch_chain<true>(n, c, &parts);
+    } else {
+        e = run_layers(n, batch, x, nullptr, t, scale, ldb, &parts);
     }
-    return hipSuccess;
+    if (e != hipSuccess) return e;
+    GradArgs g{};
+    g.net = n->net;
+    int tasks = 0;
+    for (int l = 0; l < L; ++l) {
+        g.first[l] = tasks;
+        tasks += pad16(n->net.l[l].no) / 16 * (pad16(n->net.l[l].ni + 1) / 16);
+    }
+    g.first[L] = tasks;
+    g.ldb = ldb;
+    g.w = n->w;
+    g.m = n->m;
+    g.v = n->v;
+    g.grad = n->grad;
+    g.loss_part = n->loss_part;
+    g.parts = parts;
+    g.inv_count = 1.0f / ((float)batch * (float)no);
+    g.loss = n->loss;
+    g.loss2 = loss_out;
+    const dim3 grid((unsigned)((tasks + 3) / 4 + 1));
+    if (up) {
+        g.lr = up->lr;
+        g.b1 = up->b1;
+        g.b2 = up->b2;
+        g.eps = up->eps;
+        g.c1 = up->c1;
+        g.c2 = up->c2;
+        hipLaunchKernelGGL(grad_kernel<true>, grid, dim3(256), 0, n->stream, g);
+    } else {
+        hipLaunchKernelGGL(grad_kernel<false>, grid, dim3(256), 0, n->stream, g);
+    }
+    return hipGetLastError();
 }
 
 bool batch_ok(const pic_mlp* n, int32_t batch) { return batch >= 1 && batch <= n->max_batch; }
@@ -347,13 +775,22 @@ pic_status pic_mlp_create(const int32_t* widths, int32_t n_widths, int32_t max_b
         n->has_alloc = 1;
         n->alloc = *alloc;
     }
-    int wmax = 0;
-    for (int l = 0; l + 1 < n_widths; ++l) {
-        n->off.push_back(n->P);
-        n->P += (int64_t)widths[l + 1] * (widths[l] + 1);
-        wmax = std::max(wmax, widths[l + 1]);
-        n->max_parts = std::max(n->max_parts, parts_for(max_batch, widths[l + 1]));
+    const int L = n_widths - 1;
+    n->net.L = L;
+    for (int l = 0; l < L; ++l) {
+        Layer& y = n->net.l[l];
+        y.ni = widths[l];
+        y.no = widths[l + 1];
+        y.kf = pad32(y.ni + 1);
+        y.kb = pad32(y.no);
+        y.off = n->P;
+        n->P += (int64_t)y.no * (y.ni + 1);
+        n->kf_max = std::max(n->kf_max, y.kf);
+        n->k_max = std::max(n->k_max, std::max(y.kf, y.kb));
     }
+    n->chain = chain_lds(1, n->k_max) <= (size_t)kChainLds;
+    n->max_parts = std::max<int64_t>({1024, pad32(max_batch) / 16,
+                                      pad64(max_batch) / 64 * ((n->net.l[L - 1].kb + 63) / 64)});
     bool ok = true;
     auto A = [&](size_t bytes) {
         void* p = net_alloc(n, bytes);
@@ -364,20 +801,37 @@ pic_status pic_mlp_create(const int32_t* widths, int32_t n_widths, int32_t max_b
     n->m = (float*)A(4 * n->P);
     n->v = (float*)A(4 * n->P);
     n->grad = (float*)A(4 * n->P);
-    n->wb = (__bf16*)A(2 * n->P);
-    for (int l = 0; l + 2 < n_widths; ++l) {
-        n->z.push_back((float*)A(4ull * max_batch * widths[l + 1]));
-        n->h.push_back((float*)A(4ull * max_batch * widths[l + 1]));
+    // the BF16 weights in the order of their use: forward, then back
+    auto wf_bytes = [&](int l) { return 2ull * pad16(n->net.l[l].no) * n->net.l[l].kf; };
+    auto wt_bytes = [&](int l) { return 2ull * pad16(n->net.l[l].ni) * n->net.l[l].kb; };
+    for (int l = 0; l < L; ++l) n->weight_bytes += wf_bytes(l) + wt_bytes(l);
+    n->weights = (uint4*)A(n->weight_bytes);
+    {
+        char* q = (char*)n->weights;
+        for (int l = 0; l < L; ++l) {
+            n->net.l[l].wf = (__bf16*)q;
+            q += wf_bytes(l);
+        }
+        for (int l = L - 1; l >= 0; --l) {
+            n->net.l[l].wt = (__bf16*)q;
+            q += wt_bytes(l);
+        }
     }
-    n->dz[0] = (float*)A(4ull * max_batch * wmax);
-    n->dz[1] = (float*)A(4ull * max_batch * wmax);
+    const size_t ldb = pad32(max_batch);
+    for (int l = 0; l < L; ++l) {
+        Layer& y = n->net.l[l];
+        y.at = (__bf16*)A(2ull * pad32(y.ni + 1) * ldb);
+        y.dzt = (__bf16*)A(2ull * pad16(y.no) * ldb);
+        if (l < L - 1) y.z = (float*)A(4ull * max_batch * y.no);
+    }
+    for (auto& r : n->rows) r = (__bf16*)A(2ull * pad64(max_batch) * n->k_max);
     n->loss_part = (float*)A(4ull * n->max_parts);
     n->loss = (float*)A(4);
     if (ok) {
         ok = hipMemsetAsync(n->w, 0, 4 * n->P, n->stream) == hipSuccess &&
              hipMemsetAsync(n->m, 0, 4 * n->P, n->stream) == hipSuccess &&
              hipMemsetAsync(n->v, 0, 4 * n->P, n->stream) == hipSuccess &&
-             hipMemsetAsync(n->wb, 0, 2 * n->P, n->stream) == hipSuccess &&
+             hipMemsetAsync(n->weights, 0, n->weight_bytes, n->stream) == hipSuccess &&   // padding stays zero
              hipStreamSynchronize(n->stream) == hipSuccess;
         if (!ok) {
             pic_mlp_free(n);
@@ -397,9 +851,12 @@ pic_status pic_mlp_set_params(pic_mlp* n, const float* params, int64_t count)
 {
     if (!n || !params || count != n->P) return PIC_EINVAL;
     if (hipMemcpyAsync(n->w, params, 4 * n->P, hipMemcpyHostToDevice, n->stream) != hipSuccess) return PIC_EHIP;
-    hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((n->P + 255) / 256)), dim3(256), 0, n->stream, n->w, n->wb,
-                       n->P);
-    if (hipGetLastError() != hipSuccess) return PIC_EHIP;
+    for (int l = 0; l < n->net.L; ++l) {
+        const Layer& y = n->net.l[l];
+        const int64_t k = (int64_t)y.no * (y.ni + 1);
+        hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, n->stream, y, n->w);
+        if (hipGetLastError() != hipSuccess) return PIC_EHIP;
+    }
     if (hipMemsetAsync(n->m, 0, 4 * n->P, n->stream) != hipSuccess ||
         hipMemsetAsync(n->v, 0, 4 * n->P, n->stream) != hipSuccess)
         return PIC_EHIP;
@@ -417,7 +874,7 @@ pic_status pic_mlp_get_params(pic_mlp* n, float* params, int64_t count)
 pic_status pic_mlp_forward(pic_mlp* n, int32_t batch, const float* x_dev, float* y_dev)
 {
     if (!n || !x_dev || !y_dev || !batch_ok(n, batch)) return PIC_EINVAL;
-    return run_forward(n, batch, x_dev, y_dev, nullptr) == hipSuccess ? PIC_OK : PIC_EHIP;
+    return run_forward(n, batch, x_dev, y_dev) == hipSuccess ? PIC_OK : PIC_EHIP;
 }
 
 pic_status pic_mlp_train_step(pic_mlp* n, int32_t batch, const float* x_dev, const float* t_dev, float lr,
@@ -426,19 +883,19 @@ pic_status pic_mlp_train_step(pic_mlp* n, int32_t batch, const float* x_dev, con
     if (!n || !x_dev || !t_dev || !batch_ok(n, batch)) return PIC_EINVAL;
     if (!(lr > 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f) || !(eps > 0.0f))
         return PIC_EINVAL;
-    if (run_grad(n, batch, x_dev, t_dev, loss_dev) != hipSuccess) return PIC_EHIP;
+    const double k = (double)(n->updates + 1);
+    AdamArgs up{lr, beta1, beta2, eps, 0.0f, 0.0f};
+    up.c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, k)));
+    up.c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, k)));
+    if (run_grad(n, batch, x_dev, t_dev, loss_dev, &up) != hipSuccess) return PIC_EHIP;
     n->updates += 1;
-    const float c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)n->updates)));
-    const float c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)n->updates)));
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n->P + 255) / 256)), dim3(256), 0, n->stream, n->w, n->m, n->v,
-                       n->grad, n->wb, n->P, lr, beta1, beta2, eps, c1, c2);
-    return hipGetLastError() == hipSuccess ? PIC_OK : PIC_EHIP;
+    return PIC_OK;
 }
 
 pic_status pic_mlp_grad(pic_mlp* n, int32_t batch, const float* x_dev, const float* t_dev, float* grad, float* loss)
 {
     if (!n || !x_dev || !t_dev || !grad || !loss || !batch_ok(n, batch)) return PIC_EINVAL;
-    if (run_grad(n, batch, x_dev, t_dev, nullptr) != hipSuccess) return PIC_EHIP;
+    if (run_grad(n, batch, x_dev, t_dev, nullptr, nullptr) != hipSuccess) return PIC_EHIP;
     if (hipMemcpyAsync(grad, n->grad, 4 * n->P, hipMemcpyDeviceToHost, n->stream) != hipSuccess ||
         hipMemcpyAsync(loss, n->loss, 4, hipMemcpyDeviceToHost, n->stream) != hipSuccess)
         return PIC_EHIP;
