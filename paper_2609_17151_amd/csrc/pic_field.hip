@@ -21,7 +21,6 @@ namespace {
 
 constexpr int kFT = kFinThreads;          // finalize threads
 constexpr int kWaves = kFT / 64;
-constexpr int kBook = kFT - 64;           // first thread of the bookkeeping wave
 
 // Prefix state of a run of nodes for the nested sums of the solve: n nodes,
 // S = sum of g, P = sum over the run of the running sums of g, Q = sum over
@@ -92,6 +91,15 @@ __device__ __forceinline__ double wave_total_f64(double v)
     return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
+// a workgroup barrier that orders LDS only: __syncthreads also waits for the
+// outstanding stores to global memory, which no thread of the kernel reads back
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 }  // namespace
 
 // A step that can have births takes two workgroups per discharge that run side
@@ -123,6 +131,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     __shared__ double s_a[kMaxCells + 1];     // rho, then phi
     __shared__ double s_bc[4];                // rho at the walls
     __shared__ double s_w[kWaves];
+    __shared__ double s_src[2];               // the source's voltage and charge at the solve's time
     __shared__ Run s_run[kWaves];
 
     // ---- births, appended after the last slot in the order of their tiles --
@@ -269,13 +278,28 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
         return;
     }
 
-    if (tid >= kBook) {
-        if (lane == 0) s_w[wid] = 0.0;                  // no share of the charge sum
-        if (a.mode == kFinStep && !split) bookkeeping(false);
-    } else {
-        // ---- densities and charge (into s_a) ------------------------------------
-        double rsum = 0.0;
-        for (int i = tid; i < nn; i += kBook) {
+    const double t = a.mode == kFinExternal ? a.t_ext
+                   : (double)(ds.step + (a.mode == kFinStep ? 1 : 0)) * dc.dt;
+    // One CU's sixteen waves share four SIMDs, so work that every wave repeats
+    // costs four times its length: the source (a sine of a large argument) is
+    // left to the last wave, which has the fewest nodes, and waves without
+    // nodes skip the loops.
+    const bool node_wave = wid * 64 < nn;
+    if (wid == kWaves - 1) {
+        if (!periodic && dc.field_solve) {
+            const bool cur = dc.drive == PIC_DRIVE_CURRENT;
+            const double sv = cur ? 0.0 : source_voltage(dc, t);
+            const double sq = source_charge(dc, t);
+            if (lane == 0) {
+                s_src[0] = sv;
+                s_src[1] = sq;
+            }
+        }
+    }
+    // ---- densities and charge (into s_a) ------------------------------------
+    double rsum = 0.0;
+    if (node_wave) {
+        for (int i = tid; i < nn; i += kFT) {
             double r;
             if (a.mode == kFinExternal) {
                 r = a.rho_ext[i];
@@ -303,12 +327,12 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
             const double w = wave_total_f64(rsum);
             if (lane == 0) s_w[wid] = w;
         }
+    } else if (lane == 0) {
+        s_w[wid] = 0.0;
     }
-    __syncthreads();
+    lds_barrier();
 
     // ---- Poisson: phi[i] = phi0 + i d0 - K[i] (file header) -------------------
-    const double t = a.mode == kFinExternal ? a.t_ext
-                   : (double)(ds.step + (a.mode == kFinStep ? 1 : 0)) * dc.dt;
     double circ_qbase = 0.0;                  // circuit: the conductor's base charge of this solve
     bool win_closed = false;                  // an RF window ended with this step
     if (!periodic && tid == 0) {
@@ -316,13 +340,6 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
         s_bc[1] = s_a[nn - 1];
     }
     if (dc.field_solve) {
-        double mean = 0.0;
-        if (periodic) {
-            double tot = 0.0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) tot += s_w[w];
-            mean = tot / nn;
-        }
         // thread tid holds the consecutive nodes kNodesPerThread tid + j; only
         // the waves that hold nodes take part (one per SIMD on meshes of up to
         // 1024 nodes), each thread summing its own nodes in sequence
@@ -332,6 +349,13 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
         double g[kNodesPerThread];
         Run inc{0.0, 0.0, 0.0, 0.0};
         if (active) {
+            double mean = 0.0;
+            if (periodic) {
+                double tot = 0.0;
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) tot += s_w[w];
+                mean = tot / nn;
+            }
             Run loc{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int j = 0; j < kNodesPerThread; ++j) {
@@ -349,45 +373,61 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
             inc = wave_run_scan(loc);
             if (lane == 63) s_run[wid] = inc;
         }
-        __syncthreads();
-        // inclusive prefix over the waves, in place (the wave's reads are
-        // issued before its writes); waves without nodes count as empty runs
-        if (tid < 64) {
-            const Run v = (tid < kWaves && tid * 64 * kNodesPerThread < nn) ? s_run[tid] : Run{0.0, 0.0, 0.0, 0.0};
-            const Run vi = wave_run_scan(v);
-            if (tid < kWaves) s_run[tid] = vi;
+        lds_barrier();
+        // the runs before this wave's and all runs: up to four waves directly,
+        // in the association of the scan below; more by a scan over the waves
+        // (in place: the wave's reads are issued before its writes; waves
+        // without nodes count as empty runs)
+        constexpr int kFew = 4;
+        const bool few = nn <= kFew * 64 * kNodesPerThread;      // uniform
+        Run before{0.0, 0.0, 0.0, 0.0}, all = before;
+        if (!few) {
+            if (tid < 64) {
+                const Run v = (tid < kWaves && tid * 64 * kNodesPerThread < nn) ? s_run[tid] : Run{0.0, 0.0, 0.0, 0.0};
+                const Run vi = wave_run_scan(v);
+                if (tid < kWaves) s_run[tid] = vi;
+            }
+            lds_barrier();
+            all = s_run[kWaves - 1];
+            if (wid > 0) before = s_run[wid - 1];
         }
-        __syncthreads();
-        const Run all = s_run[kWaves - 1];
-        const double totS = all.S, totP = all.P;
-        double phi0, d0;
-        if (periodic) {
-            phi0 = 0.0;
-            d0 = totP / nc;                              // H = sum_{i<N} G[i]
-        } else if (dc.drive == PIC_DRIVE_VOLTAGE) {
-            phi0 = source_voltage(dc, t);
-            d0 = (totP - totS - phi0) / nc;              // H = P - G[N], phi[N] = 0
-        } else {
-            // external circuit: psi (phi0 = 0) has phi[1] = (P - G[N]) / N; its
-            // surface field at x = 0 by Gauss's law over the half cell; then
-            // q = eps0 (E0[psi] + phi0 / L) + C (phi0 - V) gives phi0
-            const double e0psi = -((totP - totS) / nc) * dc.inv_dx - s_bc[0] * dc.wall_coef;
-            const bool capd = dc.drive == PIC_DRIVE_CAPACITOR;
-            const double C = capd ? dc.cap : 0.0;
-            const double v = capd ? source_voltage(dc, t) : 0.0;
-            const double qc = collected_charge(dc, d.cnt + (size_t)b * S * kRep * C_N, S);
-            const double qs = source_charge(dc, t);
-            // first solve: the electrode starts at the source's potential
-            const double qb = ds.circ_init ? ds.qbase : dc.eps0 * (v / dc.L + e0psi) - qs - qc;
-            phi0 = (C * v + (qb + qs + qc) - dc.eps0 * e0psi) / (C + dc.eps0 / dc.L);
-            d0 = (totP - totS - phi0) / nc;
-            circ_qbase = qb;
-        }
-        // zero-mean gauge of a periodic mesh: the sum of phi[i] is
-        // d0 N (N - 1) / 2 minus the sum of K[i], and the K[i] = P_incl[i] - G[i]
-        // sum to Q - P over all nodes
-        const double pm = periodic ? (d0 * (0.5 * (double)nn * (double)(nn - 1)) - (all.Q - all.P)) / nn : 0.0;
+        double phi0 = 0.0, d0 = 0.0;
         if (active) {
+            if (few) {
+                const int nw = (nn + 64 * kNodesPerThread - 1) / (64 * kNodesPerThread);
+                const Run zero{0.0, 0.0, 0.0, 0.0};
+                const Run r0 = s_run[0], r1 = nw > 1 ? s_run[1] : zero, r2 = nw > 2 ? s_run[2] : zero,
+                          r3 = nw > 3 ? s_run[3] : zero;
+                const Run p1 = run_combine(r0, r1), p2 = run_combine(r0, run_combine(r1, r2));
+                all = run_combine(p1, run_combine(r2, r3));
+                if (wid > 0) before = wid == 1 ? r0 : (wid == 2 ? p1 : p2);
+            }
+            const double totS = all.S, totP = all.P;
+            if (periodic) {
+                d0 = totP / nc;                              // H = sum_{i<N} G[i]
+            } else if (dc.drive == PIC_DRIVE_VOLTAGE) {
+                phi0 = s_src[0];
+                d0 = (totP - totS - phi0) / nc;              // H = P - G[N], phi[N] = 0
+            } else {
+                // external circuit: psi (phi0 = 0) has phi[1] = (P - G[N]) / N; its
+                // surface field at x = 0 by Gauss's law over the half cell; then
+                // q = eps0 (E0[psi] + phi0 / L) + C (phi0 - V) gives phi0
+                const double e0psi = -((totP - totS) / nc) * dc.inv_dx - s_bc[0] * dc.wall_coef;
+                const bool capd = dc.drive == PIC_DRIVE_CAPACITOR;
+                const double C = capd ? dc.cap : 0.0;
+                const double v = s_src[0];
+                const double qc = collected_charge(dc, d.cnt + (size_t)b * S * kRep * C_N, S);
+                const double qs = s_src[1];
+                // first solve: the electrode starts at the source's potential
+                const double qb = ds.circ_init ? ds.qbase : dc.eps0 * (v / dc.L + e0psi) - qs - qc;
+                phi0 = (C * v + (qb + qs + qc) - dc.eps0 * e0psi) / (C + dc.eps0 / dc.L);
+                d0 = (totP - totS - phi0) / nc;
+                circ_qbase = qb;
+            }
+            // zero-mean gauge of a periodic mesh: the sum of phi[i] is
+            // d0 N (N - 1) / 2 minus the sum of K[i], and the K[i] = P_incl[i] - G[i]
+            // sum to Q - P over all nodes
+            const double pm = periodic ? (d0 * (0.5 * (double)nn * (double)(nn - 1)) - (all.Q - all.P)) / nn : 0.0;
             // the runs before this thread: the waves before, then the lanes before
             Run lx;
             lx.n = __shfl_up(inc.n, 1, 64);
@@ -395,7 +435,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
             lx.P = __shfl_up(inc.P, 1, 64);
             lx.Q = 0.0;
             if (lane == 0) lx = Run{0.0, 0.0, 0.0, 0.0};
-            const Run ex = wid > 0 ? run_combine(s_run[wid - 1], lx) : lx;
+            const Run ex = wid > 0 ? run_combine(before, lx) : lx;
             // every read of rho was before the barrier after the wave scans
             double G = ex.S, P = ex.P;
 #pragma unroll
@@ -411,12 +451,14 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
             }
         }
     } else {
-        __syncthreads();                                 // the wall charges are read
+        lds_barrier();                                   // the wall charges are read
         for (int i = tid; i < nn; i += kFT) s_a[i] = 0.0;
     }
-    __syncthreads();
+    lds_barrier();
+    // counts and ids while the other waves form the field
+    if (wid == kWaves - 1 && a.mode == kFinStep && !split) bookkeeping(false);
 
-    // ---- field at the nodes (all threads) ------------------------------------
+    // ---- field at the nodes, and the cells' pairs for the gather ---------------
     auto efield = [&](int i) -> double {
         if (!dc.field_solve) return 0.0;
         if (periodic) {
@@ -427,30 +469,34 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
         if (i == nn - 1) return -(s_a[nn - 1] - s_a[nn - 2]) * dc.inv_dx + s_bc[1] * dc.wall_coef;
         return (s_a[i - 1] - s_a[i + 1]) * dc.inv_2dx;
     };
-    double fe_loc = 0.0;
-    for (int i = tid; i < nn; i += kFT) {
-        const double e = efield(i);
-        const double vol = (!periodic && (i == 0 || i == nn - 1)) ? 0.5 : 1.0;
-        fe_loc += e * e * vol;
-        if (a.mode == kFinExternal) {
-            if (a.phi_out) a.phi_out[i] = s_a[i];
-            if (a.e_out) a.e_out[i] = e;
-        } else {
-            d.phi[nb + i] = s_a[i];
-            d.ef[nb + i] = e;
+    if (node_wave) {
+        double fe_loc = 0.0;
+        for (int i = tid; i < nn; i += kFT) {
+            const double e = efield(i);
+            const double vol = (!periodic && (i == 0 || i == nn - 1)) ? 0.5 : 1.0;
+            fe_loc += e * e * vol;
+            if (a.mode == kFinExternal) {
+                if (a.phi_out) a.phi_out[i] = s_a[i];
+                if (a.e_out) a.e_out[i] = e;
+            } else {
+                d.phi[nb + i] = s_a[i];
+                d.ef[nb + i] = e;
+                if (i < nc)
+                    d.epair[(size_t)b * d.cells_max + i] =
+                        make_float2((float)e, (float)efield(periodic && i + 1 == nc ? 0 : i + 1));
+            }
+        }
+        // field energy: per-wave sums, added in wave order
+        if (a.mode != kFinExternal) {
+            fe_loc = wave_total_f64(fe_loc);
+            if (lane == 0) s_w[wid] = fe_loc;
         }
     }
     if (a.mode == kFinExternal) return;
-    for (int c = tid; c < nc; c += kFT) {
-        const int c1 = (periodic && c + 1 == nc) ? 0 : c + 1;
-        d.epair[(size_t)b * d.cells_max + c] = make_float2((float)efield(c), (float)efield(c1));
-    }
-    // field energy: per-wave sums, added in wave order
-    fe_loc = wave_total_f64(fe_loc);
-    if (lane == 0) s_w[wid] = fe_loc;
 
     // ---- time averages -------------------------------------------------------
     if (a.mode == kFinStep && a.diag) {
+        __syncthreads();                                 // the densities are read back
         double* av = d.avg + (size_t)b * (S + 2) * d.nodes_max;
         unsigned long long* ea = d.eacc + nb;
         const double ecoef = dc.dens_coef[0] * kDepScale / 1048576.0;   // w / dx / 2^20
@@ -535,10 +581,10 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
             win_closed = true;
         }
     }
-    __syncthreads();
+    lds_barrier();
     if (tid == 0) {
         double fe = 0.0;
-        for (int w = 0; w < kWaves; ++w) fe += s_w[w];
+        for (int w = 0; w < kWaves && w * 64 < nn; ++w) fe += s_w[w];
         ds.fe = 0.5 * dc.eps0 * dc.dx * fe;
         if (!periodic && dc.field_solve && dc.drive != PIC_DRIVE_VOLTAGE && !ds.circ_init) {
             ds.qbase = circ_qbase;
