@@ -25,7 +25,7 @@ BYTES_PER_PARTICLE_STEP = 32
 PUSH_SOURCES = ("pic_push_kernel.h", "pic_push_inst.h", "pic_push_vm2.hip", "pic_push.hip", "pic_device.h", "pic_internal.h")
 COUNTERS = os.path.join(ROOT, "profiles", "push_kernel_exb_counters.txt")
 STATS = os.path.join(ROOT, "profiles", "push_kernel_exb_stats.txt")
-PUSH_KERNEL = "push_kernel<4, 1024, false, false, 2>"
+PUSH_KERNEL = "push_kernel<4, 1024, false, false, 2, false>"
 
 
 _TOKENS = re.compile(r'"(?:\\.|[^"\\\n])*"|\'(?:\\.|[^\'\\\n])*\'|//[^\n]*|/\*.*?\*/', re.S)

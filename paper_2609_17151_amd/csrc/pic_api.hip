@@ -519,6 +519,7 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
         return p;
     };
     // particle storage
+    std::vector<char*> seg_base((size_t)B * S, nullptr);
     for (int b = 0; b < B && rc == PIC_OK; ++b) {
         const pic_config& c = cfg[b];
         DisConst& dc = ctx->disc[b];
@@ -570,13 +571,18 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
             const int64_t cap = pad_cap(c.species[s].capacity);
             sc.cap = c.species[s].capacity;
             ctx->grid_cap[s] += cap;
-            for (int k = 0; k < 2; ++k) {        // the compaction and the sort write the other copy
-                sc.cell[k] = (int32_t*)A(cap * 4);
-                sc.off[k] = (float*)A(cap * 4);
-                sc.vx[k] = (float*)A(cap * 4);
-                sc.vy[k] = (float*)A(cap * 4);
-                sc.vz[k] = (float*)A(cap * 4);
-                sc.id[k] = (uint32_t*)A(cap * 4);
+            // both copies (the compaction and the sort write the other one) in
+            // one block
+            char* q = (char*)A((size_t)2 * kFields * cap * 4);
+            seg_base[b * S + s] = q;
+            for (int k = 0; k < 2 && q; ++k) {
+                char* f = q + (size_t)k * kFields * cap * 4;
+                sc.cell[k] = (int32_t*)f;
+                sc.off[k] = (float*)(f + cap * 4);
+                sc.vx[k] = (float*)(f + 2 * cap * 4);
+                sc.vy[k] = (float*)(f + 3 * cap * 4);
+                sc.vz[k] = (float*)(f + 4 * cap * 4);
+                sc.id[k] = (uint32_t*)(f + 5 * cap * 4);
                 sc.z[k] = c.renew_lz > 0.0 ? (double*)A(cap * 8) : nullptr;
             }
             fill_push_consts(c, s, sc);
@@ -636,6 +642,8 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
             ss[b * S + s].count = n;
             ss[b * S + s].live = n;
             ss[b * S + s].next_id = (uint32_t)n;
+            ss[b * S + s].base = seg_base[b * S + s];
+            ss[b * S + s].stride = pad_cap(sp.capacity) * 4;
         }
     std::vector<DisState> ds(B);
     std::memset(ds.data(), 0, ds.size() * sizeof(DisState));
@@ -825,7 +833,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     const int T = p.threads * p.ppt;
     int64_t tiles = 0;
     for (int g = 0; g < B * S; ++g) tiles += (pad_cap(ctx->segc[g].cap) + T - 1) / T;
-    const int64_t resident = (int64_t)push_occupancy(p.ppt, p.threads, p.general, p.fuse, p.vm, lds) * ctx->n_cu;
+    const int64_t resident = (int64_t)push_occupancy(p.ppt, p.threads, p.general, p.fuse, p.vm, ctx->diag != 0, lds) * ctx->n_cu;
     p.grid = std::max<int64_t>(1, std::min(std::min(tiles, resident), (int64_t)kMaxPushGrid));
     PushArgs& pa = p.pa;
     pa.d = ctx->d;

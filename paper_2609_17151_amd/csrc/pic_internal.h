@@ -40,6 +40,8 @@ constexpr int kPow = 5;                                     // power time sums p
 // 8e6 (in the Infinity Cache) 66.2 -> 54.5 us; with axial renewal 111 -> 95 us.
 constexpr int kUseY = 1, kUseZ = 2;
 
+constexpr int kFields = 6;                 // particle arrays of a segment: cell, off, vx, vy, vz, id
+
 // latched device flags
 constexpr uint32_t kFlagCapacity = 1u << 0;
 constexpr uint32_t kFlagNumeric = 1u << 1;
@@ -149,8 +151,18 @@ struct SegState {
     int64_t tile_first, ntiles;  // tile range of the current step (tiles are numbered over all segments)
     uint32_t next_id;
     int32_t parity;         // which copy holds the particles
+    char* base;             // the segment's storage, SegConst's arrays in one block: copy p of field f (cell, off,
+    int64_t stride;         // vx, vy, vz, id) at base + (p kFields + f) stride bytes; constant, beside the count so
+                            // that the push reads where the particles are in one round
     double ke;              // time-centred kinetic energy of the last step
 };
+
+// the discharge of segment g, g < PIC_MAX_BATCH S (S = 1 .. 4; exact for S = 3
+// up to g = 1023)
+__host__ __device__ inline int seg_discharge(int g, int S)
+{
+    return S == 2 ? g >> 1 : (S == 1 ? g : (S == 4 ? g >> 2 : (g * 683) >> 11));
+}
 
 // mutable, one per discharge
 struct DisState {

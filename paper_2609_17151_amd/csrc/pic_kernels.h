@@ -72,7 +72,7 @@ template <int VM>
 hipError_t launch_push_vm(const PushArgs& a, int ppt, int threads, bool general, bool fuse, int64_t grid,
                           hipStream_t st);
 template <int VM>
-int push_occupancy_vm(int ppt, int threads, bool general, bool fuse, size_t lds);
+int push_occupancy_vm(int ppt, int threads, bool general, bool fuse, bool diag, size_t lds);
 // whether a push of this shape can do its workgroups' own events
 bool push_fusable(int ppt, int threads, bool general);
 void push_shape(int& ppt, int& threads, bool general);
@@ -92,6 +92,6 @@ int64_t compact_tiles_for(int64_t padded_count);
 size_t sort_scratch_bytes(int64_t max_tiles, int B, int cells_max);
 int64_t sort_tiles_for(int64_t padded_count);
 size_t push_lds_bytes(int n_nodes, int n_cells, int diag);
-int push_occupancy(int ppt, int threads, bool general, bool fuse, int vm, size_t lds);
+int push_occupancy(int ppt, int threads, bool general, bool fuse, int vm, bool diag, size_t lds);
 
 }  // namespace pic

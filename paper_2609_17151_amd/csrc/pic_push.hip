@@ -76,7 +76,7 @@ __global__ __launch_bounds__(BS) void events_kernel(EvArgs a)
         const uint32_t nx = ck + stride;
         uint4 rec_n = make_uint4(0u, 0u, 0u, 0u), rq_n = rec_n;
         const bool act_n = nx < nchunk && records(nx, rec_n, rq_n);
-        event_chunk(d, s_pref, NS, e, act, rec, rq);
+        event_chunk(d, s_pref, e, act, rec, rq);
         rec = rec_n;
         rq = rq_n;
         act = act_n;
@@ -123,13 +123,13 @@ hipError_t launch_push(const PushArgs& a, int ppt, int threads, bool general, bo
     }
 }
 
-int push_occupancy(int ppt, int threads, bool general, bool fuse, int vm, size_t lds)
+int push_occupancy(int ppt, int threads, bool general, bool fuse, int vm, bool diag, size_t lds)
 {
     switch (vm) {
-        case 0: return push_occupancy_vm<0>(ppt, threads, general, fuse, lds);
-        case kUseY: return push_occupancy_vm<kUseY>(ppt, threads, general, fuse, lds);
-        case kUseZ: return push_occupancy_vm<kUseZ>(ppt, threads, general, fuse, lds);
-        default: return push_occupancy_vm<kUseY | kUseZ>(ppt, threads, general, fuse, lds);
+        case 0: return push_occupancy_vm<0>(ppt, threads, general, fuse, diag, lds);
+        case kUseY: return push_occupancy_vm<kUseY>(ppt, threads, general, fuse, diag, lds);
+        case kUseZ: return push_occupancy_vm<kUseZ>(ppt, threads, general, fuse, diag, lds);
+        default: return push_occupancy_vm<kUseY | kUseZ>(ppt, threads, general, fuse, diag, lds);
     }
 }
 

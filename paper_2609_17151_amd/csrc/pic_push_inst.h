@@ -31,7 +31,8 @@ hipError_t launch_push_vm<PIC_PUSH_VM>(const PushArgs& a, int ppt, int threads, 
     const dim3 g((unsigned)grid);
 #define PIC_LAUNCH(P, B, G, F)                                                                       \
     if (ppt == P && threads == B && general == G && fuse == F) {                                     \
-        hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM>), g, dim3(B), lds, st, a);         \
+        if (a.diag) hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM, true>), g, dim3(B), lds, st, a); \
+        else hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM, false>), g, dim3(B), lds, st, a);       \
         return hipGetLastError();                                                                    \
     }
     PIC_KERNELS(PIC_LAUNCH)
@@ -40,14 +41,16 @@ hipError_t launch_push_vm<PIC_PUSH_VM>(const PushArgs& a, int ppt, int threads, 
 }
 
 template <>
-int push_occupancy_vm<PIC_PUSH_VM>(int ppt, int threads, bool general, bool fuse, size_t lds)
+int push_occupancy_vm<PIC_PUSH_VM>(int ppt, int threads, bool general, bool fuse, bool diag, size_t lds)
 {
     int nb = 0;
 #define PIC_OCC(P, B, G, F)                                                                                  \
     if (ppt == P && threads == B && general == G && fuse == F) {                                             \
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(                                                    \
-                &nb, reinterpret_cast<const void*>(push_kernel<P, B, G, F, PIC_PUSH_VM>), B, lds) !=         \
-            hipSuccess)                                                                                      \
+                &nb,                                                                                         \
+                diag ? reinterpret_cast<const void*>(push_kernel<P, B, G, F, PIC_PUSH_VM, true>)             \
+                     : reinterpret_cast<const void*>(push_kernel<P, B, G, F, PIC_PUSH_VM, false>),           \
+                B, lds) != hipSuccess)                                                                       \
             nb = 0;                                                                                          \
     }
     PIC_KERNELS(PIC_OCC)

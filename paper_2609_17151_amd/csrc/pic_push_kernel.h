@@ -169,27 +169,37 @@ constexpr int kEvSegShift = 20;             // the particle's segment (kMaxSeg <
 static_assert(kMaxSeg <= 1024, "the event word holds the segment in 10 bits");
 static_assert(C_N <= 64, "the flush's counters are held by one wave's lanes");
 
-// The constants of a tile's segment that the particle loop reads, copied to
-// registers once per tile.  The segment index is made wave-uniform, so these
-// are scalar loads; read through the segment's structure instead, every
-// particle would reload them, since the loop's atomics could alias them.
+// The constants of a segment that the particle loop reads: loaded with the
+// first tile's particles when a workgroup comes to the segment, then held in
+// scalar registers (the segment is the same for the whole workgroup) until the
+// next one.
 struct PushC {
     int nc, periodic, emits, nch;
-    uint32_t t32, key0, key1;
-    float ex, ey, ez, qmh, tx, ty, tz, sx, sy, sz, dtdx, hme, wedf_inv_bin, mscale1, mscale2;
+    uint32_t t32, key0, key1, step;
+    float ex, ey, ez, qmh, tx, ty, tz, sx, sy, sz, dtdx;
+    float hme, mscale1, mscale2;             // diagnostics
     int bulk_lo, bulk_hi;
+    double renew_lz, dt_d;
 };
 
-__device__ __forceinline__ PushC push_consts(const SegConst& sc, const DisConst& dc)
+__device__ __forceinline__ int sgpr(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint32_t sgpr(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ float sgpr(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ double sgpr(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((uint64_t)sgpr((uint32_t)(u >> 32)) << 32) | sgpr((uint32_t)u)));
+}
+
+template <bool GENERAL, int VM, bool DIAG>
+__device__ __forceinline__ PushC push_consts(const SegConst& sc, const DisConst& dc, const DisState& ds)
 {
     PushC k;
     k.nc = dc.n_cells;
     k.periodic = dc.bc == PIC_BC_PERIODIC;
-    k.emits = sc.emits;
-    k.nch = sc.nch;
-    k.t32 = sc.t32;
-    k.key0 = dc.key0;
-    k.key1 = dc.key1;
     k.ex = sc.eext[0];
     k.ey = sc.eext[1];
     k.ez = sc.eext[2];
@@ -201,33 +211,100 @@ __device__ __forceinline__ PushC push_consts(const SegConst& sc, const DisConst&
     k.sy = sc.sv[1];
     k.sz = sc.sv[2];
     k.dtdx = sc.dtdx;
-    k.hme = sc.half_m_over_e;
-    k.wedf_inv_bin = sc.wedf_inv_bin;
-    k.mscale1 = sc.mscale1;
-    k.mscale2 = sc.mscale2;
-    k.bulk_lo = dc.bulk_lo;
-    k.bulk_hi = dc.bulk_hi;
+    if (GENERAL) {
+        k.emits = sc.emits;
+        k.nch = sc.nch;
+        k.t32 = sc.t32;
+        k.key0 = dc.key0;
+        k.key1 = dc.key1;
+        k.step = (uint32_t)ds.step;
+        if (VM & kUseZ) {                    // renewal sums vz
+            k.renew_lz = sc.renew_lz;
+            k.dt_d = sc.dt_d;
+        }
+    }
+    if (DIAG) {
+        k.hme = sc.half_m_over_e;
+        k.mscale1 = sc.mscale1;
+        k.mscale2 = sc.mscale2;
+        k.bulk_lo = dc.bulk_lo;
+        k.bulk_hi = dc.bulk_hi;
+    }
     return k;
 }
 
-// A particle's step in the push: gather, Boris push, cell-relative move,
-// periodic wrap or absorption, and the collision test.  Returns whether the
-// particle stays; `ev` collects its event bits (the collision itself, the
-// secondary emission and the renewal are the events pass's).
-template <bool GENERAL, int VM>
-__device__ __forceinline__ bool advance(const DevPtrs& d, const PushC& k, const PushArgs& a, int s, int b,
-                                        uint32_t step, const float2* ep, unsigned int* s_cnt,
-                                        unsigned long long* s_wen, int& c, float& f, float& ux, float& uy,
-                                        float& uz, const float* p_vy, const float* p_vz, int64_t slot,
-                                        uint32_t pid, float& ke_sum, uint32_t& ev)
+template <bool GENERAL, int VM, bool DIAG>
+__device__ __forceinline__ PushC push_consts_sgpr(const PushC& v)
+{
+    PushC k;
+    k.nc = sgpr(v.nc);
+    k.periodic = sgpr(v.periodic);
+    k.ex = sgpr(v.ex);
+    k.qmh = sgpr(v.qmh);
+    k.dtdx = sgpr(v.dtdx);
+    if (VM & kUseY) k.ey = sgpr(v.ey);
+    if (VM & kUseZ) k.ez = sgpr(v.ez);
+    if (VM == (kUseY | kUseZ)) {
+        k.tx = sgpr(v.tx);
+        k.sx = sgpr(v.sx);
+    }
+    if (VM & kUseZ) {
+        k.ty = sgpr(v.ty);
+        k.sy = sgpr(v.sy);
+    }
+    if (VM & kUseY) {
+        k.tz = sgpr(v.tz);
+        k.sz = sgpr(v.sz);
+    }
+    if (GENERAL) {
+        k.emits = sgpr(v.emits);
+        k.nch = sgpr(v.nch);
+        k.t32 = sgpr(v.t32);
+        k.key0 = sgpr(v.key0);
+        k.key1 = sgpr(v.key1);
+        k.step = sgpr(v.step);
+        if (VM & kUseZ) {
+            k.renew_lz = sgpr(v.renew_lz);
+            k.dt_d = sgpr(v.dt_d);
+        }
+    }
+    if (DIAG) {
+        k.hme = sgpr(v.hme);
+        k.mscale1 = sgpr(v.mscale1);
+        k.mscale2 = sgpr(v.mscale2);
+        k.bulk_lo = sgpr(v.bulk_lo);
+        k.bulk_hi = sgpr(v.bulk_hi);
+    }
+    return k;
+}
+
+// A float that holds an integer, as a 64-bit word: one conversion where it
+// fits 32 bits, which the sampled moments and energies do but for extreme
+// particles; the general conversion takes ten times as many instructions.
+__device__ __forceinline__ unsigned long long fixed_i64(float r)
+{
+    if (fabsf(r) < 2147483648.0f) return (unsigned long long)(long long)(int)r;
+    return (unsigned long long)(long long)r;
+}
+
+__device__ __forceinline__ unsigned long long fixed_u64(float r)
+{
+    if (r < 4294967296.0f) return (unsigned long long)(uint32_t)r;
+    return (unsigned long long)r;
+}
+
+// Gather, Boris push and cell-relative move of one particle, without a branch:
+// the few particles that need more (a wall, a corrupt or non-finite state) are
+// found by their results afterwards.  Returns whether the cell was out of
+// range (the particle is parked in cell 0).
+template <int VM, bool DIAG>
+__device__ __forceinline__ bool advance(const PushC& k, const float2* ep, int& c, float& f, float& ux, float& uy,
+                                        float& uz, float& ke)
 {
     constexpr bool UY = (VM & kUseY) != 0, UZ = (VM & kUseZ) != 0;
-    const int nc = k.nc;
-    if ((unsigned)c >= (unsigned)nc) {     // corrupt state: latch, park the particle
-        atomicOr(&d.diss[b].flags, kFlagCell);
-        c = 0;
-        f = 0.0f;
-    }
+    const bool c_bad = (unsigned)c >= (unsigned)k.nc;
+    c = c_bad ? 0 : c;
+    f = c_bad ? 0.0f : f;
     // gather
     const float2 e2 = ep[c];
     const float ex = e2.x + f * (e2.y - e2.x) + k.ex;
@@ -235,7 +312,7 @@ __device__ __forceinline__ bool advance(const DevPtrs& d, const PushC& k, const 
     // change nor read (VM) is left out: its terms in the others' rotation are
     // products with zero, so the rest is the same, bit for bit.
     const float qmh = k.qmh;
-    const float vold2 = a.diag ? ux * ux + uy * uy + uz * uz : 0.0f;
+    const float vold2 = DIAG ? ux * ux + uy * uy + uz * uz : 0.0f;
     ux += qmh * ex;
     if (UY) uy += qmh * k.ey;
     if (UZ) uz += qmh * k.ez;
@@ -262,61 +339,30 @@ __device__ __forceinline__ bool advance(const DevPtrs& d, const PushC& k, const 
     ux += qmh * ex;
     if (UY) uy += qmh * k.ey;
     if (UZ) uz += qmh * k.ez;
-    if (a.diag) ke_sum += vold2 + (ux * ux + uy * uy + uz * uz);
+    ke = DIAG ? vold2 + (ux * ux + uy * uy + uz * uz) : 0.0f;
     // move, relative to the cell
     f += ux * k.dtdx;
     const float fl = floorf(f);
     c += (int)fl;
     f -= fl;
-    if (f >= 1.0f) {
-        f -= 1.0f;
-        c += 1;
-    }
-    if (!(f >= 0.0f && f < 1.0f) || !(fabsf(ux) < 3.0e38f)) {   // non-finite state
-        atomicOr(&d.diss[b].flags, kFlagNumeric);
-        f = 0.0f;
-        c = 0;
-        ux = uy = uz = 0.0f;
-        if (!UY) const_cast<float*>(p_vy)[slot] = 0.0f;
-        if (!UZ) const_cast<float*>(p_vz)[slot] = 0.0f;
-    }
-    if (k.periodic) {
-        if (c < 0) c += nc;
-        else if (c >= nc) c -= nc;
-        if ((unsigned)c >= (unsigned)nc) {                     // moved more than the domain
-            atomicOr(&d.diss[b].flags, kFlagCell);
-            c = 0;
-            f = 0.0f;
-        }
-        if (!GENERAL) return true;
-    } else if (c < 0 || c >= nc) {
-        const int wall = c < 0 ? 0 : 1;
-        // components the push does not carry are read for the few particles
-        // that reach a wall
-        const float wy = (UY || a.diag) ? uy : p_vy[slot];
-        const float wz = (UZ || a.diag) ? uz : p_vz[slot];
-        const float vnew2 = ux * ux + wy * wy + wz * wz;
-        atomicAdd(&s_cnt[C_ABS0 + wall], 1u);
-        atomicAdd(&s_wen[wall], (unsigned long long)(k.hme * vnew2 * 1048576.0f));
-        if (a.diag) {
-            // impact energy: this species' histogram at this wall, and for
-            // electrons the wall energy distribution
-            const float eps = k.hme * vnew2;
-            const int wb = (int)(eps * k.wedf_inv_bin);
-            if ((unsigned)wb < (unsigned)kEepfBins)
-                atomicAdd(&d.wedf[(((size_t)b * d.S + s) * 2 + wall) * kEepfBins + wb], 1ull);
-            const int bin = (int)(eps * a.eepf_inv_bin);
-            if (s == 0 && (unsigned)bin < (unsigned)kEepfBins)
-                atomicAdd(&d.eepf[((size_t)b * 2 + 1) * kEepfBins + bin], 1ull);
-        }
-        if (GENERAL && k.emits) ev = kEvSee | (wall ? kEvWall1 : 0u);
-        return false;
-    }
-    if (!GENERAL || k.nch == 0) return true;
-    // null-collision Monte Carlo: integer candidate test on the first draw
-    const uint4 r = philox10(pid, step, ((uint32_t)s << 24), 0u, k.key0, k.key1);
-    if (r.x < k.t32) ev |= kEvCand;
-    return true;
+    const bool up = f >= 1.0f;
+    f = up ? f - 1.0f : f;
+    c += up ? 1 : 0;
+    return c_bad;
+}
+
+// a particle whose state is not finite after its move: f is in [0, 1) or, for
+// an infinite or undefined velocity, undefined
+__device__ __forceinline__ bool not_finite(float f, float ux) { return !(f < 1.0f) || !(fabsf(ux) < 3.0e38f); }
+
+// First word of the particle's draw (the candidate test).  The round keys come
+// from scalar adds: hidden from the optimiser, which would otherwise hold all
+// twenty of them in registers across the loop and spill.
+__device__ __forceinline__ uint32_t candidate_draw(uint32_t id, const PushC& k, int s)
+{
+    uint32_t k0 = k.key0, k1 = k.key1;
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    return philox10(id, k.step, ((uint32_t)s << 24), 0u, k0, k1).x;
 }
 
 // velocity moments of a particle at the nodes, fixed point (diagnostics);
@@ -328,10 +374,10 @@ __device__ __forceinline__ void moment_diag(float ms1, float ms2, unsigned long 
     const int c1 = (periodic && c + 1 == nc) ? 0 : c + 1;
     const float a = ux * ms1, b2 = ux * ux * ms2;
     const float w0 = 1.0f - f;
-    atomicAdd(&fh[c], (unsigned long long)(long long)rintf(w0 * a));
-    atomicAdd(&fh[c1], (unsigned long long)(long long)rintf(f * a));
-    atomicAdd(&mh[c], (unsigned long long)(long long)rintf(w0 * b2));
-    atomicAdd(&mh[c1], (unsigned long long)(long long)rintf(f * b2));
+    atomicAdd(&fh[c], fixed_i64(rintf(w0 * a)));
+    atomicAdd(&fh[c1], fixed_i64(rintf(f * a)));
+    atomicAdd(&mh[c], fixed_i64(rintf(w0 * b2)));
+    atomicAdd(&mh[c1], fixed_i64(rintf(f * b2)));
 }
 
 // electron energy at the nodes and in the bulk distribution (diagnostics);
@@ -345,8 +391,8 @@ __device__ __forceinline__ void electron_diag(float hme, int lo, int hi, float e
     const float eps = hme * (ux * ux + uy * uy + uz * uz);
     const float w1 = f * eps, w0 = eps - w1;
     const int c1 = (periodic && c + 1 == nc) ? 0 : c + 1;
-    atomicAdd(&ehist[c], (unsigned long long)(w0 * 1048576.0f));
-    atomicAdd(&ehist[c1], (unsigned long long)(w1 * 1048576.0f));
+    atomicAdd(&ehist[c], fixed_u64(w0 * 1048576.0f));
+    atomicAdd(&ehist[c1], fixed_u64(w1 * 1048576.0f));
     if (c >= lo && c < hi) {
         const int bin = (int)(eps * eepf_inv_bin);
         if ((unsigned)bin < (unsigned)kEepfBins) atomicAdd(&eepf[bin], (CT)1);
@@ -434,21 +480,43 @@ struct EvPass {
 
 __device__ __forceinline__ bool event_record(const DevPtrs& d, const EvPass& ps, int g, uint32_t nev, uint32_t kc,
                                              uint4& rec, uint4& rq);
-__device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, int NS, const EvPass& ps,
-                                            bool act, uint4 rec, uint4 rq);
+__device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, const EvPass& ps, bool act,
+                                            uint4 rec, uint4 rq);
+
+// a workgroup barrier that orders LDS only: __syncthreads also waits for the
+// wave's outstanding accesses to global memory
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ int64_t readlane64(int64_t v, int l)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 
 // FUSE: the workgroup does its own tile range's events after its push (no
-// events launch; for workloads too small to fill the GPU twice)
+// events launch; for workloads too small to fill the GPU twice).
 // VM: the velocity components, besides x, that the fields change in some
-// segment of the launch (kUseY, kUseZ).
-template <int PPT, int BS, bool GENERAL, bool FUSE, int VM>
+// segment of the launch (kUseY, kUseZ).  DIAG: the step is sampled.
+//
+// A small step is a chain of dependent memory latencies, so the start keeps it
+// short: contexts of up to 64 segments read every segment's count, step and
+// place in one round, a lane each, in every wave (no LDS, no barrier); then the
+// first tile's particles, the segment's constants and the discharge's E pairs
+// are all in flight together, and one barrier later the particles are pushed.
+template <int PPT, int BS, bool GENERAL, bool FUSE, int VM, bool DIAG>
 __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
 {
     constexpr int kBS = BS;
     constexpr int T = kBS * PPT;
     constexpr bool UY = (VM & kUseY) != 0, UZ = (VM & kUseZ) != 0;
+    constexpr bool RY = UY || DIAG, RZ = UZ || DIAG;   // components read
     constexpr int kRunTiles = kDepMax / T;        // tiles one deposit histogram holds
-    const bool ry = UY || a.diag, rz = UZ || a.diag;   // components read
     constexpr int kWavesPerTile = kBS / 64;
     const DevPtrs& d = a.d;
     const int S = d.S, NS = d.B * d.S;
@@ -461,226 +529,357 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
     __shared__ float s_red[kBS / 64];
     __shared__ uint32_t s_evn;                // events recorded by the workgroup
 
-    tile_prefix(d, T, s_pref);
+    // the tiles of every segment: lane g holds segment g's row, or (more than
+    // 64 segments) the first tiles in LDS
+    const bool few = NS <= 64;
+    int64_t l_count = 0, l_base = 0, l_stride = 0;
+    int32_t l_parity = 0, l_incl = 0, NT;
+    if (few) {
+        if (lane < NS) {
+            const SegState& st = d.segs[lane];
+            l_count = st.count;
+            l_base = (int64_t)(uintptr_t)st.base;
+            l_stride = st.stride;
+            l_parity = st.parity;
+            const bool off = d.diss[seg_discharge(lane, S)].retired != 0;
+            l_incl = off ? 0 : (int32_t)((l_count + T - 1) / T);
+        }
+        for (int dd = 1; dd < NS; dd <<= 1) {
+            const int32_t o = __shfl_up(l_incl, dd, 64);
+            if (lane >= dd) l_incl += o;
+        }
+        if (wid == 0) {
+            if (lane < NS) s_pref[lane + 1] = l_incl;
+            if (lane == 0) s_pref[0] = 0;
+        }
+        NT = __builtin_amdgcn_readlane(l_incl, NS - 1);
+    } else {
+        tile_prefix(d, T, s_pref);
+        lds_barrier();
+        NT = sgpr(s_pref[NS]);
+    }
     if (tid < C_N) s_cnt[tid] = 0;
     if (tid < 2) s_wen[tid] = 0ull;
     if (tid == 0) s_evn = 0u;
-    __syncthreads();
-    const int32_t NT = s_pref[NS];
 
     // LDS layout: deposit histogram, [energy, flux and momentum-flux
     // histograms, EEPF], E pairs
     const int nn_max = a.nodes_max_dyn;
-    const int dn = a.diag ? nn_max : 0;
+    const int dn = DIAG ? nn_max : 0;
     unsigned long long* hist = reinterpret_cast<unsigned long long*>(smem);
     unsigned long long* ehist = hist + nn_max;
     unsigned long long* fhist = ehist + dn;
     unsigned long long* mhist = fhist + dn;
     unsigned int* eepf = reinterpret_cast<unsigned int*>(mhist + dn);
-    float2* ep = reinterpret_cast<float2*>(eepf + (a.diag ? kEepfBins : 0));
+    float2* ep = reinterpret_cast<float2*>(eepf + (DIAG ? kEepfBins : 0));
 
-    int cur_g = -1, cur_b = -1;
-    int32_t run_first = 0, hist_end = 0;
+    // the current segment
+    int sg = -1, b = -1, s = 0;
+    int32_t seg_first = 0, run_first = 0, hist_end = 0;
     float ke_run = 0.0f;
-    // the current segment's particle arrays and counts, read when the segment
-    // changes, so that a tile's particle loads do not wait for them
     int64_t n = 0;
-    uint32_t step = 0;
-    int32_t tile_first = 0, ntiles = 0;
-    int32_t* p_cell = nullptr;
-    float *p_off = nullptr, *p_vx = nullptr, *p_vy = nullptr, *p_vz = nullptr;
-    uint32_t* p_id = nullptr;
+    char* base_p = nullptr;                   // its particle arrays, `stride` bytes apart
+    int64_t stride = 0;
     double* p_z = nullptr;
-    double renew_lz = 0.0, dt_d = 0.0;
+    PushC k{};
     // a fixed contiguous range of tiles per workgroup
     const int32_t chunk = (NT + (int32_t)gridDim.x - 1) / (int32_t)gridDim.x;
     const int32_t t_begin = (int32_t)blockIdx.x * chunk;
     const int32_t t_end = t_begin + chunk < NT ? t_begin + chunk : NT;
+    if (t_begin >= t_end) {
+        if (GENERAL && tid == 0) d.evg[blockIdx.x] = 0u;
+        return;
+    }
+    int32_t seg_end = t_begin;
 
-    // flush the run of tiles of segment cg: deposit, diagnostics, counters,
-    // kinetic energy (ranges are fixed, so the grouping of the sums is too).
-    // The first `quiet` threads (whole waves) take part in the barriers only,
-    // so that no memory operation of the flush is outstanding in those waves
-    // when they go on to the events pass.
-    auto flush = [&](int cg, int quiet) {
-        __syncthreads();
+    // the deposit histogram's node sums go out
+    auto flush_nodes = [&](int ft, int nt) {
+        unsigned long long* acc_s = d.acc + ((size_t)sg * kRep + blockIdx.x % kRep) * d.nodes_max;
+        const int nn = k.nc + (k.periodic ? 0 : 1);
+        for (int i = ft; i < nn; i += nt) {
+            const unsigned long long v = hist_node(hist, i, k.nc, k.periodic);
+            if (v) atomicAdd(&acc_s[i], v);
+        }
+    };
+
+    // flush the run of tiles of the current segment: deposit, diagnostics,
+    // counters, kinetic energy (ranges are fixed, so the grouping of the sums
+    // is too).  The first `quiet` threads (whole waves) take part in the
+    // barriers only, so that no memory operation of the flush is outstanding
+    // in those waves when they go on to the events pass.
+    auto flush = [&](int quiet) {
         const int ft = tid - quiet, nt = kBS - quiet;
-        const int cb = cg / S, cs = cg - cb * S;
-        const DisConst& dcf = d.disc[cb];
-        const int rep = blockIdx.x % kRep;
         if (ft >= 0) {
-            unsigned long long* acc_s = d.acc + ((size_t)cg * kRep + rep) * d.nodes_max;
-            const int nc_f = dcf.n_cells, per_f = dcf.bc == PIC_BC_PERIODIC;
-            for (int i = ft; i < dcf.n_nodes; i += nt) {
-                const unsigned long long v = hist_node(hist, i, nc_f, per_f);
-                if (v) atomicAdd(&acc_s[i], v);
-            }
-            if (a.diag) {
-                unsigned long long* ma = d.macc + (size_t)cg * 2 * d.nodes_max;
-                for (int i = ft; i < dcf.n_nodes; i += nt) {
+            flush_nodes(ft, nt);
+            const int nn = k.nc + (k.periodic ? 0 : 1);
+            if (DIAG) {
+                unsigned long long* ma = d.macc + (size_t)sg * 2 * d.nodes_max;
+                for (int i = ft; i < nn; i += nt) {
                     const unsigned long long v = fhist[i], w = mhist[i];
                     if (v) atomicAdd(&ma[i], v);
                     if (w) atomicAdd(&ma[d.nodes_max + i], w);
                 }
             }
-            if (a.diag && cs == 0) {
-                unsigned long long* ea = d.eacc + (size_t)cb * d.nodes_max;
-                for (int i = ft; i < dcf.n_nodes; i += nt) {
+            if (DIAG && s == 0) {
+                unsigned long long* ea = d.eacc + (size_t)b * d.nodes_max;
+                for (int i = ft; i < nn; i += nt) {
                     const unsigned long long v = ehist[i];
                     if (v) atomicAdd(&ea[i], v);
                 }
-                unsigned long long* eg = d.eepf + (size_t)cb * 2 * kEepfBins;
+                unsigned long long* eg = d.eepf + (size_t)b * 2 * kEepfBins;
                 for (int i = ft; i < kEepfBins; i += nt) {
                     const unsigned int v = eepf[i];
                     if (v) atomicAdd(&eg[i], (unsigned long long)v);
                 }
             }
-            unsigned long long* cnt = d.cnt + ((size_t)cg * kRep + rep) * C_N;
-            if (ft < C_N) {
-                const unsigned int v = s_cnt[ft];
-                if (v) {
-                    atomicAdd(&cnt[ft], (unsigned long long)v);
-                    if (ft == C_ABS0 || ft == C_ABS1)
-                        atomicAdd(reinterpret_cast<unsigned long long*>(&d.segs[cg].dead), (unsigned long long)v);
+            if (GENERAL) {
+                unsigned long long* cnt = d.cnt + ((size_t)sg * kRep + blockIdx.x % kRep) * C_N;
+                if (ft < C_N) {
+                    const unsigned int v = s_cnt[ft];
+                    if (v) {
+                        atomicAdd(&cnt[ft], (unsigned long long)v);
+                        if (ft == C_ABS0 || ft == C_ABS1)
+                            atomicAdd(reinterpret_cast<unsigned long long*>(&d.segs[sg].dead), (unsigned long long)v);
+                    }
+                    s_cnt[ft] = 0;
                 }
-                s_cnt[ft] = 0;
-            }
-            if (ft < 2) {
-                const unsigned long long v = s_wen[ft];
-                if (v) atomicAdd(&d.wen[(size_t)cg * 2 + ft], v);
-                s_wen[ft] = 0ull;
+                if (ft < 2) {
+                    const unsigned long long v = s_wen[ft];
+                    if (v) atomicAdd(&d.wen[(size_t)sg * 2 + ft], v);
+                    s_wen[ft] = 0ull;
+                }
             }
         }
-        if (a.diag) {
+        if (DIAG) {
             const double kt = block_sum_f32<BS>(ke_run, s_red);
-            if (ft == 0) d.ke_part[run_first] = 0.5 * d.segc[cg].mw_half * kt;
+            if (ft == 0) d.ke_part[run_first] = 0.5 * d.segc[sg].mw_half * kt;
             ke_run = 0.0f;
         }
     };
 
-    // a histogram full before its run of tiles ends: its sums go out, it restarts
-    auto flush_hist = [&](int cg) {
-        __syncthreads();
-        const DisConst& dcf = d.disc[cg / S];
-        unsigned long long* acc_s = d.acc + ((size_t)cg * kRep + blockIdx.x % kRep) * d.nodes_max;
-        const int nc_f = dcf.n_cells, per_f = dcf.bc == PIC_BC_PERIODIC;
-        for (int i = tid; i < dcf.n_nodes; i += kBS) {
-            const unsigned long long v = hist_node(hist, i, nc_f, per_f);
-            if (v) atomicAdd(&acc_s[i], v);
-        }
-        __syncthreads();
-        for (int i = tid; i < nc_f; i += kBS) hist[i] = 0ull;
-        __syncthreads();
-    };
-
-    // the tile's segment, wave-uniform (its constants become scalar loads):
-    // found once, then followed along the workgroup's contiguous range
-    int sg_walk = t_begin < t_end ? tile_segment(s_pref, NS, t_begin) : 0;
     for (int32_t t = t_begin; t < t_end; ++t) {
-        while (s_pref[sg_walk + 1] <= t) ++sg_walk;
-        const int sg = __builtin_amdgcn_readfirstlane(sg_walk);
-        const int b = sg / S, s = sg - b * S;
-        const DisConst& dc = d.disc[b];
-        if (sg != cur_g) {
-            if (cur_g >= 0) flush(cur_g, 0);
-            __syncthreads();
-            if (b != cur_b) {
-                const float2* epg = d.epair + (size_t)b * d.cells_max;
-                for (int i = tid; i < dc.n_cells; i += kBS) ep[i] = epg[i];
+        const bool sw = t >= seg_end;                 // the next segment begins
+        // the next segment's values: the current ones stay until its flush
+        int sg_n = sg, b_n = b;
+        int32_t first_n = seg_first;
+        char* base_n = base_p;
+        PushC kv{};
+        if (sw) {
+            int64_t count;
+            int par;
+            if (few) {
+                sg_n = (int)__popcll(__ballot(lane < NS && l_incl <= t));
+                first_n = sg_n > 0 ? __builtin_amdgcn_readlane(l_incl, sg_n - 1) : 0;
+                seg_end = __builtin_amdgcn_readlane(l_incl, sg_n);
+                count = readlane64(l_count, sg_n);
+                base_n = (char*)(uintptr_t)readlane64(l_base, sg_n);
+                stride = readlane64(l_stride, sg_n);
+                par = __builtin_amdgcn_readlane(l_parity, sg_n);
+            } else {
+                if (sg < 0) sg_n = tile_segment(s_pref, NS, t);
+                while (s_pref[sg_n + 1] <= t) ++sg_n;
+                sg_n = sgpr(sg_n);
+                first_n = sgpr(s_pref[sg_n]);
+                seg_end = sgpr(s_pref[sg_n + 1]);
+                const SegState& st = d.segs[sg_n];
+                count = readlane64(st.count, 0);
+                base_n = (char*)(uintptr_t)readlane64((int64_t)(uintptr_t)st.base, 0);
+                stride = readlane64(st.stride, 0);
+                par = sgpr(st.parity);
             }
-            for (int i = tid; i < dc.n_nodes; i += kBS) hist[i] = 0ull;
-            if (a.diag) {
-                for (int i = tid; i < dc.n_nodes; i += kBS) {
-                    fhist[i] = 0ull;
-                    mhist[i] = 0ull;
-                }
-            }
-            if (a.diag && s == 0) {
-                for (int i = tid; i < dc.n_nodes; i += kBS) ehist[i] = 0ull;
-                for (int i = tid; i < kEepfBins; i += kBS) eepf[i] = 0u;
-            }
-            cur_g = sg;
-            cur_b = b;
-            run_first = t;
-            hist_end = t + kRunTiles;
-            const SegConst& sc = d.segc[sg];
-            const SegState& st = d.segs[sg];
-            const int io = st.parity;             // updated in place
-            n = st.count;
-            step = (uint32_t)d.diss[b].step;
-            tile_first = __builtin_amdgcn_readfirstlane(s_pref[sg]);
-            ntiles = __builtin_amdgcn_readfirstlane(s_pref[sg + 1]) - tile_first;
-            p_cell = sc.cell[io];
-            p_off = sc.off[io];
-            p_vx = sc.vx[io];
-            p_vy = sc.vy[io];
-            p_vz = sc.vz[io];
-            p_id = sc.id[io];
-            p_z = sc.z[io];
-            renew_lz = sc.renew_lz;
-            dt_d = sc.dt_d;
-            __syncthreads();
+            n = count;                                // updated in place: the copy in use
+            base_n += (int64_t)par * kFields * stride;
+            b_n = seg_discharge(sg_n, S);
+            const SegConst& sc = d.segc[sg_n];
+            if (GENERAL && UZ) p_z = sc.z[par];
+            kv = push_consts<GENERAL, VM, DIAG>(sc, d.disc[b_n], d.diss[b_n]);   // in flight with the particles
         }
-        if (t == hist_end) {
-            flush_hist(sg);
-            hist_end = t + kRunTiles;
-        }
-        const int32_t tin = t - tile_first;
-        const PushC k = push_consts(d.segc[sg], dc);   // loads in flight with the particles'
-        const int nc = k.nc;
-        const int periodic = k.periodic;
-        const int64_t base = (int64_t)tin * T + (int64_t)tid * PPT;
+        const int32_t tin = t - first_n;
+        const int64_t tile0 = (int64_t)tin * T;
+        const int rem = n - tile0 < T ? (int)(n - tile0) : T;     // slots in use
+        char* pt = base_n + tile0 * 4;
+        int32_t* p_cell = reinterpret_cast<int32_t*>(pt);
+        float* p_off = reinterpret_cast<float*>(pt + stride);
+        float* p_vx = reinterpret_cast<float*>(pt + 2 * stride);
+        float* p_vy = reinterpret_cast<float*>(pt + 3 * stride);
+        float* p_vz = reinterpret_cast<float*>(pt + 4 * stride);
+        const uint32_t* p_id = reinterpret_cast<const uint32_t*>(pt + 5 * stride);
+        const int slot0 = tid * PPT;
 
         int32_t cell[PPT];
         float off[PPT], vx[PPT], vy[PPT], vz[PPT];
         uint32_t pid[PPT];
-        vload<PPT, int4, GENERAL>(p_cell + base, cell);
-        vload<PPT, float4, GENERAL>(p_off + base, off);
-        vload<PPT, float4, GENERAL>(p_vx + base, vx);
-        if (ry) {
-            vload<PPT, float4, GENERAL>(p_vy + base, vy);
+        vload<PPT, int4, GENERAL>(p_cell + slot0, cell);
+        vload<PPT, float4, GENERAL>(p_off + slot0, off);
+        vload<PPT, float4, GENERAL>(p_vx + slot0, vx);
+        if (RY) {
+            vload<PPT, float4, GENERAL>(p_vy + slot0, vy);
         } else {
 #pragma unroll
             for (int j = 0; j < PPT; ++j) vy[j] = 0.0f;
         }
-        if (rz) {
-            vload<PPT, float4, GENERAL>(p_vz + base, vz);
+        if (RZ) {
+            vload<PPT, float4, GENERAL>(p_vz + slot0, vz);
         } else {
 #pragma unroll
             for (int j = 0; j < PPT; ++j) vz[j] = 0.0f;
         }
         // ids only where every particle draws; the events pass reads the
         // others' from their slots
-        if (GENERAL && k.nch > 0) {
-            vload<PPT, uint4, GENERAL>(p_id + base, pid);
+        if (GENERAL && (sw ? d.segc[sg_n].nch : k.nch) > 0) {
+            vload<PPT, uint4, GENERAL>(p_id + slot0, pid);
         } else {
 #pragma unroll
             for (int j = 0; j < PPT; ++j) pid[j] = 0u;
         }
+
+        if (sw) {
+            if (sg >= 0) {
+                lds_barrier();
+                flush(0);
+                lds_barrier();
+            }
+            if (b_n != b) {
+                const float2* epg = d.epair + (size_t)b_n * d.cells_max;
+                for (int i = tid; i < a.cells_max_dyn; i += kBS) ep[i] = epg[i];
+            }
+            for (int i = tid; i < nn_max; i += kBS) hist[i] = 0ull;
+            if (DIAG) {
+                for (int i = tid; i < nn_max; i += kBS) {
+                    fhist[i] = 0ull;
+                    mhist[i] = 0ull;
+                }
+            }
+            sg = sg_n;
+            b = b_n;
+            s = sg - b * S;
+            seg_first = first_n;
+            base_p = base_n;
+            run_first = t;
+            hist_end = t + kRunTiles;
+            if (DIAG && s == 0) {
+                for (int i = tid; i < nn_max; i += kBS) ehist[i] = 0ull;
+                for (int i = tid; i < kEepfBins; i += kBS) eepf[i] = 0u;
+            }
+            lds_barrier();
+            k = push_consts_sgpr<GENERAL, VM, DIAG>(kv);
+        } else if (t == hist_end) {
+            // a histogram full before its run of tiles ends
+            lds_barrier();
+            flush_nodes(tid, kBS);
+            lds_barrier();
+            for (int i = tid; i < k.nc; i += kBS) hist[i] = 0ull;
+            lds_barrier();
+            hist_end = t + kRunTiles;
+        }
         // axial renewal: the displacement along the third axis since
         // injection, summed in FP64 (a slow ion adds only a few binary32
         // spacings of z per step, so a binary32 sum would drift)
-        const bool renews = GENERAL && renew_lz > 0.0;
+        const bool renews = GENERAL && UZ && k.renew_lz > 0.0;
         double zax[PPT];
         if (renews) {
 #pragma unroll
-            for (int j = 0; j < PPT; ++j) zax[j] = p_z[base + j];
+            for (int j = 0; j < PPT; ++j) zax[j] = p_z[tile0 + slot0 + j];
         }
 
+        // All of a thread's particles go through each stage together, without
+        // branches (their chains overlap); what only few particles need is
+        // behind one test per wave.
         uint32_t evw[PPT];
-        float ke_tile = 0.0f;
+        bool keep[PPT];
+        float ke[PPT];
+        bool bad = false, odd = false;
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             evw[j] = 0u;
-            if (base + j >= n) continue;
-            if (GENERAL && cell[j] < 0) continue;          // a hole: absorbed earlier
-            const bool keep = advance<GENERAL, VM>(d, k, a, s, b, step, ep, s_cnt, s_wen, cell[j], off[j], vx[j],
-                                                   vy[j], vz[j], p_vy, p_vz, base + j, pid[j], ke_tile, evw[j]);
-            if (renews && keep) {
+            const int c0 = cell[j];
+            keep[j] = slot0 + j < rem && (!GENERAL || c0 >= 0);    // GENERAL: not a hole
+            const bool cb = advance<VM, DIAG>(k, ep, cell[j], off[j], vx[j], vy[j], vz[j], ke[j]);
+            bad |= keep[j] && cb;
+            odd |= keep[j] && not_finite(off[j], vx[j]);
+        }
+        if (__any(odd)) {
+#pragma unroll
+            for (int j = 0; j < PPT; ++j)
+                if (keep[j] && not_finite(off[j], vx[j])) {
+                    atomicOr(&d.diss[b].flags, kFlagNumeric);
+                    off[j] = 0.0f;
+                    cell[j] = 0;
+                    vx[j] = vy[j] = vz[j] = 0.0f;
+                    if (!UY) p_vy[slot0 + j] = 0.0f;
+                    if (!UZ) p_vz[slot0 + j] = 0.0f;
+                }
+        }
+        if (DIAG) {
+            float ke_tile = 0.0f;
+#pragma unroll
+            for (int j = 0; j < PPT; ++j)
+                if (keep[j]) ke_tile += ke[j];
+            ke_run += ke_tile;
+        }
+        const int nc = k.nc;
+        if (k.periodic) {
+#pragma unroll
+            for (int j = 0; j < PPT; ++j) {
+                int c = cell[j];
+                c += c < 0 ? nc : (c >= nc ? -nc : 0);
+                const bool out = (unsigned)c >= (unsigned)nc;       // moved more than the domain
+                cell[j] = out ? 0 : c;
+                off[j] = out ? 0.0f : off[j];
+                bad |= keep[j] && out;
+            }
+        } else {
+            bool walls = false;
+#pragma unroll
+            for (int j = 0; j < PPT; ++j) walls |= keep[j] && (unsigned)cell[j] >= (unsigned)nc;
+            if (__any(walls)) {
+                const SegConst& sc = d.segc[sg];
+#pragma unroll
+                for (int j = 0; j < PPT; ++j) {
+                    if (!(keep[j] && (unsigned)cell[j] >= (unsigned)nc)) continue;
+                    const int wall = cell[j] < 0 ? 0 : 1;
+                    // components the push does not carry are read for the
+                    // few particles that reach a wall
+                    const float wy = RY ? vy[j] : p_vy[slot0 + j];
+                    const float wz = RZ ? vz[j] : p_vz[slot0 + j];
+                    const float vnew2 = vx[j] * vx[j] + wy * wy + wz * wz;
+                    const float eps = sc.half_m_over_e * vnew2;
+                    atomicAdd(&s_cnt[C_ABS0 + wall], 1u);
+                    atomicAdd(&s_wen[wall], fixed_u64(eps * 1048576.0f));
+                    if (DIAG) {
+                        // impact energy: this species' histogram at this
+                        // wall, and for electrons the wall energy distribution
+                        const int wb = (int)(eps * sc.wedf_inv_bin);
+                        if ((unsigned)wb < (unsigned)kEepfBins)
+                            atomicAdd(&d.wedf[((size_t)sg * 2 + wall) * kEepfBins + wb], 1ull);
+                        const int bin = (int)(eps * a.eepf_inv_bin);
+                        if (s == 0 && (unsigned)bin < (unsigned)kEepfBins)
+                            atomicAdd(&d.eepf[((size_t)b * 2 + 1) * kEepfBins + bin], 1ull);
+                    }
+                    if (GENERAL && k.emits) evw[j] = kEvSee | (wall ? kEvWall1 : 0u);
+                    keep[j] = false;
+                }
+            }
+        }
+        if (__any(bad)) {
+            if (bad) atomicOr(&d.diss[b].flags, kFlagCell);
+        }
+        if (GENERAL && k.nch > 0) {
+            // null-collision Monte Carlo: integer candidate test on the first draw
+#pragma unroll
+            for (int j = 0; j < PPT; ++j) {
+                const bool cand = candidate_draw(pid[j], k, s) < k.t32;
+                evw[j] |= keep[j] && cand ? kEvCand : 0u;
+            }
+        }
+        if (renews) {
+#pragma unroll
+            for (int j = 0; j < PPT; ++j) {
+                if (!keep[j]) continue;
                 // past L_z the particle gets a fresh velocity from its
                 // species' initial distribution at the same x (events pass)
-                const double zz = zax[j] + (double)vz[j] * dt_d;
-                if (fabs(zz) >= renew_lz) {
+                const double zz = zax[j] + (double)vz[j] * k.dt_d;
+                if (fabs(zz) >= k.renew_lz) {
                     evw[j] |= kEvRenew;
                     zax[j] = 0.0;
                     atomicAdd(&s_cnt[C_REN], 1u);
@@ -688,45 +887,47 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
                     zax[j] = zz;
                 }
             }
-            if (keep) {
+        }
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            if (keep[j]) {
                 lds_deposit(hist, cell[j], off[j]);
                 // a particle whose velocity the events pass changes is
                 // sampled there
-                if (a.diag && !(evw[j] & (kEvCand | kEvRenew))) {
-                    moment_diag(k.mscale1, k.mscale2, fhist, mhist, cell[j], off[j], vx[j], nc, periodic);
+                if (DIAG && !(evw[j] & (kEvCand | kEvRenew))) {
+                    moment_diag(k.mscale1, k.mscale2, fhist, mhist, cell[j], off[j], vx[j], nc, k.periodic);
                     if (s == 0)
                         electron_diag(k.hme, k.bulk_lo, k.bulk_hi, a.eepf_inv_bin, ehist, eepf, cell[j], off[j],
-                                      vx[j], vy[j], vz[j], nc, periodic);
+                                      vx[j], vy[j], vz[j], nc, k.periodic);
                 }
-            } else {
-                cell[j] = -1;                              // absorbed: leaves a hole
             }
+            // absorbed particles leave holes, holes stay
+            if (GENERAL) cell[j] = keep[j] ? cell[j] : -1;
         }
-        ke_run += ke_tile;
 
         // in place; every particle keeps its slot
-        if (base + PPT <= n) {
-            vstore<PPT, int4, GENERAL>(p_cell + base, cell);
-            vstore<PPT, float4, GENERAL>(p_off + base, off);
-            vstore<PPT, float4, GENERAL>(p_vx + base, vx);
-            if (UY) vstore<PPT, float4, GENERAL>(p_vy + base, vy);
-            if (UZ) vstore<PPT, float4, GENERAL>(p_vz + base, vz);
+        if (slot0 + PPT <= rem) {
+            vstore<PPT, int4, GENERAL>(p_cell + slot0, cell);
+            vstore<PPT, float4, GENERAL>(p_off + slot0, off);
+            vstore<PPT, float4, GENERAL>(p_vx + slot0, vx);
+            if (UY) vstore<PPT, float4, GENERAL>(p_vy + slot0, vy);
+            if (UZ) vstore<PPT, float4, GENERAL>(p_vz + slot0, vz);
         } else {
 #pragma unroll
             for (int j = 0; j < PPT; ++j) {
-                if (base + j < n) {
-                    p_cell[base + j] = cell[j];
-                    p_off[base + j] = off[j];
-                    p_vx[base + j] = vx[j];
-                    if (UY) p_vy[base + j] = vy[j];
-                    if (UZ) p_vz[base + j] = vz[j];
+                if (slot0 + j < rem) {
+                    p_cell[slot0 + j] = cell[j];
+                    p_off[slot0 + j] = off[j];
+                    p_vx[slot0 + j] = vx[j];
+                    if (UY) p_vy[slot0 + j] = vy[j];
+                    if (UZ) p_vz[slot0 + j] = vz[j];
                 }
             }
         }
         if (renews) {
 #pragma unroll
             for (int j = 0; j < PPT; ++j)
-                if (base + j < n) p_z[base + j] = zax[j];
+                if (slot0 + j < rem) p_z[tile0 + slot0 + j] = zax[j];
         }
         if (GENERAL) {
             // this wave's events, appended to the workgroup's packed list at
@@ -750,8 +951,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
 #pragma unroll
                 for (int j = 0; j < PPT; ++j) {
                     if (evw[j]) {
-                        d.evr[r0 + below] = make_uint4(evw[j] | (uint32_t)(tid * PPT + j) |
-                                                           ((uint32_t)sg << kEvSegShift),
+                        d.evr[r0 + below] = make_uint4(evw[j] | (uint32_t)(slot0 + j) | ((uint32_t)sg << kEvSegShift),
                                                        pid[j], __float_as_uint(vx[j]), __float_as_uint(vy[j]));
                         d.evq[r0 + below] = make_uint4(__float_as_uint(vz[j]), (uint32_t)cell[j],
                                                        __float_as_uint(off[j]), (uint32_t)t);
@@ -759,15 +959,16 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
                     }
                 }
             }
+            if (tid == 0) d.bcnt[t] = 0;   // the events pass counts this tile's births
         }
-        if (tid == 0 && tin == ntiles - 1) {
-            d.segs[sg].tile_first = tile_first;
-            d.segs[sg].ntiles = ntiles;
+        if (tid == 0 && t == seg_end - 1) {
+            d.segs[sg].tile_first = seg_first;
+            d.segs[sg].ntiles = seg_end - seg_first;
         }
-        if (GENERAL && tid == 0) d.bcnt[t] = 0;   // the events pass counts this tile's births
     }
     if (!GENERAL) {
-        if (cur_g >= 0) flush(cur_g, 0);
+        lds_barrier();
+        flush(0);
         return;
     }
     __syncthreads();                              // every wave's records are written
@@ -778,18 +979,18 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
     // flush's atomics to complete
     const uint32_t nch = FUSE ? (nev + 63u) >> 6 : 0u;
     const int quiet = nch < (uint32_t)kWavesPerTile ? (int)nch * 64 : 0;
-    if (cur_g >= 0) flush(cur_g, quiet);
+    flush(quiet);
     if (tid == kBS - 1) d.evg[blockIdx.x] = nev;  // the events pass's count of this range
     if (FUSE) {
         // this workgroup's own events, in chunks of 64 over its waves:
         // the same pass as the events kernel's, on the records and the
         // tiles this workgroup has just written
-        const EvPass ps{T, chunk, NT, (uint32_t)(T / kBirthsDiv), a.diag, a.eepf_inv_bin,
-                        (ry ? kUseY : 0) | (rz ? kUseZ : 0)};
+        const EvPass ps{T, chunk, NT, (uint32_t)(T / kBirthsDiv), DIAG, a.eepf_inv_bin,
+                        (RY ? kUseY : 0) | (RZ ? kUseZ : 0)};
         for (uint32_t kc = (uint32_t)wid; kc < nch; kc += (uint32_t)kWavesPerTile) {
             uint4 rec, rq;
             const bool act = event_record(d, ps, (int)blockIdx.x, nev, kc, rec, rq);
-            event_chunk(d, s_pref, NS, ps, act, rec, rq);
+            event_chunk(d, s_pref, ps, act, rec, rq);
         }
     }
 }
@@ -972,134 +1173,136 @@ __device__ __forceinline__ bool event_record(const DevPtrs& d, const EvPass& ps,
     return true;
 }
 
-// The events pass on one chunk: lanes with `act` hold an event's records.
-__device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, int NS, const EvPass& ps,
-                                            bool act, uint4 rec, uint4 rq)
+// The events pass on one chunk: lanes with `act` hold an event's records.  One
+// segment at a time (a chunk spans more than one only at a segment's end), so
+// its constants are read once for the wave, all in one round.
+__device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, const EvPass& ps, bool act,
+                                            uint4 rec, uint4 rq)
 {
     const int S = d.S;
     const int lane = threadIdx.x & 63;
-    bool hb = false, see = false, cand = false, viol = false, lost = false;
-    int wall = 0, ch = -1, sg = -1;
-    if (act) {
-        const int32_t t = (int32_t)rq.w;
-        const uint32_t word = rec.x;
-        sg = (int)(word >> kEvSegShift);
-        const int b = sg / S, s = sg - b * S;
-        const DisConst& dc = d.disc[b];
-        const SegConst& sc = d.segc[sg];
-        const int32_t tin = t - s_pref[sg];
-        const int io = d.segs[sg].parity;
-        const uint32_t step = (uint32_t)d.diss[b].step;
-        const int nc = dc.n_cells;
-        const int periodic = dc.bc == PIC_BC_PERIODIC;
-        const uint32_t key = word & kEvSlot;
-        const int64_t slot = (int64_t)tin * ps.T + key;
-        const uint32_t pid = sc.nch > 0 ? rec.y : sc.id[io][slot];
-        Birth bb;
-        if (word & kEvSee) {
-            see = true;
-            wall = (word & kEvWall1) ? 1 : 0;
-            const int r = secondary(sc, dc, s, step, wall, pid, bb);
-            hb = r > 0;
-            lost = r < 0;
-        } else {
-            double ux = __uint_as_float(rec.z);
-            double uy = (ps.vm & kUseY) ? __uint_as_float(rec.w) : sc.vy[io][slot];
-            double uz = (ps.vm & kUseZ) ? __uint_as_float(rq.x) : sc.vz[io][slot];
-            if (word & kEvRenew) {
-                const uint4 r6 = philox10(pid, step, ((uint32_t)s << 24) | 6u, 0u, dc.key0, dc.key1);
-                double g0, g1, g2, g3;
-                box_muller_d(u01d(r6.x), u01d(r6.y), g0, g1);
-                box_muller_d(u01d(r6.z), u01d(r6.w), g2, g3);
-                ux = sc.drift0[0] + sc.vth0 * g0;
-                uy = sc.drift0[1] + sc.vth0 * g1;
-                uz = sc.drift0[2] + sc.vth0 * g2;
-            }
-            if (word & kEvCand) {
-                cand = true;
-                ch = collide_particle(sc, dc, s, step, ux, uy, uz, pid, bb, viol, hb);
-            }
-            // the position (the push's, in the record): for an ionization's
-            // pair and the diagnostics
-            const int c = (int)rq.y;
-            const float f = __uint_as_float(rq.z);
-            if (hb) {
-                bb.cell = c;
-                bb.off = f;
-            }
-            const float fx = (float)ux, fy = (float)uy, fz = (float)uz;
-            if (ch >= 0 || (word & kEvRenew)) {          // a null collision changes nothing
-                sc.vx[io][slot] = fx;
-                sc.vy[io][slot] = fy;
-                sc.vz[io][slot] = fz;
-            }
-            if (ps.diag) {
-                unsigned long long* fh = d.macc + (size_t)sg * 2 * d.nodes_max;
-                moment_diag(sc.mscale1, sc.mscale2, fh, fh + d.nodes_max, c, f, fx, nc, periodic);
-                if (s == 0)
-                    electron_diag(sc.half_m_over_e, dc.bulk_lo, dc.bulk_hi, ps.eepf_inv_bin,
-                                  d.eacc + (size_t)b * d.nodes_max,
-                                  d.eepf + (size_t)b * 2 * kEepfBins, c, f, fx, fy, fz, nc, periodic);
-            }
-        }
-        if (hb) {
-            const uint32_t pos = atomicAdd(reinterpret_cast<uint32_t*>(&d.bcnt[t]), 1u);
-            if (pos < ps.bpt) {
-                bb.key = key;
-                d.births[(size_t)t * ps.bpt + pos] = bb;
-                unsigned long long* acc_e = d.acc + ((size_t)b * S + 0) * kRep * d.nodes_max;
-                global_deposit(acc_e, bb.cell, bb.off, nc, periodic);
-                if (!see && S > 1)          // no ions in a swarm
-                    global_deposit(d.acc + ((size_t)b * S + 1) * kRep * d.nodes_max, bb.cell, bb.off, nc,
-                                   periodic);
-                if (ps.diag) {
-                    // the births' velocity moments and the electron's
-                    // energy, with the particles of the step
-                    const SegConst& se = d.segc[b * S + 0];
-                    unsigned long long* fe = d.macc + (size_t)(b * S + 0) * 2 * d.nodes_max;
-                    moment_diag(se.mscale1, se.mscale2, fe, fe + d.nodes_max, bb.cell, bb.off, bb.vx, nc,
-                                periodic);
-                    electron_diag(se.half_m_over_e, dc.bulk_lo, dc.bulk_hi, ps.eepf_inv_bin,
-                                  d.eacc + (size_t)b * d.nodes_max, d.eepf + (size_t)b * 2 * kEepfBins,
-                                  bb.cell, bb.off, bb.vx, bb.vy, bb.vz, nc, periodic);
-                    if (!see && S > 1) {
-                        const SegConst& si = d.segc[b * S + 1];
-                        unsigned long long* fi = d.macc + (size_t)(b * S + 1) * 2 * d.nodes_max;
-                        moment_diag(si.mscale1, si.mscale2, fi, fi + d.nodes_max, bb.cell, bb.off, bb.ivx, nc,
-                                    periodic);
-                    }
-                }
-                atomicAdd(reinterpret_cast<unsigned long long*>(&d.segs[sg].staged), 1ull);
-            } else {
-                hb = false;
-                lost = true;
-                atomicOr(&d.diss[b].flags, kFlagCapacity);
-            }
-        }
-    }
-    // counters of the chunk, one segment at a time (a chunk spans more
-    // than one only at a segment's end): lane i holds counter i
+    const uint32_t word = act ? rec.x : 0u;
     uint64_t todo = __ballot(act);
     while (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const int lsg = __shfl(sg, leader, 64);
-        const bool mine = act && sg == lsg;
+        const int sg =
+            (int)((uint32_t)__builtin_amdgcn_readlane((int)word, __ffsll((long long)todo) - 1) >> kEvSegShift);
+        const bool mine = act && (int)(word >> kEvSegShift) == sg;
+        todo &= ~__ballot(mine);
+        const int b = seg_discharge(sg, S), s = sg - b * S;
+        const DisConst& dc = d.disc[b];
+        const SegConst& sc = d.segc[sg];
+        const int nc = dc.n_cells;
+        const int periodic = dc.bc == PIC_BC_PERIODIC;
+        const uint32_t step = (uint32_t)d.diss[b].step;
+        const SegState& st = d.segs[sg];
+        const int64_t stride = st.stride;
+        char* base = st.base + (int64_t)st.parity * kFields * stride;
+        const int nch = sc.nch;
+        const int32_t first = s_pref[sg];
+        bool hb = false, see = false, cand = false, viol = false, lost = false;
+        int wall = 0, ch = -1;
+        if (mine) {
+            const int32_t t = (int32_t)rq.w;
+            const uint32_t key = word & kEvSlot;
+            char* at = base + ((int64_t)(t - first) * ps.T + key) * 4;     // the particle's slot
+            const uint32_t pid = nch > 0 ? rec.y : *reinterpret_cast<const uint32_t*>(at + 5 * stride);
+            Birth bb;
+            if (word & kEvSee) {
+                see = true;
+                wall = (word & kEvWall1) ? 1 : 0;
+                const int r = secondary(sc, dc, s, step, wall, pid, bb);
+                hb = r > 0;
+                lost = r < 0;
+            } else {
+                double ux = __uint_as_float(rec.z);
+                double uy = (ps.vm & kUseY) ? __uint_as_float(rec.w) : *reinterpret_cast<const float*>(at + 3 * stride);
+                double uz = (ps.vm & kUseZ) ? __uint_as_float(rq.x) : *reinterpret_cast<const float*>(at + 4 * stride);
+                if (word & kEvRenew) {
+                    const uint4 r6 = philox10(pid, step, ((uint32_t)s << 24) | 6u, 0u, dc.key0, dc.key1);
+                    double g0, g1, g2, g3;
+                    box_muller_d(u01d(r6.x), u01d(r6.y), g0, g1);
+                    box_muller_d(u01d(r6.z), u01d(r6.w), g2, g3);
+                    ux = sc.drift0[0] + sc.vth0 * g0;
+                    uy = sc.drift0[1] + sc.vth0 * g1;
+                    uz = sc.drift0[2] + sc.vth0 * g2;
+                }
+                if (word & kEvCand) {
+                    cand = true;
+                    ch = collide_particle(sc, dc, s, step, ux, uy, uz, pid, bb, viol, hb);
+                }
+                // the position (the push's, in the record): for an ionization's
+                // pair and the diagnostics
+                const int c = (int)rq.y;
+                const float f = __uint_as_float(rq.z);
+                if (hb) {
+                    bb.cell = c;
+                    bb.off = f;
+                }
+                const float fx = (float)ux, fy = (float)uy, fz = (float)uz;
+                if (ch >= 0 || (word & kEvRenew)) {          // a null collision changes nothing
+                    *reinterpret_cast<float*>(at + 2 * stride) = fx;
+                    *reinterpret_cast<float*>(at + 3 * stride) = fy;
+                    *reinterpret_cast<float*>(at + 4 * stride) = fz;
+                }
+                if (ps.diag) {
+                    unsigned long long* fh = d.macc + (size_t)sg * 2 * d.nodes_max;
+                    moment_diag(sc.mscale1, sc.mscale2, fh, fh + d.nodes_max, c, f, fx, nc, periodic);
+                    if (s == 0)
+                        electron_diag(sc.half_m_over_e, dc.bulk_lo, dc.bulk_hi, ps.eepf_inv_bin,
+                                      d.eacc + (size_t)b * d.nodes_max,
+                                      d.eepf + (size_t)b * 2 * kEepfBins, c, f, fx, fy, fz, nc, periodic);
+                }
+            }
+            if (hb) {
+                const uint32_t pos = atomicAdd(reinterpret_cast<uint32_t*>(&d.bcnt[t]), 1u);
+                if (pos < ps.bpt) {
+                    bb.key = key;
+                    d.births[(size_t)t * ps.bpt + pos] = bb;
+                    unsigned long long* acc_e = d.acc + ((size_t)b * S + 0) * kRep * d.nodes_max;
+                    global_deposit(acc_e, bb.cell, bb.off, nc, periodic);
+                    if (!see && S > 1)          // no ions in a swarm
+                        global_deposit(d.acc + ((size_t)b * S + 1) * kRep * d.nodes_max, bb.cell, bb.off, nc,
+                                       periodic);
+                    if (ps.diag) {
+                        // the births' velocity moments and the electron's
+                        // energy, with the particles of the step
+                        const SegConst& se = d.segc[b * S + 0];
+                        unsigned long long* fe = d.macc + (size_t)(b * S + 0) * 2 * d.nodes_max;
+                        moment_diag(se.mscale1, se.mscale2, fe, fe + d.nodes_max, bb.cell, bb.off, bb.vx, nc,
+                                    periodic);
+                        electron_diag(se.half_m_over_e, dc.bulk_lo, dc.bulk_hi, ps.eepf_inv_bin,
+                                      d.eacc + (size_t)b * d.nodes_max, d.eepf + (size_t)b * 2 * kEepfBins,
+                                      bb.cell, bb.off, bb.vx, bb.vy, bb.vz, nc, periodic);
+                        if (!see && S > 1) {
+                            const SegConst& si = d.segc[b * S + 1];
+                            unsigned long long* fi = d.macc + (size_t)(b * S + 1) * 2 * d.nodes_max;
+                            moment_diag(si.mscale1, si.mscale2, fi, fi + d.nodes_max, bb.cell, bb.off, bb.ivx, nc,
+                                        periodic);
+                        }
+                    }
+                    atomicAdd(reinterpret_cast<unsigned long long*>(&d.segs[sg].staged), 1ull);
+                } else {
+                    hb = false;
+                    lost = true;
+                    atomicOr(&d.diss[b].flags, kFlagCapacity);
+                }
+            }
+        }
+        // counters of the segment's events: lane i holds counter i
         uint32_t cnt_lane = 0u;
         auto count = [&](int i, bool p) {
-            const uint32_t v = popc_ballot(mine && p);
+            const uint32_t v = popc_ballot(p);
             cnt_lane += lane == i ? v : 0u;
         };
         count(C_CAND, cand);
         count(C_NULL, cand && ch < 0);
         count(C_VIOL, viol);
-        const int nch = d.segc[lsg].nch;
-        for (int k = 0; k < nch; ++k) count(C_COLL + k, ch == k);
+        for (int q = 0; q < nch; ++q) count(C_COLL + q, ch == q);
         count(C_SEE0, hb && see && wall == 0);
         count(C_SEE1, hb && see && wall == 1);
         count(C_DROP, lost);
         if (lane < C_N && cnt_lane)
-            atomicAdd(&d.cnt[((size_t)lsg * kRep) * C_N + lane], (unsigned long long)cnt_lane);
-        todo &= ~__ballot(mine);
+            atomicAdd(&d.cnt[((size_t)sg * kRep) * C_N + lane], (unsigned long long)cnt_lane);
     }
 }
 

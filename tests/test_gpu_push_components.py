@@ -125,3 +125,53 @@ def test_more_particles_in_one_cell_than_a_packed_word_holds(pic, cells, at, bou
         sim.config_tiles(ppt, thr, 0)
         sim.step(1)
         assert np.array_equal(sim.density()[0], expect), (ppt, thr)
+
+
+@pytest.mark.parametrize("ppt,thr,fused", [(4, 1024, False), (1, 256, True)])
+def test_more_segments_than_a_wave_has_lanes(pic, ppt, thr, fused):
+    # up to 64 segments a wave holds the tile table in its lanes, beyond that
+    # it lies in LDS: discharges of a batch of 33 (66 segments, some retired)
+    # equal single runs bit for bit
+    cfgs, tabs = [], None
+    for i in range(33):
+        cfg, tabs = small_argon(n_init=300 + 97 * i, seed=60 + i, n_cells=40 + 3 * i)
+        cfgs.append(cfg)
+    both = pic.Sim(cfgs, tabs)
+    both.config_tiles(ppt, thr, 0, 16)
+    both.config_events(fused)
+    both.set_diag(True)
+    both.retire(4)
+    both.step(24)
+    for b in (0, 5, 31, 32):
+        one = pic.Sim(cfgs[b], tabs)
+        one.set_diag(True)
+        one.step(24)
+        for s in range(2):
+            pa, pb = both.get_particles(s, b), one.get_particles(s)
+            for k in ("cell", "off", "vx", "vy", "vz", "id"):
+                assert np.array_equal(pa[k], pb[k]), (b, s, k)
+        assert np.array_equal(both.coll(b)["coll"], one.coll()["coll"])
+        assert np.array_equal(both.phi(b), one.phi())
+        assert np.array_equal(both.avg(b)["mean_energy"], one.avg()["mean_energy"])
+    assert both.counts(4)["step"] == 0
+
+
+def test_three_species_match_oracle(pic):
+    # a third species (heavier ions beside the first) in a batch of two
+    # discharges: every segment takes its own constants
+    cfgs = []
+    for i in range(2):
+        cfg = W.exb(n_per_species=2003 + i, n_cells=64, seed=70 + i)
+        third = dict(cfg["species"][1], mass=2.0 * cfg["species"][1]["mass"], n_init=1001, capacity=1001)
+        cfg["species"] = cfg["species"] + [third]
+        cfgs.append(cfg)
+    sim = pic.Sim(cfgs)
+    sim.step(2)
+    refs = [to_oracle(sim, cfg, batch=b) for b, cfg in enumerate(cfgs)]
+    sim.step(1)
+    for b, (cfg, o) in enumerate(zip(cfgs, refs)):
+        o.step(1)
+        for s in range(3):
+            r = compare_species(sim.get_particles(s, b), o.get_particles(s), cfg, cfg["species"][s]["vth"])
+            assert r["id_equal"] and r["cell_mismatch"] == 0, (b, s)
+            assert r["max_dx_over_L"] < 1e-6 and r["max_rel_v"] < 1e-6, (b, s)
