@@ -60,7 +60,8 @@ struct pic_ctx {
     int diag = 0;
     double eepf_emax = 64.0;
     double wedf_emax[PIC_MAX_SPECIES] = {64.0, 1024.0, 1024.0, 1024.0};   // wall impact-energy ranges (eV)
-    double* poisson_scratch = nullptr;   // rho, phi, e: 3 * nodes_max
+    unsigned long long* host = nullptr;  // pinned host memory the readbacks and the Poisson call go through
+    size_t host_words = 0;
     void* sort_scratch = nullptr;
     size_t sort_scratch_bytes = 0;
     int64_t sort_tiles = 0;
@@ -404,6 +405,30 @@ pic_status solve_after_deposit(pic_ctx* ctx, int only_b)
 
 namespace {
 void drop_graph(pic_ctx* ctx);
+
+static_assert(sizeof(DisState) % 8 == 0 && sizeof(SegState) % 8 == 0, "read in 8-byte words");
+
+// A readback in stream order: pieces of device memory to pinned host memory in
+// one kernel, then a wait.  add() says where a piece will be.
+struct Readback {
+    pic_ctx* ctx;
+    ReadArgs a{};
+    explicit Readback(pic_ctx* c) : ctx(c) { a.dst = c->host; }
+    template <typename T>
+    const T* add(const T* src, size_t count)
+    {
+        const size_t words = count * sizeof(T) / 8, at = a.first[a.n];
+        a.src[a.n] = reinterpret_cast<const unsigned long long*>(src);
+        a.first[++a.n] = (uint32_t)(at + words);
+        return reinterpret_cast<const T*>(ctx->host + at);
+    }
+    pic_status go()
+    {
+        if (a.n > ReadArgs::kMax || a.first[a.n] > ctx->host_words) return PIC_EINVAL;
+        if (launch_read(a, ctx->stream) != hipSuccess) return PIC_EHIP;
+        return hip_st(hipStreamSynchronize(ctx->stream));
+    }
+};
 }
 
 // ---------------------------------------------------------------------------
@@ -463,6 +488,7 @@ void pic_free(pic_ctx* ctx)
     for (hipEvent_t e : ctx->ev) (void)hipEventDestroy(e);
     drop_graph(ctx);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
+    if (ctx->host) (void)hipHostFree(ctx->host);
     std::vector<void*> bl = ctx->blocks;
     for (void* p : bl) dev_release(ctx, p);
     delete ctx;
@@ -627,7 +653,18 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
         d.ccnt = (uint32_t*)A(4ull * tiles_max);
         d.tick = (unsigned long long*)A(8);
         d.ke_part = (double*)A(8ull * tiles_max);
-        ctx->poisson_scratch = (double*)A(8ull * 3 * nodes_max);
+    }
+    if (rc == PIC_OK) {
+        // the largest readback: the power sums of a discharge, or its wall
+        // distributions, with its state and counters
+        ctx->host_words = std::max<size_t>({(size_t)S * kPow * nodes_max, (size_t)(S + 2) * nodes_max + 1,
+                                            (size_t)3 * nodes_max, (size_t)S * 2 * kEepfBins,
+                                            sizeof(DisState) / 8 * (size_t)B}) +
+                          (sizeof(DisState) + S * sizeof(SegState)) / 8 + (size_t)S * kRep * C_N;
+        if (hipHostMalloc((void**)&ctx->host, ctx->host_words * 8, hipHostMallocDefault) != hipSuccess) {
+            ctx->host = nullptr;
+            rc = PIC_ENOMEM;
+        }
     }
     if (rc != PIC_OK) {
         pic_free(ctx);
@@ -1088,12 +1125,12 @@ pic_status pic_profile(pic_ctx* ctx, int32_t enable)
 pic_status pic_sync(pic_ctx* ctx)
 {
     if (!ctx) return PIC_EINVAL;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return PIC_EHIP;
-    std::vector<DisState> ds(ctx->B);
-    if (hipMemcpy(ds.data(), ctx->d.diss, sizeof(DisState) * ctx->B, hipMemcpyDeviceToHost) != hipSuccess)
-        return PIC_EHIP;
+    Readback rb(ctx);
+    const DisState* ds = rb.add(ctx->d.diss, (size_t)ctx->B);
+    const pic_status rc = rb.go();
+    if (rc != PIC_OK) return rc;
     uint32_t f = 0;
-    for (const auto& x : ds) f |= x.flags;
+    for (int b = 0; b < ctx->B; ++b) f |= ds[b].flags;
     return flags_status(f);
 }
 
@@ -1102,30 +1139,24 @@ pic_status pic_poisson(pic_ctx* ctx, int32_t batch, double t_s, const double* rh
 {
     if (!ctx || batch < 0 || batch >= ctx->B) return PIC_EINVAL;
     const int nn = ctx->disc[batch].n_nodes;
-    const size_t nm = ctx->d.nodes_max;
-    double* rho_d = ctx->poisson_scratch;
-    double* phi_d = rho_d + nm;
-    double* e_d = phi_d + nm;
-    hipStream_t st = ctx->stream;
-    if (hipStreamSynchronize(st) != hipSuccess) return PIC_EHIP;
-    hipError_t e;
-    if (rho_in) e = hipMemcpy(rho_d, rho_in, nn * sizeof(double), hipMemcpyHostToDevice);
-    else e = hipMemcpy(rho_d, ctx->d.rho + (size_t)batch * nm, nn * sizeof(double), hipMemcpyDeviceToDevice);
-    if (e != hipSuccess) return PIC_EHIP;
+    // the kernel reads the density from pinned host memory (or where the step
+    // left it) and writes the solution there: one launch, one wait
+    double* rho_h = reinterpret_cast<double*>(ctx->host);
+    double* phi_h = rho_h + ctx->d.nodes_max;
+    double* e_h = phi_h + ctx->d.nodes_max;
+    if (rho_in) std::memcpy(rho_h, rho_in, nn * sizeof(double));
     FinArgs fa{};
     fa.d = ctx->d;
     fa.mode = kFinExternal;
     fa.only_b = batch;
     fa.t_ext = t_s;
-    fa.rho_ext = rho_d;
-    fa.phi_out = phi_d;
-    fa.e_out = e_d;
-    if (launch_finalize(fa, st) != hipSuccess) return PIC_EHIP;
-    if (hipStreamSynchronize(st) != hipSuccess) return PIC_EHIP;
-    if (phi_out && hipMemcpy(phi_out, phi_d, nn * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
-        return PIC_EHIP;
-    if (e_out && hipMemcpy(e_out, e_d, nn * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
-        return PIC_EHIP;
+    fa.rho_ext = rho_in ? rho_h : ctx->d.rho + (size_t)batch * ctx->d.nodes_max;
+    fa.phi_out = phi_out ? phi_h : nullptr;
+    fa.e_out = e_out ? e_h : nullptr;
+    if (launch_finalize(fa, ctx->stream) != hipSuccess) return PIC_EHIP;
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return PIC_EHIP;
+    if (phi_out) std::memcpy(phi_out, phi_h, nn * sizeof(double));
+    if (e_out) std::memcpy(e_out, e_h, nn * sizeof(double));
     return PIC_OK;
 }
 
@@ -1149,21 +1180,24 @@ pic_status pic_get_windows(pic_ctx* ctx, int32_t batch, int64_t first, int32_t c
                            int64_t* n_done)
 {
     if (!ctx || batch < 0 || batch >= ctx->B || first < 0 || count < 0 || (count > 0 && !out)) return PIC_EINVAL;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return PIC_EHIP;
-    DisState ds;
-    if (hipMemcpy(&ds, ctx->d.diss + batch, sizeof(DisState), hipMemcpyDeviceToHost) != hipSuccess) return PIC_EHIP;
-    if (n_done) *n_done = ds.nwin;
+    Readback rs(ctx);
+    const DisState* ds = rs.add(ctx->d.diss + batch, 1);
+    pic_status rc = rs.go();
+    if (rc != PIC_OK) return rc;
+    const int64_t nwin = ds->nwin;
+    if (n_done) *n_done = nwin;
     if (count == 0) return PIC_OK;
-    if (first + count > ds.nwin || first < ds.nwin - kWindowRing) return PIC_EINVAL;
+    if (first + count > nwin || first < nwin - kWindowRing) return PIC_EINVAL;
     const int S = ctx->S;
     const int nn = ctx->disc[batch].n_nodes;
     const size_t nm = ctx->d.nodes_max, stride = 1 + (size_t)(S + 2) * nm;
-    std::vector<double> w(stride);
     for (int32_t k = 0; k < count; ++k) {
         const int64_t idx = first + k;
-        if (hipMemcpy(w.data(), ctx->d.wring + ((size_t)batch * kWindowRing + (size_t)(idx % kWindowRing)) * stride,
-                      stride * 8, hipMemcpyDeviceToHost) != hipSuccess)
-            return PIC_EHIP;
+        Readback rw(ctx);
+        const double* w =
+            rw.add(ctx->d.wring + ((size_t)batch * kWindowRing + (size_t)(idx % kWindowRing)) * stride, stride);
+        rc = rw.go();
+        if (rc != PIC_OK) return rc;
         double* o = out + (size_t)k * (1 + (size_t)(S + 2) * nn);
         const double ns = w[0];
         o[0] = ns;
@@ -1418,32 +1452,75 @@ pic_status pic_load_profiles(pic_ctx* ctx, int32_t batch, int32_t m, const doubl
 pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t out_bytes)
 {
     if (!ctx || batch < 0 || batch >= ctx->B) return PIC_EINVAL;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return PIC_EHIP;
     const int S = ctx->S;
     const int nn = ctx->disc[batch].n_nodes;
     const size_t nm = ctx->d.nodes_max;
-    std::vector<SegState> ss(S);
-    DisState ds;
-    std::vector<unsigned long long> cr((size_t)S * kRep * C_N);
-    std::vector<unsigned long long> ev((size_t)S * C_N, 0ull);   // counters summed over copies
-    if (hipMemcpy(cr.data(), ctx->d.cnt + (size_t)batch * S * kRep * C_N, cr.size() * 8, hipMemcpyDeviceToHost) !=
-        hipSuccess)
-        return PIC_EHIP;
-    for (int s = 0; s < S; ++s)
-        for (int r = 0; r < kRep; ++r)
-            for (int k = 0; k < C_N; ++k) ev[(size_t)s * C_N + k] += cr[((size_t)s * kRep + r) * C_N + k];
-    if (hipMemcpy(ss.data(), ctx->d.segs + (size_t)batch * S, sizeof(SegState) * S, hipMemcpyDeviceToHost) !=
-            hipSuccess ||
-        hipMemcpy(&ds, ctx->d.diss + batch, sizeof(DisState), hipMemcpyDeviceToHost) != hipSuccess)
-        return PIC_EHIP;
-    auto need = [&](size_t bytes) { return out && out_bytes >= bytes; };
-    auto d2h = [&](void* dst, const void* src, size_t bytes) {
-        return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) == hipSuccess;
-    };
+    // what the selector needs, beside the discharge's state: its species'
+    // states, its counters, rows of device memory
+    bool states = false, counters = false, found = true;
+    struct { const void* p; size_t words; } row[PIC_MAX_SPECIES] = {};
+    int rows = 0;
+    size_t need = 0;
+    auto take = [&](const void* p, size_t words) { row[rows++] = {p, words}; };
+    const size_t at = (size_t)batch * nm;
+    switch (what) {
+        case PIC_DIAG_COUNTS: need = 8 * (4 + 2 * (size_t)S); states = true; break;
+        case PIC_DIAG_RHO: need = 8ull * nn; take(ctx->d.rho + at, nn); break;
+        case PIC_DIAG_PHI: need = 8ull * nn; take(ctx->d.phi + at, nn); break;
+        case PIC_DIAG_EFIELD: need = 8ull * nn; take(ctx->d.ef + at, nn); break;
+        case PIC_DIAG_DENSITY:
+            need = 8ull * S * nn;
+            for (int s = 0; s < S; ++s) take(ctx->d.dens + ((size_t)batch * S + s) * nm, nn);
+            break;
+        case PIC_DIAG_ENERGY: need = 8ull * (S + 1); states = true; break;
+        case PIC_DIAG_WALL: need = 8ull * (2 * S + 2); counters = true; break;
+        case PIC_DIAG_COLL: need = 8ull * S * (3 + kMaxChan); counters = true; break;
+        case PIC_DIAG_NUMAX: need = 8ull * 2 * S; break;
+        case PIC_DIAG_FLAGS: need = 8; break;
+        case PIC_DIAG_AVG:
+            need = 8ull * (1 + (size_t)(S + 2) * nn);
+            take(ctx->d.avg + (size_t)batch * (S + 2) * nm, (S + 2) * nm);
+            break;
+        case PIC_DIAG_EEPF:
+            need = 8ull * (2 * kEepfBins + 2);
+            take(ctx->d.eepf + (size_t)batch * 2 * kEepfBins, 2 * kEepfBins);
+            break;
+        case PIC_DIAG_RESET_AVG: break;
+        case PIC_DIAG_CIRCUIT: need = 16; counters = true; take(ctx->d.phi + at, 1); break;
+        case PIC_DIAG_GRAPHS: need = 16; break;
+        case PIC_DIAG_RENEWED: need = 8ull * S; counters = true; break;
+        case PIC_DIAG_WALL_EDF:
+            need = 8ull * ((size_t)S * 2 * kEepfBins + S + 1);
+            take(ctx->d.wedf + (size_t)batch * S * 2 * kEepfBins, (size_t)S * 2 * kEepfBins);
+            break;
+        case PIC_DIAG_WALL_ENERGY: need = 8ull * 2 * S; take(ctx->d.wen + (size_t)batch * S * 2, (size_t)S * 2); break;
+        case PIC_DIAG_POWER:
+            need = 8ull * (1 + (size_t)kPow * S * nn);
+            take(ctx->d.pavg + (size_t)batch * S * kPow * nm, (size_t)S * kPow * nm);
+            break;
+        case PIC_DIAG_TIMING: need = 8ull * 6; break;
+        case PIC_DIAG_CHARGE: need = 16; states = true; take(ctx->d.rho + at, nn); break;
+        default: found = false;
+    }
+    Readback rb(ctx);
+    const DisState* dsp = rb.add(ctx->d.diss + batch, 1);
+    const SegState* ss = states ? rb.add(ctx->d.segs + (size_t)batch * S, S) : nullptr;
+    const unsigned long long* cr =
+        counters ? rb.add(ctx->d.cnt + (size_t)batch * S * kRep * C_N, (size_t)S * kRep * C_N) : nullptr;
+    const unsigned long long* got[PIC_MAX_SPECIES] = {};
+    for (int r = 0; r < rows; ++r) got[r] = rb.add((const unsigned long long*)row[r].p, row[r].words);
+    const pic_status rc = rb.go();
+    if (rc != PIC_OK) return rc;
+    if (!found || (need && (!out || out_bytes < need))) return PIC_EINVAL;
+    DisState ds = *dsp;
+    std::vector<unsigned long long> ev(counters ? (size_t)S * C_N : 0, 0ull);   // counters summed over copies
+    if (counters)
+        for (int s = 0; s < S; ++s)
+            for (int r = 0; r < kRep; ++r)
+                for (int k = 0; k < C_N; ++k) ev[(size_t)s * C_N + k] += cr[((size_t)s * kRep + r) * C_N + k];
     bool ok = true;
     switch (what) {
         case PIC_DIAG_COUNTS: {
-            if (!need(8 * (4 + 2 * S))) return PIC_EINVAL;
             int64_t* o = (int64_t*)out;
             o[0] = (int64_t)ds.step;
             o[1] = nn;
@@ -1458,26 +1535,20 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
         case PIC_DIAG_RHO:
         case PIC_DIAG_PHI:
         case PIC_DIAG_EFIELD: {
-            if (!need(8ull * nn)) return PIC_EINVAL;
-            const double* src = what == PIC_DIAG_RHO ? ctx->d.rho : (what == PIC_DIAG_PHI ? ctx->d.phi : ctx->d.ef);
-            ok = d2h(out, src + (size_t)batch * nm, 8ull * nn);
+            std::memcpy(out, got[0], 8ull * nn);
             break;
         }
         case PIC_DIAG_DENSITY: {
-            if (!need(8ull * S * nn)) return PIC_EINVAL;
-            for (int s = 0; s < S && ok; ++s)
-                ok = d2h((double*)out + (size_t)s * nn, ctx->d.dens + ((size_t)batch * S + s) * nm, 8ull * nn);
+            for (int s = 0; s < S; ++s) std::memcpy((double*)out + (size_t)s * nn, got[s], 8ull * nn);
             break;
         }
         case PIC_DIAG_ENERGY: {
-            if (!need(8ull * (S + 1))) return PIC_EINVAL;
             double* o = (double*)out;
             for (int s = 0; s < S; ++s) o[s] = ss[s].ke;
             o[S] = ds.fe;
             break;
         }
         case PIC_DIAG_WALL: {
-            if (!need(8ull * (2 * S + 2))) return PIC_EINVAL;
             int64_t* o = (int64_t*)out;
             int64_t see0 = 0, see1 = 0;
             for (int s = 0; s < S; ++s) {
@@ -1491,7 +1562,6 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_COLL: {
-            if (!need(8ull * S * (3 + kMaxChan))) return PIC_EINVAL;
             int64_t* o = (int64_t*)out;
             for (int s = 0; s < S; ++s) {
                 int64_t* r = o + (size_t)s * (3 + kMaxChan);
@@ -1503,7 +1573,6 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_NUMAX: {
-            if (!need(8ull * 2 * S)) return PIC_EINVAL;
             double* o = (double*)out;
             for (int s = 0; s < S; ++s) {
                 o[s] = ctx->segh[(size_t)batch * S + s].numax;
@@ -1512,7 +1581,6 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_FLAGS: {
-            if (!need(8)) return PIC_EINVAL;
             *(int64_t*)out = ds.flags;
             const uint32_t z = 0;
             ok = hipMemcpy(&ctx->d.diss[batch].flags, &z, 4, hipMemcpyHostToDevice) == hipSuccess;
@@ -1520,10 +1588,8 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             return PIC_OK;
         }
         case PIC_DIAG_AVG: {
-            if (!need(8ull * (1 + (size_t)(S + 2) * nn))) return PIC_EINVAL;
             double* o = (double*)out;
-            std::vector<double> av((size_t)(S + 2) * nm);
-            ok = d2h(av.data(), ctx->d.avg + (size_t)batch * (S + 2) * nm, av.size() * 8);
+            const double* av = (const double*)got[0];
             const double ns = ds.avg_samples;
             o[0] = ns;
             for (int k = 0; k < S + 2; ++k)
@@ -1540,9 +1606,7 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_EEPF: {
-            if (!need(8ull * (2 * kEepfBins + 2))) return PIC_EINVAL;
-            std::vector<unsigned long long> h(2 * kEepfBins);
-            ok = d2h(h.data(), ctx->d.eepf + (size_t)batch * 2 * kEepfBins, h.size() * 8);
+            const unsigned long long* h = got[0];
             double* o = (double*)out;
             for (int i = 0; i < 2 * kEepfBins; ++i) o[i] = (double)h[i];
             o[2 * kEepfBins] = ctx->eepf_emax / kEepfBins;
@@ -1561,34 +1625,29 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_CIRCUIT: {
-            if (!need(16)) return PIC_EINVAL;
             double* o = (double*)out;
-            ok = d2h(o, ctx->d.phi + (size_t)batch * nm, 8);
+            std::memcpy(o, got[0], 8);
             const DisConst& dc = ctx->disc[batch];
             const bool circuit = dc.bc != PIC_BC_PERIODIC && dc.field_solve && dc.drive != PIC_DRIVE_VOLTAGE;
             o[1] = circuit && ds.circ_init
-                       ? ds.qbase + source_charge(dc, (double)ds.step * dc.dt) + collected_charge(dc, cr.data(), S)
+                       ? ds.qbase + source_charge(dc, (double)ds.step * dc.dt) + collected_charge(dc, cr, S)
                        : 0.0;
             break;
         }
         case PIC_DIAG_GRAPHS: {
-            if (!need(16)) return PIC_EINVAL;
             int64_t* o = (int64_t*)out;
             o[0] = ctx->graph_replays;
             o[1] = ctx->graph_steps;
             break;
         }
         case PIC_DIAG_RENEWED: {
-            if (!need(8ull * S)) return PIC_EINVAL;
             int64_t* o = (int64_t*)out;
             for (int s = 0; s < S; ++s) o[s] = (int64_t)ev[(size_t)s * C_N + C_REN];
             break;
         }
         case PIC_DIAG_WALL_EDF: {
             const size_t nv = (size_t)S * 2 * kEepfBins;
-            if (!need(8ull * (nv + S + 1))) return PIC_EINVAL;
-            std::vector<unsigned long long> h(nv);
-            ok = d2h(h.data(), ctx->d.wedf + (size_t)batch * nv, nv * 8);
+            const unsigned long long* h = got[0];
             double* o = (double*)out;
             for (size_t i = 0; i < nv; ++i) o[i] = (double)h[i];
             for (int sp = 0; sp < S; ++sp) o[nv + sp] = ctx->wedf_emax[sp] / kEepfBins;
@@ -1596,9 +1655,7 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_WALL_ENERGY: {
-            if (!need(8ull * 2 * S)) return PIC_EINVAL;
-            std::vector<unsigned long long> we((size_t)S * 2);
-            ok = d2h(we.data(), ctx->d.wen + (size_t)batch * S * 2, 8ull * 2 * S);
+            const unsigned long long* we = got[0];
             const pic_config& c = ctx->cfg[batch];
             double* o = (double*)out;
             for (int sp = 0; sp < S; ++sp)
@@ -1607,9 +1664,7 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_POWER: {
-            if (!need(8ull * (1 + (size_t)kPow * S * nn))) return PIC_EINVAL;
-            std::vector<double> pv((size_t)S * kPow * nm);
-            ok = d2h(pv.data(), ctx->d.pavg + (size_t)batch * S * kPow * nm, pv.size() * 8);
+            const double* pv = (const double*)got[0];
             const double ns = ds.avg_samples;
             double* o = (double*)out;
             o[0] = ns;
@@ -1622,7 +1677,6 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_TIMING: {
-            if (!need(8ull * 6)) return PIC_EINVAL;
             prof_collect(ctx);
             double* o = (double*)out;
             o[0] = ctx->fin_n;
@@ -1634,9 +1688,7 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
             break;
         }
         case PIC_DIAG_CHARGE: {
-            if (!need(16)) return PIC_EINVAL;
-            std::vector<double> rho(nn);
-            ok = d2h(rho.data(), ctx->d.rho + (size_t)batch * nm, 8ull * nn);
+            const double* rho = (const double*)got[0];
             const DisConst& dc = ctx->disc[batch];
             double q = 0.0;
             for (int i = 0; i < nn; ++i) {

@@ -64,6 +64,17 @@ struct ProfileArgs {
     double e_over_m;              // e / m of the species
 };
 
+// Pieces of device memory (8-byte words) copied one after another to pinned
+// host memory by one kernel.
+struct ReadArgs {
+    static constexpr int kMax = 8;
+    const unsigned long long* src[kMax];
+    uint32_t first[kMax + 1];     // first word of every piece in the output; first[n]: the words in all
+    int32_t n;
+    unsigned long long* dst;
+};
+
+hipError_t launch_read(const ReadArgs& a, hipStream_t st);
 hipError_t launch_profile_load(const ProfileArgs& a, hipStream_t st);
 hipError_t launch_push(const PushArgs& a, int ppt, int threads, bool general, bool fuse, int vm, int64_t grid,
                        hipStream_t st);
