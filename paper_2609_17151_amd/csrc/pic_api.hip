@@ -55,6 +55,8 @@ struct pic_ctx {
     int64_t steps_since_sort = 0;
     int compact_every = 16;              // steps between compactions of the holes
     int events_in_push = 0;              // 256-thread general pushes do their own events
+    bool schedule_set = false;           // by pic_config_tiles or pic_config_events; else plan_step's rule
+    std::vector<int64_t> known;          // particles per segment when the host last set them
     int64_t steps_since_compact = 0;
     int64_t compact_tiles = 0;           // grid of the compaction passes
     int diag = 0;
@@ -527,6 +529,7 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
     ctx->segc.assign((size_t)B * S, SegConst{});
     ctx->segh.assign((size_t)B * S, SegHost{});
     ctx->disc.assign(B, DisConst{});
+    ctx->known.assign((size_t)B * S, 0);
     DevPtrs& d = ctx->d;
     d.B = B;
     d.S = S;
@@ -643,10 +646,10 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
         d.eepf = (unsigned long long*)A(8ull * B * 2 * kEepfBins);
         d.wedf = (unsigned long long*)A(8ull * B * S * 2 * kEepfBins);
         d.wring = (double*)A(8ull * B * kWindowRing * (1 + (size_t)(S + 2) * nodes_max));
-        d.births = (Birth*)A(sizeof(Birth) * (size_t)tiles_max * kBirthsPerTileMin);
         d.bcnt = (int32_t*)A(4ull * tiles_max);
         int64_t slots = 0;
         for (int s = 0; s < S; ++s) slots += ctx->grid_cap[s];
+        d.births = (Birth*)A(sizeof(Birth) * (size_t)(slots / kBirthSlots + (int64_t)B * S * births_per_tile(kTileMax)));
         d.evr = (uint4*)A(16ull * slots);
         d.evq = (uint4*)A(16ull * slots);
         d.evg = (uint32_t*)A(4ull * kMaxPushGrid);
@@ -679,6 +682,7 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
             ss[b * S + s].count = n;
             ss[b * S + s].live = n;
             ss[b * S + s].next_id = (uint32_t)n;
+            ctx->known[(size_t)b * S + s] = n;
             ss[b * S + s].base = seg_base[b * S + s];
             ss[b * S + s].stride = pad_cap(sp.capacity) * 4;
         }
@@ -792,6 +796,7 @@ pic_status pic_config_tiles(pic_ctx* ctx, int32_t ppt, int32_t threads, int32_t 
     }
     ctx->ppt = ppt;
     ctx->threads = threads;
+    ctx->schedule_set = true;
     ctx->sort_every = sort_every;
     ctx->steps_since_sort = 0;
     ctx->compact_every = compact_every;
@@ -805,6 +810,7 @@ pic_status pic_config_events(pic_ctx* ctx, int32_t in_push)
     pic_status rc = hip_st(hipStreamSynchronize(ctx->stream));
     if (rc != PIC_OK) return rc;
     ctx->events_in_push = in_push;
+    ctx->schedule_set = true;
     return rc;
 }
 
@@ -865,8 +871,27 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
         p.vm |= sc.vuse;
         if (sc.compacts || sc.nch > 0 || sc.emits || sc.renew_lz > 0.0) p.general = true;
     }
+    int events_in_push = ctx->events_in_push;
+    if (!ctx->schedule_set && p.general) {
+        // Nobody chose a schedule: small tiles whose workgroups do their own
+        // events up to kFuseParticles particles, as one launch and the tiles'
+        // number count there; large tiles and the events kernel above.
+        // Measured, us per step, 4 x 1024 with the events kernel / 4 x 256
+        // with its own events: one argon discharge of 2e4 particles 26.6 /
+        // 16.5, 4e5 28.4 / 21.8 (sampled 44.7 / 35.1), 1.5e6 37.7 / 33.5, 4e6
+        // 56.1 / 55.7; 16 of 3.2e6 in all 58.6 / 53.0, 64 of 4e6 70.0 / 62.6, 64
+        // of 1.77e7 184 / 201 (sampled 309 / 302).
+        constexpr int64_t kFuseParticles = 8000000;
+        int64_t n = 0;
+        for (int64_t v : ctx->known) n += v;
+        if (n <= kFuseParticles) {
+            p.ppt = 4;
+            p.threads = 256;
+            events_in_push = 1;
+        }
+    }
     push_shape(p.ppt, p.threads, p.general);
-    p.fuse = ctx->events_in_push && push_fusable(p.ppt, p.threads, p.general);
+    p.fuse = events_in_push && push_fusable(p.ppt, p.threads, p.general);
     const int T = p.threads * p.ppt;
     int64_t tiles = 0;
     for (int g = 0; g < B * S; ++g) tiles += (pad_cap(ctx->segc[g].cap) + T - 1) / T;
@@ -895,11 +920,11 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     p.fa.mode = kFinStep;
     p.fa.diag = ctx->diag;
     p.fa.only_b = -1;
-    p.fa.births_per_tile = p.general ? T / kBirthsDiv : 0;
+    p.fa.births_per_tile = p.general ? births_per_tile(T) : 0;
     p.ea.d = ctx->d;
     p.ea.T = T;
     p.ea.push_grid = (int32_t)p.grid;
-    p.ea.births_per_tile = T / kBirthsDiv;
+    p.ea.births_per_tile = births_per_tile(T);
     p.ea.diag = ctx->diag;
     p.ea.eepf_inv_bin = pa.eepf_inv_bin;
     p.ea.vm = ctx->diag ? (kUseY | kUseZ) : p.vm;
@@ -1353,6 +1378,7 @@ pic_status pic_set_particles(pic_ctx* ctx, int32_t batch, int32_t species, int64
         ok = ok && hipMemcpy(sc.id[p], id, nb, hipMemcpyHostToDevice) == hipSuccess;
         if (sc.z[p]) ok = ok && hipMemset(sc.z[p], 0, 2 * nb) == hipSuccess;
     }
+    ctx->known[idx] = n;
     ss.count = n;
     ss.live = n;
     ss.dead = 0;
@@ -1426,6 +1452,7 @@ pic_status pic_load_profiles(pic_ctx* ctx, int32_t batch, int32_t m, const doubl
         const SegConst& zc = ctx->segc[batch * S + s];
         if (ok && zc.z[ss[s].parity] && n[s] > 0)
             ok = hipMemsetAsync(zc.z[ss[s].parity], 0, 8ull * n[s], st) == hipSuccess;
+        ctx->known[(size_t)batch * S + s] = n[s];
         ss[s].count = ss[s].live = n[s];
         ss[s].dead = 0;
         ss[s].staged = 0;

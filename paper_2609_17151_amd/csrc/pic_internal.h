@@ -23,8 +23,11 @@ constexpr int kWindowRing = PIC_WINDOW_RING;
 constexpr int kMaxSeg = PIC_MAX_BATCH * PIC_MAX_SPECIES;   // (discharge, species) segments of a context
 constexpr int64_t kMaxTiles = 1ll << 30;                    // tile numbers fit in int32
 constexpr int kTileMin = 256;                               // smallest tile of the push (particles)
-constexpr int kBirthsDiv = 16;                              // a tile stages up to T / 16 births per step
-constexpr int kBirthsPerTileMin = kTileMin / kBirthsDiv;
+// Births a tile of T particles stages per step: T / 16, and up to 256 in the
+// small tiles, so that a small tile takes whatever births a larger one that
+// holds it would.
+__host__ __device__ constexpr int births_per_tile(int T) { return T / 4 < 256 ? T / 4 : (T / 16 > 256 ? T / 16 : 256); }
+constexpr int kBirthSlots = 4;                              // staging: one birth per 4 slots holds every tile size's
 constexpr int kMaxPushGrid = 4096;                          // workgroups of a push launch
 constexpr int kPow = 5;                                     // power time sums per species and node
 
@@ -239,7 +242,7 @@ struct DevPtrs {
     unsigned long long* eepf;    // [B][2][bins]
     double* wring;               // [B][kWindowRing][1 + (S+2) nodes_max] completed windows: samples, sums as avg
     unsigned long long* wedf;    // [B][S][2][bins] impact energies at each wall
-    Birth* births;               // [tiles_max * kBirthsPerTileMin] births staged by tile, in particle order
+    Birth* births;               // [slots / kBirthSlots] births staged by tile, in any order
     int32_t* bcnt;               // [tiles_max] births staged by each tile
     uint4* evr;                  // [slots] events of the step, packed per push workgroup from the first slot
                                  // of its tile range, in any order: (slot in tile | event bits, id, vx, vy)
