@@ -624,38 +624,54 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
     for (int s = 0; s < S; ++s) tiles_max += ctx->grid_cap[s] / kTileMin;
     if (tiles_max > kMaxTiles) rc = PIC_EINVAL;
     d.tiles_max = tiles_max;
+    char* zero_ptr = nullptr;
+    size_t zero_bytes = 0;
     if (rc == PIC_OK) {
-        d.segc = (SegConst*)A(sizeof(SegConst) * B * S);
-        d.segs = (SegState*)A(sizeof(SegState) * B * S);
-        d.disc = (DisConst*)A(sizeof(DisConst) * B);
-        d.diss = (DisState*)A(sizeof(DisState) * B);
-        d.acc = (unsigned long long*)A(8ull * B * S * kRep * nodes_max);
-        d.cnt = (unsigned long long*)A(8ull * B * S * kRep * C_N);
-        d.eacc = (unsigned long long*)A(8ull * B * nodes_max);
-        d.macc = (unsigned long long*)A(8ull * B * S * 2 * nodes_max);
-        d.pavg = (double*)A(8ull * B * S * kPow * nodes_max);
-        d.gprev = (double*)A(8ull * B * S * nodes_max);
-        d.ptmp = (double*)A(8ull * B * 2 * nodes_max);
-        d.wen = (unsigned long long*)A(8ull * B * S * 2);
-        d.rho = (double*)A(8ull * B * nodes_max);
-        d.phi = (double*)A(8ull * B * nodes_max);
-        d.ef = (double*)A(8ull * B * nodes_max);
-        d.dens = (double*)A(8ull * B * S * nodes_max);
-        d.epair = (float2*)A(8ull * B * cells_max);
-        d.avg = (double*)A(8ull * B * (S + 2) * nodes_max);
-        d.eepf = (unsigned long long*)A(8ull * B * 2 * kEepfBins);
-        d.wedf = (unsigned long long*)A(8ull * B * S * 2 * kEepfBins);
-        d.wring = (double*)A(8ull * B * kWindowRing * (1 + (size_t)(S + 2) * nodes_max));
-        d.bcnt = (int32_t*)A(4ull * tiles_max);
+        // the small arrays in one block, those that start at zero together
+        size_t bytes = 0, zero_from = 0;
+        std::vector<std::pair<void**, size_t>> at;
+        auto place = [&](auto*& p, size_t n) {
+            at.emplace_back((void**)&p, bytes);
+            bytes += (n * sizeof(*p) + 255) & ~(size_t)255;
+        };
+        place(d.segc, (size_t)B * S);
+        place(d.segs, (size_t)B * S);
+        place(d.disc, B);
+        place(d.diss, B);
+        place(d.ptmp, (size_t)B * 2 * nodes_max);
+        place(d.rho, (size_t)B * nodes_max);
+        place(d.phi, (size_t)B * nodes_max);
+        place(d.ef, (size_t)B * nodes_max);
+        place(d.dens, (size_t)B * S * nodes_max);
+        place(d.epair, (size_t)B * cells_max);
+        place(d.wring, (size_t)B * kWindowRing * (1 + (size_t)(S + 2) * nodes_max));
+        place(d.ccnt, tiles_max);
+        zero_from = bytes;
+        place(d.acc, (size_t)B * S * kRep * nodes_max);
+        place(d.cnt, (size_t)B * S * kRep * C_N);
+        place(d.eacc, (size_t)B * nodes_max);
+        place(d.macc, (size_t)B * S * 2 * nodes_max);
+        place(d.pavg, (size_t)B * S * kPow * nodes_max);
+        place(d.gprev, (size_t)B * S * nodes_max);
+        place(d.wen, (size_t)B * S * 2);
+        place(d.avg, (size_t)B * (S + 2) * nodes_max);
+        place(d.eepf, (size_t)B * 2 * kEepfBins);
+        place(d.wedf, (size_t)B * S * 2 * kEepfBins);
+        place(d.bcnt, tiles_max);
+        place(d.evg, kMaxPushGrid);
+        place(d.tick, 1);
+        place(d.ke_part, tiles_max);
+        char* block = (char*)A(bytes);
+        if (block) {
+            for (auto& x : at) *x.first = block + x.second;
+            zero_ptr = block + zero_from;
+            zero_bytes = bytes - zero_from;
+        }
         int64_t slots = 0;
         for (int s = 0; s < S; ++s) slots += ctx->grid_cap[s];
         d.births = (Birth*)A(sizeof(Birth) * (size_t)(slots / kBirthSlots + (int64_t)B * S * births_per_tile(kTileMax)));
         d.evr = (uint4*)A(16ull * slots);
         d.evq = (uint4*)A(16ull * slots);
-        d.evg = (uint32_t*)A(4ull * kMaxPushGrid);
-        d.ccnt = (uint32_t*)A(4ull * tiles_max);
-        d.tick = (unsigned long long*)A(8);
-        d.ke_part = (double*)A(8ull * tiles_max);
     }
     if (rc == PIC_OK) {
         // the largest readback: the power sums of a discharge, or its wall
@@ -694,24 +710,11 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
     ok = ok && hipMemcpy(d.segs, ss.data(), sizeof(SegState) * B * S, hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(d.disc, ctx->disc.data(), sizeof(DisConst) * B, hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(d.diss, ds.data(), sizeof(DisState) * B, hipMemcpyHostToDevice) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.acc, 0, 8ull * B * S * kRep * nodes_max, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.cnt, 0, 8ull * B * S * kRep * C_N, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.eacc, 0, 8ull * B * nodes_max, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.macc, 0, 8ull * B * S * 2 * nodes_max, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.pavg, 0, 8ull * B * S * kPow * nodes_max, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.gprev, 0, 8ull * B * S * nodes_max, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.wen, 0, 8ull * B * S * 2, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.avg, 0, 8ull * B * (S + 2) * nodes_max, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.eepf, 0, 8ull * B * 2 * kEepfBins, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.wedf, 0, 8ull * B * S * 2 * kEepfBins, st) == hipSuccess;
+    ok = ok && hipMemsetAsync(zero_ptr, 0, zero_bytes, st) == hipSuccess;
     for (int g = 0; g < B * S && ok; ++g)
         for (int k = 0; k < 2 && ok; ++k)
             if (ctx->segc[g].z[k])
                 ok = hipMemsetAsync(ctx->segc[g].z[k], 0, 8ull * pad_cap(ctx->segc[g].cap), st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.bcnt, 0, 4ull * tiles_max, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.evg, 0, 4ull * kMaxPushGrid, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.tick, 0, 8, st) == hipSuccess;
-    ok = ok && hipMemsetAsync(d.ke_part, 0, 8ull * tiles_max, st) == hipSuccess;
     for (int b = 0; b < B && ok; ++b)
         for (int s = 0; s < S && ok; ++s) {
             const pic_species_cfg& sp = cfg[b].species[s];

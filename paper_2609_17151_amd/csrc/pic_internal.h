@@ -23,9 +23,9 @@ constexpr int kWindowRing = PIC_WINDOW_RING;
 constexpr int kMaxSeg = PIC_MAX_BATCH * PIC_MAX_SPECIES;   // (discharge, species) segments of a context
 constexpr int64_t kMaxTiles = 1ll << 30;                    // tile numbers fit in int32
 constexpr int kTileMin = 256;                               // smallest tile of the push (particles)
-// Births a tile of T particles stages per step: T / 16, and up to 256 in the
-// small tiles, so that a small tile takes whatever births a larger one that
-// holds it would.
+// Births a tile of T particles stages per step: a quarter of the particles up
+// to 256, T / 16 in larger tiles.  Tiles of 1024 to 4096 stage the same number,
+// so the default of 1024 takes whatever births a tile of 4096 would.
 __host__ __device__ constexpr int births_per_tile(int T) { return T / 4 < 256 ? T / 4 : (T / 16 > 256 ? T / 16 : 256); }
 constexpr int kBirthSlots = 4;                              // staging: one birth per 4 slots holds every tile size's
 constexpr int kMaxPushGrid = 4096;                          // workgroups of a push launch
