@@ -22,10 +22,11 @@ HBM_PEAK_GBS = 8000.0
 # read cell, off, vx, vz; write the same (no draws: no id; B along y and E along
 # z never change vy, which the push leaves alone)
 BYTES_PER_PARTICLE_STEP = 32
-PUSH_SOURCES = ("pic_push_kernel.h", "pic_push_inst.h", "pic_push_vm2.hip", "pic_push.hip", "pic_device.h", "pic_internal.h")
+PUSH_SOURCES = ("pic_push_kernel.h", "pic_solve.h", "pic_push_inst.h", "pic_push_vm2.hip", "pic_push.hip",
+                "pic_device.h", "pic_internal.h")
 COUNTERS = os.path.join(ROOT, "profiles", "push_kernel_exb_counters.txt")
 STATS = os.path.join(ROOT, "profiles", "push_kernel_exb_stats.txt")
-PUSH_KERNEL = "push_kernel<4, 1024, false, false, 2, false>"
+PUSH_KERNEL = "push_kernel<4, 1024, false, false, 2, false, true>"
 
 
 _TOKENS = re.compile(r'"(?:\\.|[^"\\\n])*"|\'(?:\\.|[^\'\\\n])*\'|//[^\n]*|/\*.*?\*/', re.S)

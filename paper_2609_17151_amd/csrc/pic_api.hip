@@ -399,6 +399,7 @@ pic_status solve_after_deposit(pic_ctx* ctx, int only_b)
     fa.d = ctx->d;
     fa.mode = kFinSolve;
     fa.only_b = only_b;
+    fa.acc = ctx->d.acc;
     if (launch_finalize(fa, ctx->stream) != hipSuccess) return PIC_EHIP;
     return PIC_OK;
 }
@@ -647,7 +648,7 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
         place(d.wring, (size_t)B * kWindowRing * (1 + (size_t)(S + 2) * nodes_max));
         place(d.ccnt, tiles_max);
         zero_from = bytes;
-        place(d.acc, (size_t)B * S * kRep * nodes_max);
+        place(d.acc, (size_t)kAccSets * B * S * kRep * nodes_max);
         place(d.cnt, (size_t)B * S * kRep * C_N);
         place(d.eacc, (size_t)B * nodes_max);
         place(d.macc, (size_t)B * S * 2 * nodes_max);
@@ -846,6 +847,7 @@ struct StepPlan {
     bool general = false;
     bool fuse = false;                   // the push does the events (no events launch)
     int vm = kUseY | kUseZ;              // transverse velocity components the push carries
+    bool solve = false;                  // streaming steps after the first of a run solve for their field themselves
     int64_t grid = 1;
     EvArgs ea{};
     int64_t ev_grid = 1;
@@ -895,6 +897,10 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     }
     push_shape(p.ppt, p.threads, p.general);
     p.fuse = events_in_push && push_fusable(p.ppt, p.threads, p.general);
+    // unsampled streaming steps need no finalize in between (nothing is born,
+    // lost or averaged): the push solves for the field itself, on meshes that
+    // the lanes of four waves hold (both sides' times at the push kernel)
+    p.solve = !p.general && !ctx->diag && nn_max <= kSolveNodes;
     const int T = p.threads * p.ppt;
     int64_t tiles = 0;
     for (int g = 0; g < B * S; ++g) tiles += (pad_cap(ctx->segc[g].cap) + T - 1) / T;
@@ -906,6 +912,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     pa.eepf_inv_bin = (float)(kEepfBins / ctx->eepf_emax);
     pa.nodes_max_dyn = nn_max;
     pa.cells_max_dyn = nc_max;
+    pa.acc = ctx->d.acc;
     uint64_t key = 1469598103934665603ull;
     auto mix = [&](uint64_t v) { key = (key ^ v) * 1099511628211ull; };
     mix((uint64_t)ctx->diag);
@@ -918,11 +925,14 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     mix((uint64_t)p.threads);
     mix((uint64_t)p.general);
     mix((uint64_t)p.fuse);
+    mix((uint64_t)p.solve);
     mix((uint64_t)p.grid);
     p.fa.d = ctx->d;
     p.fa.mode = kFinStep;
     p.fa.diag = ctx->diag;
     p.fa.only_b = -1;
+    p.fa.steps = 1;
+    p.fa.acc = ctx->d.acc;
     p.fa.births_per_tile = p.general ? births_per_tile(T) : 0;
     p.ea.d = ctx->d;
     p.ea.T = T;
@@ -943,6 +953,8 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
 // queue `n` steps on stream st; `prof` wraps every launch in an event pair
 pic_status enqueue_steps(pic_ctx* ctx, const StepPlan& p, int n, hipStream_t st, bool prof)
 {
+    const size_t acc_words = (size_t)ctx->B * ctx->S * kRep * ctx->d.nodes_max;
+    auto set = [&](int it) { return ctx->d.acc + (size_t)(it % kAccSets) * acc_words; };
     for (int it = 0; it < n; ++it) {
         if (ctx->sort_every > 0 && ++ctx->steps_since_sort >= ctx->sort_every) {
             ctx->steps_since_sort = 0;
@@ -951,17 +963,34 @@ pic_status enqueue_steps(pic_ctx* ctx, const StepPlan& p, int n, hipStream_t st,
                     hipSuccess)
                     return PIC_EHIP;
         }
+        PushArgs pa = p.pa;
+        if (p.solve) {
+            // deposit sets go round: this step's, the one it solves for (not
+            // in the first step, whose field the last finalize left), and the
+            // one it clears
+            pa.acc = set(it);
+            pa.acc_in = it > 0 ? set(it - 1) : nullptr;
+            pa.acc_clear = set(it + 1);
+        }
         const int pp = prof ? prof_begin(ctx) : -1;
-        if (launch_push(p.pa, p.ppt, p.threads, p.general, p.fuse, p.vm, p.grid, st) != hipSuccess) return PIC_EHIP;
+        if (launch_push(pa, p.ppt, p.threads, p.general, p.fuse, p.vm, p.grid, st) != hipSuccess) return PIC_EHIP;
         prof_end(ctx, pp, 0);
         if (p.general && !p.fuse) {
             const int pv = prof ? prof_begin(ctx) : -1;
             if (launch_events(p.ea, p.ev_grid, st) != hipSuccess) return PIC_EHIP;
             prof_end(ctx, pv, 1);
         }
-        const int pe = prof ? prof_begin(ctx) : -1;
-        if (launch_finalize(p.fa, st) != hipSuccess) return PIC_EHIP;
-        prof_end(ctx, pe, -1);
+        if (!p.solve || it == n - 1) {
+            FinArgs fa = p.fa;
+            if (p.solve) {
+                fa.steps = n;
+                fa.acc = set(n - 1);
+                fa.acc_clear = n > 1 ? set(n - 2) : nullptr;
+            }
+            const int pe = prof ? prof_begin(ctx) : -1;
+            if (launch_finalize(fa, st) != hipSuccess) return PIC_EHIP;
+            prof_end(ctx, pe, -1);
+        }
         // the general kernel leaves holes where particles were absorbed
         if (p.general && ++ctx->steps_since_compact >= ctx->compact_every) {
             ctx->steps_since_compact = 0;

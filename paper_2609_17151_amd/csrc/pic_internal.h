@@ -56,6 +56,10 @@ constexpr uint32_t kFlagStall = 1u << 4;
 // copy w % kRep, so no address takes more than 1/kRep of the atomics (device-
 // scope atomics on one address serialise); readers sum the copies.
 constexpr int kRep = 1;
+// Sets of deposit sums: a streaming step deposits into one while it reads the
+// step before's and clears the one before that.  Everything else uses the first.
+constexpr int kAccSets = 3;
+constexpr int kSolveNodes = 1024;          // largest mesh a streaming push solves itself (four nodes per lane of four waves)
 // event counters per segment
 enum { C_ABS0, C_ABS1, C_SEE0, C_SEE1, C_CAND, C_NULL, C_VIOL, C_DROP, C_REN, C_COLL, C_N = C_COLL + kMaxChan };
 
@@ -224,7 +228,7 @@ struct DevPtrs {
     SegState* segs;              // [B*S]
     DisConst* disc;              // [B]
     DisState* diss;              // [B]
-    unsigned long long* acc;     // [B][S][kRep][nodes_max] deposit sums (fixed point)
+    unsigned long long* acc;     // [kAccSets][B][S][kRep][nodes_max] deposit sums (fixed point)
     unsigned long long* cnt;     // [B][S][kRep][C_N] event counters
     unsigned long long* eacc;    // [B][nodes_max] electron energy deposit (eV, fixed point 2^20)
     unsigned long long* macc;    // [B][S][2][nodes_max] flux and x-momentum flux sums of the step (fixed point)

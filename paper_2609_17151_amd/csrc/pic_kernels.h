@@ -11,6 +11,11 @@ struct PushArgs {
     int32_t diag;                 // accumulate electron energy deposit and EEPF
     float eepf_inv_bin;           // 1 / bin width (eV)
     int32_t nodes_max_dyn, cells_max_dyn;
+    unsigned long long* acc;      // deposit sums of this step ([B][S][kRep][nodes_max])
+    // a streaming step that solves for its field itself (SOLVE): the sums of
+    // the step before, and the set to clear for the next step
+    const unsigned long long* acc_in;
+    unsigned long long* acc_clear;
 };
 
 // The events kernel: the push's events of a step (collisions, renewals,
@@ -38,6 +43,9 @@ struct FinArgs {
     int32_t only_b;               // -1: all discharges (grid = B), else this one (grid = 1)
     int32_t births_per_tile;      // staging slots of a push tile (0: the step cannot have births)
     float eepf_inv_bin;           // 1 / bin width (eV) of the bulk electron energy distribution
+    int32_t steps;                // steps since the last finalize
+    unsigned long long* acc;      // deposit sums to solve for (cleared)
+    unsigned long long* acc_clear;   // another set to clear, or null
     double t_ext;
     const double* rho_ext;
     double* phi_out;
@@ -77,7 +85,7 @@ struct ReadArgs {
 hipError_t launch_read(const ReadArgs& a, hipStream_t st);
 hipError_t launch_profile_load(const ProfileArgs& a, hipStream_t st);
 hipError_t launch_push(const PushArgs& a, int ppt, int threads, bool general, bool fuse, int vm, int64_t grid,
-                       hipStream_t st);
+                       hipStream_t st);      // acc_in set: the streaming step that solves for its field
 // the same for one set of velocity components (one source file each)
 template <int VM>
 hipError_t launch_push_vm(const PushArgs& a, int ppt, int threads, bool general, bool fuse, int64_t grid,

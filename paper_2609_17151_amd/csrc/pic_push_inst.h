@@ -31,8 +31,10 @@ hipError_t launch_push_vm<PIC_PUSH_VM>(const PushArgs& a, int ppt, int threads, 
     const dim3 g((unsigned)grid);
 #define PIC_LAUNCH(P, B, G, F)                                                                       \
     if (ppt == P && threads == B && general == G && fuse == F) {                                     \
-        if (a.diag) hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM, true>), g, dim3(B), lds, st, a); \
-        else hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM, false>), g, dim3(B), lds, st, a);       \
+        if (a.diag) hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM, true, false>), g, dim3(B), lds, st, a); \
+        else if (!G && a.acc_in)                                                                             \
+            hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM, false, !G>), g, dim3(B), lds, st, a);    \
+        else hipLaunchKernelGGL((push_kernel<P, B, G, F, PIC_PUSH_VM, false, false>), g, dim3(B), lds, st, a); \
         return hipGetLastError();                                                                    \
     }
     PIC_KERNELS(PIC_LAUNCH)
@@ -48,8 +50,8 @@ int push_occupancy_vm<PIC_PUSH_VM>(int ppt, int threads, bool general, bool fuse
     if (ppt == P && threads == B && general == G && fuse == F) {                                             \
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(                                                    \
                 &nb,                                                                                         \
-                diag ? reinterpret_cast<const void*>(push_kernel<P, B, G, F, PIC_PUSH_VM, true>)             \
-                     : reinterpret_cast<const void*>(push_kernel<P, B, G, F, PIC_PUSH_VM, false>),           \
+                diag ? reinterpret_cast<const void*>(push_kernel<P, B, G, F, PIC_PUSH_VM, true, false>)      \
+                     : reinterpret_cast<const void*>(push_kernel<P, B, G, F, PIC_PUSH_VM, false, !G>),       \
                 B, lds) != hipSuccess)                                                                       \
             nb = 0;                                                                                          \
     }

@@ -46,6 +46,7 @@
 #include "pic_device.h"
 #include "pic_internal.h"
 #include "pic_kernels.h"
+#include "pic_solve.h"
 
 namespace pic {
 
@@ -523,20 +524,105 @@ __device__ __forceinline__ bool event_record(const DevPtrs& d, const EvPass& ps,
 __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, const EvPass& ps, bool act,
                                             uint4 rec, uint4 rq);
 
-// a workgroup barrier that orders LDS only: __syncthreads also waits for the
-// wave's outstanding accesses to global memory
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __device__ __forceinline__ int64_t readlane64(int64_t v, int l)
 {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, l);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
     return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// The field of a periodic mesh of up to kSolveNodes nodes from the deposit sums
+// `acc` of its species, as the finalize kernel forms it (the same operations in
+// the same order), straight into the E pairs of the gather; s_a: LDS for nn
+// doubles.  The whole workgroup calls it.
+template <int BS>
+__device__ __forceinline__ void solve_pairs(const DevPtrs& d, const DisConst& dc, int b,
+                                            const unsigned long long* acc, double* s_a, double* s_w, Run* s_run,
+                                            float2* ep)
+{
+    const int S = d.S, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int nn = dc.n_nodes;
+    const unsigned long long* ab = acc + (size_t)b * S * kRep * d.nodes_max;
+    for (int base = wid * 64; base < nn; base += BS) {
+        const int i = base + lane;
+        double r = 0.0;
+        if (i < nn) {
+            unsigned long long v[kMaxSpecies];
+#pragma unroll
+            for (int s = 0; s < kMaxSpecies; ++s) {
+                v[s] = 0ull;
+                if (s < S)
+                    for (int q = 0; q < kRep; ++q) v[s] += ab[((size_t)s * kRep + q) * d.nodes_max + i];
+            }
+            r = dc.rho_bg;
+#pragma unroll
+            for (int s = 0; s < kMaxSpecies; ++s)
+                if (s < S) r += dc.q[s] * ((double)v[s] * dc.dens_coef[s]);
+            s_a[i] = r;
+        }
+        const double w = wave_total_f64(r);
+        if (lane == 0) s_w[base >> 6] = w;
+    }
+    lds_barrier();
+    constexpr int kN = 4;                                // nodes per thread
+    const int i0 = tid * kN;
+    const bool active = wid * 64 * kN < nn;
+    double g[kN];
+    Run inc{0.0, 0.0, 0.0, 0.0};
+    if (active) {
+        double tot = 0.0;
+#pragma unroll
+        for (int w = 0; w < kSolveNodes / 64; ++w) tot += w * 64 < nn ? s_w[w] : 0.0;
+        const double mean = tot / nn, c2 = dc.c2;
+        Run loc{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int j = 0; j < kN; ++j) {
+            const int i = i0 + j;
+            g[j] = 0.0;
+            if (i < nn) {
+                g[j] = i >= 1 ? (s_a[i] - mean) * c2 : 0.0;
+                loc.n += 1.0;
+                loc.S += g[j];
+                loc.P += loc.S;
+                loc.Q += loc.P;
+            }
+        }
+        inc = wave_run_scan(loc);
+        if (lane == 63) s_run[wid] = inc;
+    }
+    lds_barrier();
+    if (active) {
+        Run before, all;
+        few_runs(s_run, (nn + 64 * kN - 1) / (64 * kN), wid, before, all);
+        const double d0 = all.P / nn;
+        const double pm = (d0 * (0.5 * (double)nn * (double)(nn - 1)) - (all.Q - all.P)) / nn;
+        Run lx;
+        lx.n = __shfl_up(inc.n, 1, 64);
+        lx.S = __shfl_up(inc.S, 1, 64);
+        lx.P = __shfl_up(inc.P, 1, 64);
+        lx.Q = 0.0;
+        if (lane == 0) lx = Run{0.0, 0.0, 0.0, 0.0};
+        const Run ex = wid > 0 ? run_combine(before, lx) : lx;
+        double G = ex.S, P = ex.P;
+#pragma unroll
+        for (int j = 0; j < kN; ++j) {
+            const int i = i0 + j;
+            if (i >= nn) break;
+            G += g[j];
+            P += G;
+            double ph = 0.0 + (double)i * d0 - (P - G);
+            if (i == 0) ph = 0.0;
+            s_a[i] = ph - pm;
+        }
+    }
+    lds_barrier();
+    const double h = dc.inv_2dx;
+    for (int c = tid; c < nn; c += BS) {
+        const int cm = c == 0 ? nn - 1 : c - 1, c1 = c + 1 == nn ? 0 : c + 1, c2 = c1 + 1 == nn ? 0 : c1 + 1;
+        ep[c] = dc.field_solve ? make_float2((float)((s_a[cm] - s_a[c1]) * h), (float)((s_a[c] - s_a[c2]) * h))
+                               : make_float2(0.0f, 0.0f);
+    }
+    lds_barrier();                                       // s_a is free again
 }
 
 // FUSE: the workgroup does its own tile range's events after its push (no
@@ -549,7 +635,15 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l)
 // place in one round, a lane each, in every wave (no LDS, no barrier); then the
 // first tile's particles, the segment's constants and the discharge's E pairs
 // are all in flight together, and one barrier later the particles are pushed.
-template <int PPT, int BS, bool GENERAL, bool FUSE, int VM, bool DIAG>
+//
+// SOLVE (streaming steps after the first of a run): every workgroup solves for
+// the field itself, from the deposit of the step before, so the steps of a run
+// are one launch each and the finalize kernel runs once at its end.  A finalize
+// in between is one workgroup with the GPU idle around it, 4 to 6 us and two
+// launch gaps of 1.2 to 3 us.  Per step, 6.5e4 particles on 128 cells: 11.2
+// us with the finalize, 7.9 us with the solve; 8e6 on 1024 cells: 51.8 and
+// 47.8 us; 6.4e7: 424 and 418 us.
+template <int PPT, int BS, bool GENERAL, bool FUSE, int VM, bool DIAG, bool SOLVE>
 __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
 {
     constexpr int kBS = BS;
@@ -568,6 +662,13 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
     __shared__ unsigned long long s_wen[2];   // energy carried into each wall by the run (eV, 2^20)
     __shared__ float s_red[kBS / 64];
     __shared__ uint32_t s_evn;                // events recorded by the workgroup
+    __shared__ double s_w[SOLVE ? kSolveNodes / 64 : 1];
+    __shared__ Run s_run[SOLVE ? 4 : 1];
+
+    if (SOLVE) {
+        const size_t words = (size_t)NS * kRep * d.nodes_max;
+        for (size_t i = (size_t)blockIdx.x * kBS + tid; i < words; i += (size_t)gridDim.x * kBS) a.acc_clear[i] = 0ull;
+    }
 
     // the tiles of every segment: lane g holds segment g's row, or (more than
     // 64 segments) the first tiles in LDS
@@ -634,7 +735,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
 
     // the deposit histogram's node sums go out
     auto flush_nodes = [&](int ft, int nt) {
-        unsigned long long* acc_s = d.acc + ((size_t)sg * kRep + blockIdx.x % kRep) * d.nodes_max;
+        unsigned long long* acc_s = a.acc + ((size_t)sg * kRep + blockIdx.x % kRep) * d.nodes_max;
         const int nn = k.nc + (k.periodic ? 0 : 1);
         for (int i = ft; i < nn; i += nt) {
             const unsigned long long v = hist_node(hist, i, k.nc, k.periodic);
@@ -780,8 +881,12 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
                 lds_barrier();
             }
             if (b_n != b) {
-                const float2* epg = d.epair + (size_t)b_n * d.cells_max;
-                for (int i = tid; i < a.cells_max_dyn; i += kBS) ep[i] = epg[i];
+                if (SOLVE) {
+                    solve_pairs<BS>(d, d.disc[b_n], b_n, a.acc_in, reinterpret_cast<double*>(hist), s_w, s_run, ep);
+                } else {
+                    const float2* epg = d.epair + (size_t)b_n * d.cells_max;
+                    for (int i = tid; i < a.cells_max_dyn; i += kBS) ep[i] = epg[i];
+                }
             }
             for (int i = tid; i < nn_max; i += kBS) hist[i] = 0ull;
             if (DIAG) {
