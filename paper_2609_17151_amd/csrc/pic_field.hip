@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     const bool births_wg = split && (blockIdx.x & 1u) == 0u;
     const int b = a.only_b >= 0 ? a.only_b : (int)(split ? blockIdx.x >> 1 : blockIdx.x);
     const int S = d.S, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const DisConst& dc = d.disc[b];
+    CDis& dc = const_dis(d, b);
     DisState& ds = d.diss[b];
     const int nn = dc.n_nodes, nc = dc.n_cells;
     const int periodic = dc.bc == PIC_BC_PERIODIC;
@@ -106,15 +106,15 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     };
     if (births_wg) {
         const SegState& s0 = d.segs[b * S + 0];
-        const SegConst& c0 = d.segc[b * S + 0];
+        CSeg& c0 = const_seg(d, b * S + 0);
         const int64_t slot0 = s0.count, slot1 = S > 1 ? d.segs[b * S + 1].count : 0;
         const uint32_t id0 = s0.next_id, id1 = S > 1 ? d.segs[b * S + 1].next_id : 0u;
         const int io0 = s0.parity, io1 = S > 1 ? d.segs[b * S + 1].parity : 0;
-        const int64_t cap0 = c0.cap, cap1 = S > 1 ? d.segc[b * S + 1].cap : 0;
+        const int64_t cap0 = c0.cap, cap1 = S > 1 ? const_seg(d, b * S + 1).cap : 0;
         int64_t pos0 = slot0, pos1 = slot1;
         for (int src = 0; src < S; ++src) {
             const int g = b * S + src;
-            if (src > 0 && !d.segc[g].emits) continue;
+            if (src > 0 && !const_seg(d, g).emits) continue;
             if (d.segs[g].staged == 0) continue;          // no tile of this segment staged a birth
             const int64_t tf = d.segs[g].tile_first, nt = d.segs[g].ntiles;
             const bool pair = src == 0 && S > 1;            // ionization: an ion with every electron
@@ -162,25 +162,25 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
                 for (uint32_t q = 0; q < nk; ++q) rank += tb[q].key < bb.key;
                 const int64_t e = pos0 + t0 + rank;
                 if (e < cap0) {
-                    c0.cell[io0][e] = bb.cell;
-                    c0.off[io0][e] = bb.off;
-                    c0.vx[io0][e] = bb.vx;
-                    c0.vy[io0][e] = bb.vy;
-                    c0.vz[io0][e] = bb.vz;
-                    c0.id[io0][e] = id0 + (uint32_t)(e - slot0);
-                    if (c0.z[0]) c0.z[io0][e] = 0.0;
+                    ((PIC_GLOBAL int32_t*)c0.cell[io0])[e] = bb.cell;
+                    ((PIC_GLOBAL float*)c0.off[io0])[e] = bb.off;
+                    ((PIC_GLOBAL float*)c0.vx[io0])[e] = bb.vx;
+                    ((PIC_GLOBAL float*)c0.vy[io0])[e] = bb.vy;
+                    ((PIC_GLOBAL float*)c0.vz[io0])[e] = bb.vz;
+                    ((PIC_GLOBAL uint32_t*)c0.id[io0])[e] = id0 + (uint32_t)(e - slot0);
+                    if (c0.z[0]) ((PIC_GLOBAL double*)c0.z[io0])[e] = 0.0;
                 }
                 if (pair) {
-                    const SegConst& c1 = d.segc[b * S + 1];
+                    CSeg& c1 = const_seg(d, b * S + 1);
                     const int64_t q = pos1 + t0 + rank;
                     if (q < cap1) {
-                        c1.cell[io1][q] = bb.cell;
-                        c1.off[io1][q] = bb.off;
-                        c1.vx[io1][q] = bb.ivx;
-                        c1.vy[io1][q] = bb.ivy;
-                        c1.vz[io1][q] = bb.ivz;
-                        c1.id[io1][q] = id1 + (uint32_t)(q - slot1);
-                        if (c1.z[0]) c1.z[io1][q] = 0.0;
+                        ((PIC_GLOBAL int32_t*)c1.cell[io1])[q] = bb.cell;
+                        ((PIC_GLOBAL float*)c1.off[io1])[q] = bb.off;
+                        ((PIC_GLOBAL float*)c1.vx[io1])[q] = bb.ivx;
+                        ((PIC_GLOBAL float*)c1.vy[io1])[q] = bb.ivy;
+                        ((PIC_GLOBAL float*)c1.vz[io1])[q] = bb.ivz;
+                        ((PIC_GLOBAL uint32_t*)c1.id[io1])[q] = id1 + (uint32_t)(q - slot1);
+                        if (c1.z[0]) ((PIC_GLOBAL double*)c1.z[io1])[q] = 0.0;
                     }
                 }
             }

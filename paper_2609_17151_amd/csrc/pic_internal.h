@@ -188,14 +188,16 @@ struct DisState {
 // The source of the electrode at x = 0: its voltage V(t), and the charge per
 // area a current source has delivered since t = 0 (the integral of
 // j_amp sin(w t + phase)).
-__host__ __device__ inline double source_voltage(const DisConst& dc, double t)
+template <typename D>
+__host__ __device__ inline double source_voltage(const D& dc, double t)
 {
     const double w = 6.283185307179586476925286766559 * dc.v_freq;
     if (dc.waveform == PIC_WAVE_TWO_HARMONIC) return dc.v_amp * (cos(w * t + dc.v_phase) + cos(2.0 * w * t));
     return dc.v_amp * sin(w * t + dc.v_phase);
 }
 
-__host__ __device__ inline double source_charge(const DisConst& dc, double t)
+template <typename D>
+__host__ __device__ inline double source_charge(const D& dc, double t)
 {
     if (dc.drive != PIC_DRIVE_CURRENT) return 0.0;
     const double w = 6.283185307179586476925286766559 * dc.v_freq;
@@ -205,7 +207,8 @@ __host__ __device__ inline double source_charge(const DisConst& dc, double t)
 // Charge per area particles have brought to the electrode at x = 0, from the
 // event counters [S][kRep][C_N] of one discharge: absorbed particles bring
 // theirs, each secondary electron emitted there takes one away.
-__host__ __device__ inline double collected_charge(const DisConst& dc, const unsigned long long* cnt, int S)
+template <typename D>
+__host__ __device__ inline double collected_charge(const D& dc, const unsigned long long* cnt, int S)
 {
     double q = 0.0;
     unsigned long long see = 0ull;
@@ -259,5 +262,33 @@ struct DevPtrs {
     int32_t nodes_max, cells_max;
     int64_t tiles_max;
 };
+
+// Particle arrays are device global memory.  Reaching them through
+// address-space-1 pointers lets the compiler use global instead of flat
+// memory instructions (measured 8 % faster on the streaming push).
+#define PIC_GLOBAL __attribute__((address_space(1)))
+
+// What no kernel writes is reached through address-space-4 pointers: loads of
+// it at a uniform place go through the scalar cache, many at a time and next
+// to one another, also after the kernel has stored something, where the
+// compiler otherwise reads uniform values with vector loads, each waiting for
+// the stores and atomics before it.  Per step, before and after: one sampled
+// argon discharge of 4e5 particles 37.7 and 33.3 us, unsampled 21.1 and 20.4;
+// 64 discharges of 4.9e7 480 and 455; forty swarms 91.6 and 87.9.
+#define PIC_CONST __attribute__((address_space(4)))
+typedef const PIC_CONST SegConst CSeg;
+typedef const PIC_CONST DisConst CDis;
+__device__ __forceinline__ CSeg& const_seg(const DevPtrs& d, int g) { return ((CSeg*)(uintptr_t)d.segc)[g]; }
+__device__ __forceinline__ CDis& const_dis(const DevPtrs& d, int b) { return ((CDis*)(uintptr_t)d.disc)[b]; }
+// the step number and a segment's place, which only the finalize kernel and the
+// compaction change: for the push and the events kernel
+__device__ __forceinline__ uint32_t const_step(const DevPtrs& d, int b)
+{
+    return (uint32_t)((const PIC_CONST DisState*)(uintptr_t)d.diss)[b].step;
+}
+__device__ __forceinline__ const PIC_CONST SegState& const_state(const DevPtrs& d, int g)
+{
+    return ((const PIC_CONST SegState*)(uintptr_t)d.segs)[g];
+}
 
 }  // namespace pic

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(BS) void events_kernel(EvArgs a)
         const uint32_t nx = ck + stride;
         uint4 rec_n = make_uint4(0u, 0u, 0u, 0u), rq_n = rec_n;
         const bool act_n = nx < nchunk && records(nx, rec_n, rq_n);
-        event_chunk(d, s_pref, e, act, rec, rq);
+        event_chunk(d, s_pref, e, act, rec, rq, -1, 0, nullptr, 0);
         rec = rec_n;
         rq = rq_n;
         act = act_n;

@@ -95,11 +95,6 @@ __device__ __forceinline__ void global_deposit(unsigned long long* acc, int c, f
     atomicAdd(&acc[c1], (unsigned long long)q);
 }
 
-// Particle arrays are device global memory.  Reaching them through
-// address-space-1 pointers lets the compiler use global instead of flat
-// memory instructions (measured 8 % faster on the streaming push).
-#define PIC_GLOBAL __attribute__((address_space(1)))
-
 // NT: non-temporal (streaming) accesses, which leave the caches to the rest
 // of the step.  Measured on the 64-discharge argon sweep (4.7e7 particles):
 // the general push 541 -> 461 us (each at its fastest tile shape) and the
@@ -107,7 +102,7 @@ __device__ __forceinline__ void global_deposit(unsigned long long* acc, int c, f
 // whose particle arrays fit the Infinity Cache between steps, is 11 % slower
 // with them and does not use them.
 template <int N, typename V, bool NT = false, typename S>
-__device__ __forceinline__ void vload(const S* __restrict__ p, S* out)
+__device__ __forceinline__ void vload(const PIC_GLOBAL S* p, S* out)
 {
     if constexpr (N % 4 == 0) {
         typedef S NV __attribute__((ext_vector_type(4)));
@@ -130,7 +125,7 @@ __device__ __forceinline__ void vload(const S* __restrict__ p, S* out)
 }
 
 template <int N, typename V, bool NT = false, typename S>
-__device__ __forceinline__ void vstore(S* __restrict__ p, const S* in)
+__device__ __forceinline__ void vstore(PIC_GLOBAL S* p, const S* in)
 {
     if constexpr (N % 4 == 0) {
         typedef S NV __attribute__((ext_vector_type(4)));
@@ -196,7 +191,7 @@ __device__ __forceinline__ double sgpr(double v)
 }
 
 template <bool GENERAL, int VM, bool DIAG>
-__device__ __forceinline__ PushC push_consts(const SegConst& sc, const DisConst& dc, const DisState& ds)
+__device__ __forceinline__ PushC push_consts(CSeg& sc, CDis& dc, uint32_t step)
 {
     PushC k;
     k.nc = dc.n_cells;
@@ -218,7 +213,7 @@ __device__ __forceinline__ PushC push_consts(const SegConst& sc, const DisConst&
         k.t32 = sc.t32;
         k.key0 = dc.key0;
         k.key1 = dc.key1;
-        k.step = (uint32_t)ds.step;
+        k.step = step;
         if (VM & kUseZ) {                    // renewal sums vz
             k.renew_lz = sc.renew_lz;
             k.dt_d = sc.dt_d;
@@ -423,7 +418,7 @@ __device__ __forceinline__ void add_bulk(CT* eepf, float eepf_inv_bin, float eps
 }
 
 // one particle's samples in the events pass: hme = m / 2e
-__device__ __forceinline__ void sample_particle(const DevPtrs& d, const SegConst& sc, const DisConst& dc, int b, int sg,
+__device__ __forceinline__ void sample_particle(const DevPtrs& d, CSeg& sc, CDis& dc, int b, int sg,
                                                 bool electron, float eepf_inv_bin, int c, float f, float ux,
                                                 float uy, float uz)
 {
@@ -446,7 +441,7 @@ __device__ __forceinline__ void sample_particle(const DevPtrs& d, const SegConst
 // hundred of the ions').  When it added every candidate's samples itself, up to
 // seven atomics on global memory each, a step of 64 sampled discharges with
 // 1.77e7 particles took 340 us, now 280.
-__device__ __forceinline__ void sample_change(const DevPtrs& d, const SegConst& sc, const DisConst& dc, int b, int sg,
+__device__ __forceinline__ void sample_change(const DevPtrs& d, CSeg& sc, CDis& dc, int b, int sg,
                                               bool electron, float eepf_inv_bin, int c, float f, float ox, float oy,
                                               float oz, float ux, float uy, float uz)
 {
@@ -561,7 +556,8 @@ struct EvPass {
 __device__ __forceinline__ bool event_record(const DevPtrs& d, const EvPass& ps, int g, uint32_t nev, uint32_t kc,
                                              uint4& rec, uint4& rq);
 __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, const EvPass& ps, bool act,
-                                            uint4 rec, uint4 rq);
+                                            uint4 rec, uint4 rq, int k_sg, int32_t k_first, char* k_base,
+                                            int64_t k_stride);
 
 __device__ __forceinline__ int64_t readlane64(int64_t v, int l)
 {
@@ -575,7 +571,7 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l)
 // the same order), straight into the E pairs of the gather; s_a: LDS for nn
 // doubles.  The whole workgroup calls it.
 template <int BS>
-__device__ __forceinline__ void solve_pairs(const DevPtrs& d, const DisConst& dc, int b,
+__device__ __forceinline__ void solve_pairs(const DevPtrs& d, CDis& dc, int b,
                                             const unsigned long long* acc, double* s_a, double* s_w, Run* s_run,
                                             float2* ep)
 {
@@ -701,6 +697,12 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
     __shared__ unsigned long long s_wen[2];   // energy carried into each wall by the run (eV, 2^20)
     __shared__ float s_red[kBS / 64];
     __shared__ uint32_t s_evn;                // events recorded by the workgroup
+    // FUSE: the first events' records stay in LDS (the others' go to memory),
+    // one round trip less in a step that is little else (with the table rows
+    // read together: 4e5 particles of argon 21.5 -> 21.1 us per step, forty
+    // swarms 95.2 -> 91.6)
+    constexpr uint32_t kEvLds = FUSE ? 128u : 1u;
+    __shared__ uint4 s_rec[kEvLds], s_rq[kEvLds];
     __shared__ double s_w[SOLVE ? kSolveNodes / 64 : 1];
     __shared__ Run s_run[SOLVE ? 4 : 1];
 
@@ -760,7 +762,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
     int64_t n = 0;
     char* base_p = nullptr;                   // its particle arrays, `stride` bytes apart
     int64_t stride = 0;
-    double* p_z = nullptr;
+    PIC_GLOBAL double* p_z = nullptr;
     PushC k{};
     // a fixed contiguous range of tiles per workgroup
     const int32_t chunk = (NT + (int32_t)gridDim.x - 1) / (int32_t)gridDim.x;
@@ -870,20 +872,20 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
             n = count;                                // updated in place: the copy in use
             base_n += (int64_t)par * kFields * stride;
             b_n = seg_discharge(sg_n, S);
-            const SegConst& sc = d.segc[sg_n];
-            if (GENERAL && UZ) p_z = sc.z[par];
-            kv = push_consts<GENERAL, VM, DIAG>(sc, d.disc[b_n], d.diss[b_n]);   // in flight with the particles
+            CSeg& sc = const_seg(d, sg_n);
+            if (GENERAL && UZ) p_z = (PIC_GLOBAL double*)sc.z[par];
+            kv = push_consts<GENERAL, VM, DIAG>(sc, const_dis(d, b_n), const_step(d, b_n));   // in flight with the particles
         }
         const int32_t tin = t - first_n;
         const int64_t tile0 = (int64_t)tin * T;
         const int rem = n - tile0 < T ? (int)(n - tile0) : T;     // slots in use
         char* pt = base_n + tile0 * 4;
-        int32_t* p_cell = reinterpret_cast<int32_t*>(pt);
-        float* p_off = reinterpret_cast<float*>(pt + stride);
-        float* p_vx = reinterpret_cast<float*>(pt + 2 * stride);
-        float* p_vy = reinterpret_cast<float*>(pt + 3 * stride);
-        float* p_vz = reinterpret_cast<float*>(pt + 4 * stride);
-        const uint32_t* p_id = reinterpret_cast<const uint32_t*>(pt + 5 * stride);
+        PIC_GLOBAL int32_t* p_cell = (PIC_GLOBAL int32_t*)(pt);
+        PIC_GLOBAL float* p_off = (PIC_GLOBAL float*)(pt + stride);
+        PIC_GLOBAL float* p_vx = (PIC_GLOBAL float*)(pt + 2 * stride);
+        PIC_GLOBAL float* p_vy = (PIC_GLOBAL float*)(pt + 3 * stride);
+        PIC_GLOBAL float* p_vz = (PIC_GLOBAL float*)(pt + 4 * stride);
+        const PIC_GLOBAL uint32_t* p_id = (const PIC_GLOBAL uint32_t*)(pt + 5 * stride);
         const int slot0 = tid * PPT;
 
         int32_t cell[PPT];
@@ -906,7 +908,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
         }
         // ids only where every particle draws; the events pass reads the
         // others' from their slots
-        if (GENERAL && (sw ? d.segc[sg_n].nch : k.nch) > 0) {
+        if (GENERAL && (sw ? const_seg(d, sg_n).nch : k.nch) > 0) {
             vload<PPT, uint4, GENERAL>(p_id + slot0, pid);
         } else {
 #pragma unroll
@@ -921,7 +923,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
             }
             if (b_n != b) {
                 if (SOLVE) {
-                    solve_pairs<BS>(d, d.disc[b_n], b_n, a.acc_in, reinterpret_cast<double*>(hist), s_w, s_run, ep);
+                    solve_pairs<BS>(d, const_dis(d, b_n), b_n, a.acc_in, reinterpret_cast<double*>(hist), s_w, s_run, ep);
                 } else {
                     const float2* epg = d.epair + (size_t)b_n * d.cells_max;
                     for (int i = tid; i < a.cells_max_dyn; i += kBS) ep[i] = epg[i];
@@ -1017,7 +1019,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
 #pragma unroll
             for (int j = 0; j < PPT; ++j) walls |= keep[j] && (unsigned)cell[j] >= (unsigned)nc;
             if (__any(walls)) {
-                const SegConst& sc = d.segc[sg];
+                CSeg& sc = const_seg(d, sg);
 #pragma unroll
                 for (int j = 0; j < PPT; ++j) {
                     if (!(keep[j] && (unsigned)cell[j] >= (unsigned)nc)) continue;
@@ -1174,15 +1176,23 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
                 wbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)wbase);
                 // the particle after the push: slot, event bits, id, velocity,
                 // position and tile, so the events pass reads the record only
-                const size_t r0 = (size_t)t_begin * T + wbase;
+                const size_t r0 = (size_t)t_begin * T;
+                uint32_t at = wbase + below;
 #pragma unroll
                 for (int j = 0; j < PPT; ++j) {
                     if (evw[j]) {
-                        d.evr[r0 + below] = make_uint4(evw[j] | (uint32_t)(slot0 + j) | ((uint32_t)sg << kEvSegShift),
-                                                       pid[j], __float_as_uint(vx[j]), __float_as_uint(vy[j]));
-                        d.evq[r0 + below] = make_uint4(__float_as_uint(vz[j]), (uint32_t)cell[j],
-                                                       __float_as_uint(off[j]), (uint32_t)t);
-                        ++below;
+                        const uint4 rec = make_uint4(evw[j] | (uint32_t)(slot0 + j) | ((uint32_t)sg << kEvSegShift),
+                                                     pid[j], __float_as_uint(vx[j]), __float_as_uint(vy[j]));
+                        const uint4 rq = make_uint4(__float_as_uint(vz[j]), (uint32_t)cell[j],
+                                                    __float_as_uint(off[j]), (uint32_t)t);
+                        if (FUSE && at < kEvLds) {
+                            s_rec[at] = rec;
+                            s_rq[at] = rq;
+                        } else {
+                            d.evr[r0 + at] = rec;
+                            d.evq[r0 + at] = rq;
+                        }
+                        ++at;
                     }
                 }
             }
@@ -1216,8 +1226,18 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
                         (RY ? kUseY : 0) | (RZ ? kUseZ : 0)};
         for (uint32_t kc = (uint32_t)wid; kc < nch; kc += (uint32_t)kWavesPerTile) {
             uint4 rec, rq;
-            const bool act = event_record(d, ps, (int)blockIdx.x, nev, kc, rec, rq);
-            event_chunk(d, s_pref, ps, act, rec, rq);
+            bool act;
+            if (kc * 64u + 64u <= kEvLds) {
+                const uint32_t e = kc * 64u + (uint32_t)lane;
+                act = e < nev;
+                if (act) {
+                    rec = s_rec[e];
+                    rq = s_rq[e];
+                }
+            } else {
+                act = event_record(d, ps, (int)blockIdx.x, nev, kc, rec, rq);
+            }
+            event_chunk(d, s_pref, ps, act, rec, rq, sg, seg_first, base_p, stride);
         }
     }
 }
@@ -1232,7 +1252,7 @@ namespace {
 // bound, `born` whether an ionization filled the velocities of `bb` (the
 // ejected electron and the new ion; the caller places them at the parent's
 // position).
-__device__ __forceinline__ int collide_particle(const SegConst& sc, const DisConst& dc, int s, uint32_t step,
+__device__ __forceinline__ int collide_particle(CSeg& sc, CDis& dc, int s, uint32_t step,
                                                 double& ux, double& uy, double& uz, uint32_t pid, Birth& bb,
                                                 bool& viol, bool& born)
 {
@@ -1257,10 +1277,12 @@ __device__ __forceinline__ int collide_particle(const SegConst& sc, const DisCon
         eps = sc.half_m_over_e_d * g2s;
     }
     // channel: the first k whose running sum of n_g sigma_k g / nu_max passes
-    // u1, one pass over the table row (the full sum checks the bound)
+    // u1, one pass over the table row (the full sum checks the bound).  The
+    // row's entries are read four at a time, all in flight together, and the
+    // channel's kind and threshold are kept from the pass: no chain of reads.
     const double u1 = u01d(r.y);
-    double cum = 0.0;
-    int ch = -1;
+    double cum = 0.0, th = 0.0;
+    int ch = -1, kind = 0;
     {
         const double lx = (log(fmax(eps, 1e-300)) - sc.xs_ln0) * sc.xs_inv_dln;
         int i;
@@ -1276,12 +1298,33 @@ __device__ __forceinline__ int collide_particle(const SegConst& sc, const DisCon
             if (i > sc.xs_n - 2) i = sc.xs_n - 2;
             fr = lx - (double)i;
         }
-        const double* r0 = sc.xs + (size_t)i * sc.nch;
-        const double* r1 = r0 + sc.nch;
-        for (int k = 0; k < sc.nch; ++k) {
-            const double v = r0[k] + fr * (r1[k] - r0[k]);
-            cum += ((eps < sc.th[k]) ? 0.0 : v) * speed;
-            if (ch < 0 && u1 < cum) ch = k;
+        const PIC_GLOBAL double* r0 = (const PIC_GLOBAL double*)sc.xs + (size_t)i * sc.nch;
+        const PIC_GLOBAL double* r1 = r0 + sc.nch;
+        const int nch = sc.nch;
+        constexpr int kGroup = 4;
+        static_assert(kMaxChan % kGroup == 0, "thresholds are read in whole groups");
+        for (int k0 = 0; k0 < nch; k0 += kGroup) {
+            double a0[kGroup], a1[kGroup], tk[kGroup];
+            int kd[kGroup];
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) {
+                const int k = k0 + q < nch ? k0 + q : nch - 1;
+                a0[q] = r0[k];
+                a1[q] = r1[k];
+                tk[q] = sc.th[k0 + q];
+                kd[q] = sc.kind[k0 + q];
+            }
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) {
+                if (k0 + q >= nch) break;                 // uniform
+                const double v = a0[q] + fr * (a1[q] - a0[q]);
+                cum += ((eps < tk[q]) ? 0.0 : v) * speed;
+                if (ch < 0 && u1 < cum) {
+                    ch = k0 + q;
+                    kind = kd[q];
+                    th = tk[q];
+                }
+            }
         }
     }
     viol = cum > 1.0;
@@ -1289,7 +1332,6 @@ __device__ __forceinline__ int collide_particle(const SegConst& sc, const DisCon
     if (ch < 0) return -1;
     const double cos_chi = 1.0 - 2.0 * u01d(r.z);
     const double u_phi = u01d(r.w);           // azimuth 2 pi u_phi
-    const int kind = sc.kind[ch];
     if (!sc.ion_type) {
         const double inv = 1.0 / speed;
         const double dx_ = ux * inv, dy_ = uy * inv, dz_ = uz * inv;
@@ -1299,11 +1341,11 @@ __device__ __forceinline__ int collide_particle(const SegConst& sc, const DisCon
         if (kind == PIC_XS_ELASTIC) {
             enew = eps * (1.0 - sc.mr2 * (1.0 - cos_chi));
         } else if (kind == PIC_XS_EXCITATION) {
-            enew = eps - sc.th[ch];
+            enew = eps - th;
         } else {
             const uint4 r1 = philox10(pid, step, ((uint32_t)s << 24) | 1u, 0u, dc.key0, dc.key1);
             const uint4 r2 = philox10(pid, step, ((uint32_t)s << 24) | 2u, 0u, dc.key0, dc.key1);
-            const double avail = eps - sc.th[ch];
+            const double avail = eps - th;
             const double eej = u01d(r1.x) * avail;
             enew = avail - eej;
             double edx, edy, edz;
@@ -1349,7 +1391,7 @@ __device__ __forceinline__ int collide_particle(const SegConst& sc, const DisCon
 // flux-weighted half-Maxwellian, tangential components Maxwellian, placed
 // u v_n dt into the gap.  Returns 1 with `bb` filled when one is placed,
 // -1 when one is emitted but lands beyond the gap, 0 when none is emitted.
-__device__ __forceinline__ int secondary(const SegConst& sc, const DisConst& dc, int s, uint32_t step, int wall,
+__device__ __forceinline__ int secondary(CSeg& sc, CDis& dc, int s, uint32_t step, int wall,
                                          uint32_t pid, Birth& bb)
 {
     const uint4 r4 = philox10(pid, step, ((uint32_t)s << 24) | 4u, 0u, dc.key0, dc.key1);
@@ -1402,9 +1444,12 @@ __device__ __forceinline__ bool event_record(const DevPtrs& d, const EvPass& ps,
 
 // The events pass on one chunk: lanes with `act` hold an event's records.  One
 // segment at a time (a chunk spans more than one only at a segment's end), so
-// its constants are read once for the wave, all in one round.
+// its constants are read once for the wave, all in one round.  k_sg: a segment
+// the caller knows the place of (first tile, particle arrays and their
+// distance), or -1.
 __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, const EvPass& ps, bool act,
-                                            uint4 rec, uint4 rq)
+                                            uint4 rec, uint4 rq, int k_sg, int32_t k_first, char* k_base,
+                                            int64_t k_stride)
 {
     const int S = d.S;
     const int lane = threadIdx.x & 63;
@@ -1416,23 +1461,28 @@ __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_p
         const bool mine = act && (int)(word >> kEvSegShift) == sg;
         todo &= ~__ballot(mine);
         const int b = seg_discharge(sg, S), s = sg - b * S;
-        const DisConst& dc = d.disc[b];
-        const SegConst& sc = d.segc[sg];
+        CDis& dc = const_dis(d, b);
+        CSeg& sc = const_seg(d, sg);
         const int nc = dc.n_cells;
         const int periodic = dc.bc == PIC_BC_PERIODIC;
-        const uint32_t step = (uint32_t)d.diss[b].step;
-        const SegState& st = d.segs[sg];
-        const int64_t stride = st.stride;
-        char* base = st.base + (int64_t)st.parity * kFields * stride;
+        const uint32_t step = const_step(d, b);
+        int64_t stride = k_stride;
+        char* base = k_base;
+        int32_t first = k_first;
+        if (sg != k_sg) {
+            const PIC_CONST SegState& st = const_state(d, sg);
+            stride = st.stride;
+            base = st.base + (int64_t)st.parity * kFields * stride;
+            first = s_pref[sg];
+        }
         const int nch = sc.nch;
-        const int32_t first = s_pref[sg];
         bool hb = false, see = false, cand = false, viol = false, lost = false;
         int wall = 0, ch = -1;
         if (mine) {
             const int32_t t = (int32_t)rq.w;
             const uint32_t key = word & kEvSlot;
-            char* at = base + ((int64_t)(t - first) * ps.T + key) * 4;     // the particle's slot
-            const uint32_t pid = nch > 0 ? rec.y : *reinterpret_cast<const uint32_t*>(at + 5 * stride);
+            PIC_GLOBAL char* at = (PIC_GLOBAL char*)base + ((int64_t)(t - first) * ps.T + key) * 4;   // the particle's slot
+            const uint32_t pid = nch > 0 ? rec.y : *(const PIC_GLOBAL uint32_t*)(at + 5 * stride);
             Birth bb;
             if (word & kEvSee) {
                 see = true;
@@ -1442,8 +1492,8 @@ __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_p
                 lost = r < 0;
             } else {
                 double ux = __uint_as_float(rec.z);
-                double uy = (ps.vm & kUseY) ? __uint_as_float(rec.w) : *reinterpret_cast<const float*>(at + 3 * stride);
-                double uz = (ps.vm & kUseZ) ? __uint_as_float(rq.x) : *reinterpret_cast<const float*>(at + 4 * stride);
+                double uy = (ps.vm & kUseY) ? __uint_as_float(rec.w) : *(const PIC_GLOBAL float*)(at + 3 * stride);
+                double uz = (ps.vm & kUseZ) ? __uint_as_float(rq.x) : *(const PIC_GLOBAL float*)(at + 4 * stride);
                 if (word & kEvRenew) {
                     const uint4 r6 = philox10(pid, step, ((uint32_t)s << 24) | 6u, 0u, dc.key0, dc.key1);
                     double g0, g1, g2, g3;
@@ -1467,9 +1517,9 @@ __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_p
                 }
                 const float fx = (float)ux, fy = (float)uy, fz = (float)uz;
                 if (ch >= 0 || (word & kEvRenew)) {          // a null collision changes nothing
-                    *reinterpret_cast<float*>(at + 2 * stride) = fx;
-                    *reinterpret_cast<float*>(at + 3 * stride) = fy;
-                    *reinterpret_cast<float*>(at + 4 * stride) = fz;
+                    *(PIC_GLOBAL float*)(at + 2 * stride) = fx;
+                    *(PIC_GLOBAL float*)(at + 3 * stride) = fy;
+                    *(PIC_GLOBAL float*)(at + 4 * stride) = fz;
                     if (ps.diag)                             // the push sampled the velocity of the record
                         sample_change(d, sc, dc, b, sg, s == 0, ps.eepf_inv_bin, c, f, __uint_as_float(rec.z),
                                       __uint_as_float(rec.w), __uint_as_float(rq.x), fx, fy, fz);
@@ -1488,10 +1538,10 @@ __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_p
                     if (ps.diag) {
                         // the births' velocity moments and the electron's
                         // energy, with the particles of the step
-                        sample_particle(d, d.segc[b * S + 0], dc, b, b * S + 0, true, ps.eepf_inv_bin, bb.cell, bb.off,
+                        sample_particle(d, const_seg(d, b * S + 0), dc, b, b * S + 0, true, ps.eepf_inv_bin, bb.cell, bb.off,
                                         bb.vx, bb.vy, bb.vz);
                         if (!see && S > 1)
-                            sample_particle(d, d.segc[b * S + 1], dc, b, b * S + 1, false, ps.eepf_inv_bin, bb.cell,
+                            sample_particle(d, const_seg(d, b * S + 1), dc, b, b * S + 1, false, ps.eepf_inv_bin, bb.cell,
                                             bb.off, bb.ivx, bb.ivy, bb.ivz);
                     }
                     atomicAdd(reinterpret_cast<unsigned long long*>(&d.segs[sg].staged), 1ull);
