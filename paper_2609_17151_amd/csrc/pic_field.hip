@@ -36,6 +36,9 @@ constexpr int kWaves = kFT / 64;
 // node, a wave-level scan and one scan over the waves' totals give K[i] and
 // G[i] at every node, and phi follows directly; the totals also give the
 // mean of phi.
+// DIAG: a sampled step (mode kFinStep); an instance of its own because the sums
+// it reads early take registers that the others' chain does better without.
+template <bool DIAG>
 __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
 {
     const DevPtrs& d = a.d;
@@ -56,6 +59,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     __shared__ double s_w[kWaves];
     __shared__ double s_src[2];               // the source's voltage and charge at the solve's time
     __shared__ Run s_run[kWaves];
+    __shared__ double s_kp[2][2][DIAG ? kFT : 1];        // m Gamma^2 / n and p at the nodes, two species in turn
 
     // ---- births, appended after the last slot in the order of their tiles --
     // (and, inside a tile, of their parents): ionization electrons, then the
@@ -72,7 +76,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     __shared__ uint32_t s_tinc[kFT];         // inclusive prefix of the threads' runs' birth counts
     // the bookkeeping of a step, by one wave: counts, ids, kinetic energy
     auto bookkeeping = [&](bool births) {
-        if (a.diag) {
+        if (DIAG) {
             // kinetic-energy partials of the step's runs (zeros elsewhere),
             // fixed order, cleared after reading
             for (int s = 0; s < S; ++s) {
@@ -221,6 +225,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     }
     // ---- densities and charge (into s_a) ------------------------------------
     double rsum = 0.0;
+    double n_dens[kMaxSpecies];                          // of the thread's (last) node
     if (node_wave) {
         for (int i = tid; i < nn; i += kFT) {
             double r;
@@ -229,7 +234,9 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
             } else {
                 r = dc.rho_bg;
                 const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
-                for (int s = 0; s < S; ++s) {
+#pragma unroll
+                for (int s = 0; s < kMaxSpecies; ++s) {
+                    if (s >= S) break;
                     unsigned long long* acc = a.acc + ((size_t)b * S + s) * kRep * d.nodes_max;
                     unsigned long long sum = 0ull;
 #pragma unroll
@@ -241,6 +248,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
                     }
                     const double den = (double)sum * (dc.dens_coef[s] * wall);
                     d.dens[((size_t)b * S + s) * d.nodes_max + i] = den;
+                    n_dens[s] = den;
                     r += dc.q[s] * den;
                 }
                 d.rho[nb + i] = r;
@@ -378,6 +386,40 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     // counts and ids while the other waves form the field
     if (wid == kWaves - 1 && a.mode == kFinStep && !split) bookkeeping(false);
 
+    // A sampled step on a mesh of up to one node per thread: the sums that the
+    // time averages need are read here, all in one round that the field stage
+    // covers; one species' chain of reads after the other, and gradients through
+    // memory, made up 5.7 of a sampled finalize's 10 us on 400 cells.  Per step,
+    // one sampled discharge of 4e5 particles: 33.3 us before, 31.4 now.
+    const bool one = nn <= kFT;                          // uniform
+    const bool avg_one = DIAG && one;
+    const bool mine = tid < nn;
+    constexpr int kPair = 2;                             // species read together
+    unsigned long long m_f[kPair], m_m[kPair], m_e = 0ull;
+    double m_g[kPair], m_p[kPair][kPow], m_a[kMaxSpecies + 2];
+    auto read_sums = [&](int s0) {
+#pragma unroll
+        for (int q = 0; q < kPair; ++q)
+            if (s0 + q < S) {
+                const size_t sb = (size_t)b * S + s0 + q;
+                const unsigned long long* ma = d.macc + sb * 2 * d.nodes_max;
+                const double* pv = d.pavg + sb * kPow * d.nodes_max;
+                m_f[q] = ma[tid];
+                m_m[q] = ma[d.nodes_max + tid];
+                m_g[q] = d.gprev[sb * d.nodes_max + tid];
+#pragma unroll
+                for (int w = 0; w < kPow; ++w) m_p[q][w] = pv[(size_t)w * d.nodes_max + tid];
+            }
+    };
+    if (avg_one && mine) {
+        const double* av = d.avg + (size_t)b * (S + 2) * d.nodes_max;
+        m_e = d.eacc[nb + tid];
+#pragma unroll
+        for (int s = 0; s < kMaxSpecies + 2; ++s)
+            if (s < S + 2) m_a[s] = av[(size_t)s * d.nodes_max + tid];
+        read_sums(0);
+    }
+
     // ---- field at the nodes, and the cells' pairs for the gather ---------------
     auto efield = [&](int i) -> double {
         if (!dc.field_solve) return 0.0;
@@ -415,59 +457,25 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
     if (a.mode == kFinExternal) return;
 
     // ---- time averages -------------------------------------------------------
-    if (a.mode == kFinStep && a.diag) {
-        __syncthreads();                                 // the densities are read back
+    // flux, momentum flux and the power the new field gives each species,
+    // and the power decomposition of the electron (and ion) momentum
+    // balance, m dGamma/dt + d(m n <vx^2>)/dx = q n E + R, multiplied by
+    // u = Gamma / n: inertia u (m dGamma/dt + d(m Gamma^2 / n)/dx),
+    // pressure u dp/dx with p = m (n <vx^2> - Gamma^2 / n), and the ohmic
+    // part q Gamma E - inertia - pressure (formed by the reader).  The time
+    // derivative uses the flux of the previous step when that step was
+    // sampled; gradients are central inside, one-sided at a wall node.
+    if (DIAG) {
         double* av = d.avg + (size_t)b * (S + 2) * d.nodes_max;
         unsigned long long* ea = d.eacc + nb;
         const double ecoef = dc.dens_coef[0] * kDepScale / 1048576.0;   // w / dx / 2^20
-        for (int i = tid; i < nn; i += kFT) {
-            for (int s = 0; s < S; ++s)
-                av[(size_t)s * d.nodes_max + i] += d.dens[((size_t)b * S + s) * d.nodes_max + i];
-            av[(size_t)S * d.nodes_max + i] += s_a[i];
-            const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
-            av[(size_t)(S + 1) * d.nodes_max + i] += (double)ea[i] * ecoef * wall;   // n_e <eps>
-            ea[i] = 0ull;
-        }
-        // flux, momentum flux and the power the new field gives each species,
-        // and the power decomposition of the electron (and ion) momentum
-        // balance, m dGamma/dt + d(m n <vx^2>)/dx = q n E + R, multiplied by
-        // u = Gamma / n: inertia u (m dGamma/dt + d(m Gamma^2 / n)/dx),
-        // pressure u dp/dx with p = m (n <vx^2> - Gamma^2 / n), and the ohmic
-        // part q Gamma E - inertia - pressure (formed by the reader).  The time
-        // derivative uses the flux of the previous step when that step was
-        // sampled; gradients are central inside, one-sided at a wall node.
         const bool prev = ds.pw_next == ds.step;
-        double* kt = d.ptmp + (size_t)b * 2 * d.nodes_max;    // m Gamma^2 / n and p at the nodes
-        double* pt = kt + d.nodes_max;
-        for (int s = 0; s < S; ++s) {
-            unsigned long long* ma = d.macc + ((size_t)b * S + s) * 2 * d.nodes_max;
-            double* pv = d.pavg + ((size_t)b * S + s) * kPow * d.nodes_max;
-            const double* dn = d.dens + ((size_t)b * S + s) * d.nodes_max;
-            double* gp = d.gprev + ((size_t)b * S + s) * d.nodes_max;
-            const double m = dc.mass[s];
-            __syncthreads();                             // the previous species' gradients are read
-            for (int i = tid; i < nn; i += kFT) {
-                const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
-                const double G = (double)(long long)ma[i] * dc.flux_coef[s] * wall;
-                const double M = (double)(long long)ma[d.nodes_max + i] * dc.mom_coef[s] * wall;
-                const double nd = dn[i];
-                const double K = nd > 0.0 ? m * G * G / nd : 0.0;
-                kt[i] = K;
-                pt[i] = m * M - K;
-            }
-            __threadfence_block();
-            __syncthreads();
-            for (int i = tid; i < nn; i += kFT) {
-                const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
-                const double G = (double)(long long)ma[i] * dc.flux_coef[s] * wall;
-                const double M = (double)(long long)ma[d.nodes_max + i] * dc.mom_coef[s] * wall;
-                ma[i] = 0ull;
-                ma[d.nodes_max + i] = 0ull;
-                const double e = efield(i) + dc.e_ext[0];   // the mesh field and the imposed one
-                const double nd = dn[i];
-                const double u = nd > 0.0 ? G / nd : 0.0;
-                int il, ir;
-                double h;
+        if (one) {
+            const int i = tid;
+            const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
+            int il = i, ir = i;
+            double h = 1.0, e = 0.0;
+            if (mine) {
                 if (periodic) {
                     il = i == 0 ? nn - 1 : i - 1;
                     ir = i == nn - 1 ? 0 : i + 1;
@@ -477,14 +485,109 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
                     ir = i < nn - 1 ? i + 1 : i;
                     h = (double)(ir - il) * dc.dx;
                 }
-                const double dk = (kt[ir] - kt[il]) / h, dp = (pt[ir] - pt[il]) / h;
-                const double dgdt = prev ? (G - gp[i]) / dc.dt : 0.0;
-                pv[i] += G;
-                pv[(size_t)d.nodes_max + i] += M;
-                pv[2 * (size_t)d.nodes_max + i] += dc.q[s] * G * e;
-                pv[3 * (size_t)d.nodes_max + i] += u * (m * dgdt + dk);
-                pv[4 * (size_t)d.nodes_max + i] += u * dp;
-                gp[i] = G;
+                e = efield(i) + dc.e_ext[0];              // the mesh field and the imposed one
+#pragma unroll
+                for (int s = 0; s < kMaxSpecies; ++s)
+                    if (s < S) av[(size_t)s * d.nodes_max + i] = m_a[s] + n_dens[s];
+#pragma unroll
+                for (int s = 0; s < kMaxSpecies + 2; ++s) {
+                    if (s == S) av[(size_t)s * d.nodes_max + i] = m_a[s] + s_a[i];
+                    if (s == S + 1) av[(size_t)s * d.nodes_max + i] = m_a[s] + (double)m_e * ecoef * wall;   // n_e <eps>
+                }
+                ea[i] = 0ull;
+            }
+#pragma unroll
+            for (int s = 0; s < kMaxSpecies; ++s) {
+                if (s >= S) break;                        // uniform
+                const int q = s % kPair;
+                if (q == 0 && s > 0 && mine) read_sums(s);
+                const double G = (double)(long long)m_f[q] * dc.flux_coef[s] * wall;
+                const double M = (double)(long long)m_m[q] * dc.mom_coef[s] * wall;
+                const double m = dc.mass[s], nd = n_dens[s];
+                const double K = nd > 0.0 ? m * G * G / nd : 0.0;
+                if (mine) {
+                    s_kp[q][0][i] = K;
+                    s_kp[q][1][i] = m * M - K;
+                }
+                lds_barrier();       // (the other pair of arrays is read by then: two take turns)
+                if (mine) {
+                    const size_t sb = (size_t)b * S + s;
+                    unsigned long long* ma = d.macc + sb * 2 * d.nodes_max;
+                    double* pv = d.pavg + sb * kPow * d.nodes_max;
+                    const double u = nd > 0.0 ? G / nd : 0.0;
+                    const double dk = (s_kp[q][0][ir] - s_kp[q][0][il]) / h;
+                    const double dp = (s_kp[q][1][ir] - s_kp[q][1][il]) / h;
+                    const double dgdt = prev ? (G - m_g[q]) / dc.dt : 0.0;
+                    ma[i] = 0ull;
+                    ma[d.nodes_max + i] = 0ull;
+                    pv[i] = m_p[q][0] + G;
+                    pv[(size_t)d.nodes_max + i] = m_p[q][1] + M;
+                    pv[2 * (size_t)d.nodes_max + i] = m_p[q][2] + dc.q[s] * G * e;
+                    pv[3 * (size_t)d.nodes_max + i] = m_p[q][3] + u * (m * dgdt + dk);
+                    pv[4 * (size_t)d.nodes_max + i] = m_p[q][4] + u * dp;
+                    d.gprev[sb * d.nodes_max + i] = G;
+                }
+            }
+        } else {
+            // larger meshes: node by node, the gradients' terms through memory
+            __syncthreads();                             // the densities are read back
+            for (int i = tid; i < nn; i += kFT) {
+                for (int s = 0; s < S; ++s)
+                    av[(size_t)s * d.nodes_max + i] += d.dens[((size_t)b * S + s) * d.nodes_max + i];
+                av[(size_t)S * d.nodes_max + i] += s_a[i];
+                const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
+                av[(size_t)(S + 1) * d.nodes_max + i] += (double)ea[i] * ecoef * wall;   // n_e <eps>
+                ea[i] = 0ull;
+            }
+            double* kt = d.ptmp + (size_t)b * 2 * d.nodes_max;    // m Gamma^2 / n and p at the nodes
+            double* pt = kt + d.nodes_max;
+            for (int s = 0; s < S; ++s) {
+                unsigned long long* ma = d.macc + ((size_t)b * S + s) * 2 * d.nodes_max;
+                double* pv = d.pavg + ((size_t)b * S + s) * kPow * d.nodes_max;
+                const double* dn = d.dens + ((size_t)b * S + s) * d.nodes_max;
+                double* gp = d.gprev + ((size_t)b * S + s) * d.nodes_max;
+                const double m = dc.mass[s];
+                __syncthreads();                             // the previous species' gradients are read
+                for (int i = tid; i < nn; i += kFT) {
+                    const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
+                    const double G = (double)(long long)ma[i] * dc.flux_coef[s] * wall;
+                    const double M = (double)(long long)ma[d.nodes_max + i] * dc.mom_coef[s] * wall;
+                    const double nd = dn[i];
+                    const double K = nd > 0.0 ? m * G * G / nd : 0.0;
+                    kt[i] = K;
+                    pt[i] = m * M - K;
+                }
+                __threadfence_block();
+                __syncthreads();
+                for (int i = tid; i < nn; i += kFT) {
+                    const double wall = (!periodic && (i == 0 || i == nn - 1)) ? 2.0 : 1.0;
+                    const double G = (double)(long long)ma[i] * dc.flux_coef[s] * wall;
+                    const double M = (double)(long long)ma[d.nodes_max + i] * dc.mom_coef[s] * wall;
+                    ma[i] = 0ull;
+                    ma[d.nodes_max + i] = 0ull;
+                    const double e = efield(i) + dc.e_ext[0];   // the mesh field and the imposed one
+                    const double nd = dn[i];
+                    const double u = nd > 0.0 ? G / nd : 0.0;
+                    int il, ir;
+                    double h;
+                    if (periodic) {
+                        il = i == 0 ? nn - 1 : i - 1;
+                        ir = i == nn - 1 ? 0 : i + 1;
+                        h = 2.0 * dc.dx;
+                    } else {
+                        il = i > 0 ? i - 1 : i;
+                        ir = i < nn - 1 ? i + 1 : i;
+                        h = (double)(ir - il) * dc.dx;
+                    }
+                    const double dk = (kt[ir] - kt[il]) / h, dp = (pt[ir] - pt[il]) / h;
+                    const double dgdt = prev ? (G - gp[i]) / dc.dt : 0.0;
+                    pv[i] += G;
+                    pv[(size_t)d.nodes_max + i] += M;
+                    pv[2 * (size_t)d.nodes_max + i] += dc.q[s] * G * e;
+                    pv[3 * (size_t)d.nodes_max + i] += u * (m * dgdt + dk);
+                    pv[4 * (size_t)d.nodes_max + i] += u * dp;
+                    gp[i] = G;
+                }
             }
         }
         // an RF window ends with this step: its sums go to the ring (each
@@ -511,7 +614,7 @@ __global__ __launch_bounds__(kFT) void finalize_kernel(FinArgs a)
             ds.circ_init = 1;
         }
         if (a.mode == kFinStep) {
-            if (a.diag) {
+            if (DIAG) {
                 ds.pw_next = ds.step + 1;                // this step's flux is stored
                 ds.avg_samples += 1.0;
                 ds.eepf_samples += 1.0;
@@ -529,7 +632,8 @@ hipError_t launch_finalize(const FinArgs& a, hipStream_t st)
 {
     const unsigned per = (a.mode == kFinStep && a.births_per_tile > 0) ? 2u : 1u;   // births workgroup
     const unsigned g = (a.only_b >= 0 ? 1u : (unsigned)a.d.B) * per;
-    hipLaunchKernelGGL(finalize_kernel, dim3(g), dim3(kFT), 0, st, a);
+    if (a.mode == kFinStep && a.diag) hipLaunchKernelGGL(finalize_kernel<true>, dim3(g), dim3(kFT), 0, st, a);
+    else hipLaunchKernelGGL(finalize_kernel<false>, dim3(g), dim3(kFT), 0, st, a);
     return hipGetLastError();
 }
 
