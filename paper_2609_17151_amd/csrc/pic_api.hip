@@ -659,7 +659,7 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
         place(d.eepf, (size_t)B * 2 * kEepfBins);
         place(d.wedf, (size_t)B * S * 2 * kEepfBins);
         place(d.bcnt, tiles_max);
-        place(d.evg, kMaxPushGrid);
+        place(d.evg, (size_t)kMaxPushGrid + 1);
         place(d.tick, 1);
         place(d.ke_part, tiles_max);
         char* block = (char*)A(bytes);

@@ -255,7 +255,7 @@ struct DevPtrs {
                                  // of its tile range, in any order: (slot in tile | event bits, id, vx, vy)
                                  // of the particle after the push
     uint4* evq;                  // [slots] the same events' (vz, cell, offset, tile)
-    uint32_t* evg;               // [kMaxPushGrid] events of each push workgroup's range
+    uint32_t* evg;               // [kMaxPushGrid + 1] events of each push workgroup's range; last, its tiles
     unsigned long long* tick;    // steps taken by the context
     uint32_t* ccnt;              // [tiles_max] compaction: live particles of each tile, then their first slot
     double* ke_part;             // [tiles_max] kinetic-energy partial sums by tile

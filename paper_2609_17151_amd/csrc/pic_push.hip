@@ -15,18 +15,19 @@ namespace pic {
 // slot, by which the finalize orders the tile's births; its charge goes
 // straight into the discharge's fixed-point sums.  Counters come from
 // ballots, per segment of the chunk.
+// The segments' first tiles and the push workgroups' ranges come from the push,
+// which left them in memory (forming them again from the segments' counts took
+// 2.7 us of a launch of 54; 64 sampled discharges 262 -> 260 us per step).
 template <int BS>
 __global__ __launch_bounds__(BS) void events_kernel(EvArgs a)
 {
     const DevPtrs& d = a.d;
-    const int NS = d.B * d.S;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     constexpr int kW = BS / 64;
-    __shared__ int32_t s_pref[kMaxSeg + 1];
     __shared__ uint32_t s_cp[kMaxPushGrid + 1];   // chunks of the push workgroups before each
     __shared__ uint32_t s_ne[kMaxPushGrid];       // events of each push workgroup
     __shared__ uint32_t s_w[kW];
-    tile_prefix(d, a.T, s_pref);
+    const int32_t chunk_t = (int32_t)d.evg[kMaxPushGrid];   // the push workgroups' tile ranges
     const int G = a.push_grid;
     uint32_t run = 0;
     for (int r = 0; r < G; r += BS) {
@@ -50,13 +51,11 @@ __global__ __launch_bounds__(BS) void events_kernel(EvArgs a)
     }
     if (tid == 0) s_cp[G] = run;
     __syncthreads();
-    const int32_t NT = s_pref[NS];
-    const int32_t chunk_t = (NT + G - 1) / G;     // the push workgroups' tile ranges
     const uint32_t bpt = (uint32_t)a.births_per_tile;
     const uint32_t nchunk = s_cp[G];
     const uint32_t stride = gridDim.x * kW;
 
-    const EvPass e{a.T, chunk_t, NT, bpt, a.diag, a.eepf_inv_bin, a.vm};
+    const EvPass e{a.T, chunk_t, bpt, a.diag, a.eepf_inv_bin, a.vm};
     // the records of chunk ck, for the lanes that hold one; the push
     // workgroup of chunk ck is the last g with s_cp[g] <= ck
     auto records = [&](uint32_t ck, uint4& rec, uint4& rq) -> bool {
@@ -76,7 +75,7 @@ __global__ __launch_bounds__(BS) void events_kernel(EvArgs a)
         const uint32_t nx = ck + stride;
         uint4 rec_n = make_uint4(0u, 0u, 0u, 0u), rq_n = rec_n;
         const bool act_n = nx < nchunk && records(nx, rec_n, rq_n);
-        event_chunk(d, s_pref, e, act, rec, rq, -1, 0, nullptr, 0);
+        event_chunk(d, nullptr, e, act, rec, rq, -1, 0, nullptr, 0);
         rec = rec_n;
         rq = rq_n;
         act = act_n;

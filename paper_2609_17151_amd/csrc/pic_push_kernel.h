@@ -546,7 +546,7 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m)
 // the chunk, then the work on them.
 struct EvPass {
     int32_t T;                    // particles of the push's tile
-    int32_t chunk_t, NT;          // tiles per push workgroup, tiles in all
+    int32_t chunk_t;              // tiles per push workgroup
     uint32_t bpt;                 // births staged per tile at most
     int32_t diag;
     float eepf_inv_bin;
@@ -766,6 +766,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
     PushC k{};
     // a fixed contiguous range of tiles per workgroup
     const int32_t chunk = (NT + (int32_t)gridDim.x - 1) / (int32_t)gridDim.x;
+    if (GENERAL && !FUSE && blockIdx.x == 0 && tid == 0) d.evg[kMaxPushGrid] = (uint32_t)chunk;
     const int32_t t_begin = (int32_t)blockIdx.x * chunk;
     const int32_t t_end = t_begin + chunk < NT ? t_begin + chunk : NT;
     if (t_begin >= t_end) {
@@ -1222,7 +1223,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
         // this workgroup's own events, in chunks of 64 over its waves:
         // the same pass as the events kernel's, on the records and the
         // tiles this workgroup has just written
-        const EvPass ps{T, chunk, NT, (uint32_t)births_per_tile(T), DIAG, a.eepf_inv_bin,
+        const EvPass ps{T, chunk, (uint32_t)births_per_tile(T), DIAG, a.eepf_inv_bin,
                         (RY ? kUseY : 0) | (RZ ? kUseZ : 0)};
         for (uint32_t kc = (uint32_t)wid; kc < nch; kc += (uint32_t)kWavesPerTile) {
             uint4 rec, rq;
@@ -1446,7 +1447,8 @@ __device__ __forceinline__ bool event_record(const DevPtrs& d, const EvPass& ps,
 // segment at a time (a chunk spans more than one only at a segment's end), so
 // its constants are read once for the wave, all in one round.  k_sg: a segment
 // the caller knows the place of (first tile, particle arrays and their
-// distance), or -1.
+// distance), or -1.  s_pref: the segments' first tiles, or null after the push
+// has ended, which leaves them in the segments' states.
 __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_pref, const EvPass& ps, bool act,
                                             uint4 rec, uint4 rq, int k_sg, int32_t k_first, char* k_base,
                                             int64_t k_stride)
@@ -1473,7 +1475,7 @@ __device__ __forceinline__ void event_chunk(const DevPtrs& d, const int32_t* s_p
             const PIC_CONST SegState& st = const_state(d, sg);
             stride = st.stride;
             base = st.base + (int64_t)st.parity * kFields * stride;
-            first = s_pref[sg];
+            first = s_pref ? s_pref[sg] : (int32_t)st.tile_first;
         }
         const int nch = sc.nch;
         bool hb = false, see = false, cand = false, viol = false, lost = false;
