@@ -884,9 +884,10 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
         // Measured, us per step, 4 x 1024 with the events kernel / 4 x 256
         // with its own events: one argon discharge of 2e4 particles 26.6 /
         // 16.5, 4e5 28.4 / 21.8 (sampled 44.7 / 35.1), 1.5e6 37.7 / 33.5, 4e6
-        // 56.1 / 55.7; 16 of 3.2e6 in all 58.6 / 53.0, 64 of 4e6 70.0 / 62.6, 64
-        // of 1.77e7 184 / 201 (sampled 309 / 302).
-        constexpr int64_t kFuseParticles = 8000000;
+        // 56.1 / 55.7; 16 of 3.2e6 in all 58.6 / 53.0, 64 of 4e6 70.0 / 62.6; a
+        // renewing box of 8e6 82.6 / 84.0, 64 discharges of 1.77e7 184 / 201
+        // (sampled 309 / 302).
+        constexpr int64_t kFuseParticles = 6000000;
         int64_t n = 0;
         for (int64_t v : ctx->known) n += v;
         if (n <= kFuseParticles) {

@@ -28,7 +28,7 @@ def _state(sim):
 
 @pytest.mark.parametrize("n", [700, 60_000, 4_100_000])
 def test_default_schedule_gives_the_same_run(pic, n):
-    # 4.1e6 per species is past the rule's 8e6 particles
+    # 4.1e6 per species is past the rule's 6e6 particles
     cfg, tabs = small_argon(n_init=n, weight=6e13 / n)
     for sp in cfg["species"]:
         sp["capacity"] = n + n // 8 + 4096
