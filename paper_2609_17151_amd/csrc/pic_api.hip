@@ -845,6 +845,7 @@ struct StepPlan {
     PushArgs pa{};
     int ppt = 4, threads = 256;
     bool general = false;
+    bool holes = false;                  // particles can be absorbed
     bool fuse = false;                   // the push does the events (no events launch)
     int vm = kUseY | kUseZ;              // transverse velocity components the push carries
     bool solve = false;                  // streaming steps after the first of a run solve for their field themselves
@@ -874,6 +875,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     for (int g = 0; g < B * S; ++g) {
         const SegConst& sc = ctx->segc[g];
         p.vm |= sc.vuse;
+        p.holes = p.holes || sc.compacts;
         if (sc.compacts || sc.nch > 0 || sc.emits || sc.renew_lz > 0.0) p.general = true;
     }
     int events_in_push = ctx->events_in_push;
@@ -995,7 +997,9 @@ pic_status enqueue_steps(pic_ctx* ctx, const StepPlan& p, int n, hipStream_t st,
         // the general kernel leaves holes where particles were absorbed
         if (p.general && ++ctx->steps_since_compact >= ctx->compact_every) {
             ctx->steps_since_compact = 0;
-            if (launch_compact(ctx->d, ctx->compact_tiles, ctx->n_cu, st) != hipSuccess) return PIC_EHIP;
+            // nothing is absorbed on periodic meshes: no holes, no passes to
+            // find none (a renewing box of 8e6 particles 84.0 -> 83.7 us per step)
+            if (p.holes && launch_compact(ctx->d, ctx->compact_tiles, ctx->n_cu, st) != hipSuccess) return PIC_EHIP;
         }
         if (prof && ctx->ev_used + 8 > 4096) prof_collect(ctx);
     }

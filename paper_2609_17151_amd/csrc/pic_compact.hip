@@ -3,12 +3,13 @@
 // copy, and the copies swap.  Run every few steps (the push leaves holes where
 // particles were absorbed).
 //
-// Tiles of 1024 slots (256 threads, 4 consecutive slots each), numbered over
+// Tiles of 1024 slots (256 threads, 4 slots each), numbered over
 // the segments that have holes.  Four plain passes, no waiting between
 // workgroups (the two tile passes run on persistent grids):
 //   count:   live particles of every tile
 //   scan:    per segment, exclusive scan of its tiles' counts (first slot of
-//            every tile), checked against the segment's live count
+//            every tile), checked against the segment's live count (contexts
+//            of few tiles: part of the scatter)
 //   scatter: every live particle written to its tile's first slot + its rank
 //            in the tile (four rounds of 256 neighbouring slots)
 //   finish:  copies swap, count = live
@@ -72,7 +73,7 @@ __device__ __forceinline__ int seg_of_tile(const int32_t* pref, int NS, int32_t 
 }
 
 // live flags of this thread's slots
-__device__ __forceinline__ uint32_t live_mask(const int32_t* cell, int64_t base, int64_t n)
+__device__ __forceinline__ uint32_t live_mask(const PIC_GLOBAL int32_t* cell, int64_t base, int64_t n)
 {
     uint32_t m = 0;
 #pragma unroll
@@ -105,11 +106,11 @@ __global__ __launch_bounds__(kCT) void compact_count_kernel(DevPtrs d)
     hole_prefix(d, pref);
     const int NS = d.B * d.S;
     for (int32_t t = (int32_t)blockIdx.x; t < pref[NS]; t += (int32_t)gridDim.x) {
-        const int g = seg_of_tile(pref, NS, t);
-        const SegConst& sc = d.segc[g];
-        const SegState& st = d.segs[g];
+        const int g = __builtin_amdgcn_readfirstlane(seg_of_tile(pref, NS, t));
+        const PIC_CONST SegState& st = const_state(d, g);
         const int64_t base = (int64_t)(t - pref[g]) * kCTile + (int64_t)threadIdx.x * kCP;
-        const uint32_t m = live_mask(sc.cell[st.parity], base, st.count);
+        const uint32_t m =
+            live_mask((const PIC_GLOBAL int32_t*)const_seg(d, g).cell[st.parity], base, st.count);
         uint32_t tot;
         (void)block_excl((uint32_t)__popc(m), s_w, &tot);
         if (threadIdx.x == 0) d.ccnt[t] = tot;
@@ -145,41 +146,99 @@ __global__ __launch_bounds__(1024) void compact_scan_kernel(DevPtrs d)
     if (threadIdx.x == 0 && (int64_t)run != d.segs[g].live) atomicOr(&d.diss[g / d.S].flags, kFlagCell);
 }
 
+// A tile's slots, four per thread, are read together, their ranks come from one
+// barrier, and all the live particles' arrays are in flight at once: a small
+// compaction is a chain of these latencies (four rounds of them, one after the
+// other, took 13 us for one discharge of 4e5 particles), a large one wants the
+// bytes in flight.  Per step, compaction every 16 or 32 steps, before and now: 64
+// discharges of 4.9e7 particles 450 and 443 us, of 1.77e7 sampled 262 and 256;
+// one of 4e5 20.5 and 20.3, sampled 31.2 and 30.9.  SCANNED: the scan kernel has turned the counts into first
+// slots; otherwise the workgroup adds up the counts of the tiles before its own.
+template <bool SCANNED>
 __global__ __launch_bounds__(kCT) void compact_scatter_kernel(DevPtrs d)
 {
+    constexpr int kW = kCT / 64;
     __shared__ int32_t pref[kMaxSeg + 1];
-    __shared__ uint32_t s_w[2][kCT / 64];
+    __shared__ uint32_t s_w[kCP][kW], s_p[kW];
     hole_prefix(d, pref);
-    const int NS = d.B * d.S;
+    const int NS = d.B * d.S, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     for (int32_t t = (int32_t)blockIdx.x; t < pref[NS]; t += (int32_t)gridDim.x) {
-        const int g = seg_of_tile(pref, NS, t);
-        const SegConst& sc = d.segc[g];
-        const SegState& st = d.segs[g];
+        const int g = __builtin_amdgcn_readfirstlane(seg_of_tile(pref, NS, t));
+        CSeg& sc = const_seg(d, g);
+        const PIC_CONST SegState& st = const_state(d, g);
         const int in = st.parity, out = in ^ 1;
-        const int64_t base = (int64_t)(t - pref[g]) * kCTile;
+        const int64_t count = st.count, live_n = st.live;
+        const int32_t t0 = pref[g];
+        const int64_t base = (int64_t)(t - t0) * kCTile;
+        const PIC_GLOBAL int32_t* cell = (const PIC_GLOBAL int32_t*)sc.cell[in];
         // rounds of 256 consecutive slots: lanes read and write neighbours
-        int64_t first = d.ccnt[t];
+        int32_t c[kCP];
 #pragma unroll
         for (int r = 0; r < kCP; ++r) {
-            const int64_t i = base + r * kCT + threadIdx.x;
-            const int32_t c = i < st.count ? sc.cell[in][i] : -1;
-            const bool live = c >= 0;
-            uint32_t tot;
-            const int64_t dst = first + block_excl(live ? 1u : 0u, s_w[r & 1], &tot);
-            if (live) {
-                if (dst < st.live) {
-                    sc.cell[out][dst] = c;
-                    sc.off[out][dst] = sc.off[in][i];
-                    sc.vx[out][dst] = sc.vx[in][i];
-                    sc.vy[out][dst] = sc.vy[in][i];
-                    sc.vz[out][dst] = sc.vz[in][i];
-                    sc.id[out][dst] = sc.id[in][i];
-                    if (sc.z[0]) sc.z[out][dst] = sc.z[in][i];
-                } else {                           // cannot happen when the counts agree
-                    atomicOr(&d.diss[g / d.S].flags, kFlagCell);
-                }
+            const int64_t i = base + r * kCT + tid;
+            c[r] = i < count ? cell[i] : -1;
+        }
+        uint32_t before = 0;                       // live particles of the tiles before
+        if (SCANNED) {
+            before = d.ccnt[t];
+        } else {
+            for (int32_t k = t0 + tid; k < t; k += kCT) before += d.ccnt[k];
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) before += (uint32_t)__shfl_xor((int)before, m, 64);
+            if (lane == 0) s_p[wid] = before;
+        }
+        uint64_t m[kCP];
+#pragma unroll
+        for (int r = 0; r < kCP; ++r) {
+            m[r] = __ballot(c[r] >= 0);
+            if (lane == 0) s_w[r][wid] = (uint32_t)__popcll(m[r]);
+        }
+        __syncthreads();
+        int64_t first = before;
+        if (!SCANNED) {
+            first = 0;
+#pragma unroll
+            for (int w = 0; w < kW; ++w) first += s_p[w];
+        }
+        int64_t dst[kCP];
+        bool bad = false;
+#pragma unroll
+        for (int r = 0; r < kCP; ++r) {
+            uint32_t wex = 0, tot = 0;
+#pragma unroll
+            for (int w = 0; w < kW; ++w) {
+                if (w < wid) wex += s_w[r][w];
+                tot += s_w[r][w];
             }
+            dst[r] = first + wex +
+                     __builtin_amdgcn_mbcnt_hi((uint32_t)(m[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0u));
             first += tot;
+            bad |= c[r] >= 0 && dst[r] >= live_n;   // cannot happen when the counts agree
+            if (dst[r] >= live_n) c[r] = -1;
+        }
+        if (!SCANNED) bad |= t + 1 == pref[g + 1] && first != live_n;
+        if (bad) atomicOr(&d.diss[g / d.S].flags, kFlagCell);
+        uint32_t v[5][kCP];
+        const PIC_GLOBAL uint32_t* from[5] = {
+            (const PIC_GLOBAL uint32_t*)sc.off[in], (const PIC_GLOBAL uint32_t*)sc.vx[in],
+            (const PIC_GLOBAL uint32_t*)sc.vy[in], (const PIC_GLOBAL uint32_t*)sc.vz[in],
+            (const PIC_GLOBAL uint32_t*)sc.id[in]};
+        PIC_GLOBAL uint32_t* to[5] = {(PIC_GLOBAL uint32_t*)sc.off[out], (PIC_GLOBAL uint32_t*)sc.vx[out],
+                                      (PIC_GLOBAL uint32_t*)sc.vy[out], (PIC_GLOBAL uint32_t*)sc.vz[out],
+                                      (PIC_GLOBAL uint32_t*)sc.id[out]};
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+#pragma unroll
+            for (int r = 0; r < kCP; ++r) v[k][r] = c[r] >= 0 ? from[k][base + r * kCT + tid] : 0u;
+        PIC_GLOBAL int32_t* cell_to = (PIC_GLOBAL int32_t*)sc.cell[out];
+#pragma unroll
+        for (int r = 0; r < kCP; ++r) {
+            if (c[r] < 0) continue;
+            cell_to[dst[r]] = c[r];
+#pragma unroll
+            for (int k = 0; k < 5; ++k) to[k][dst[r]] = v[k][r];
+            if (sc.z[0])
+                ((PIC_GLOBAL double*)sc.z[out])[dst[r]] = ((const PIC_GLOBAL double*)sc.z[in])[base + r * kCT + tid];
         }
         __syncthreads();                           // s_w is reused
     }
@@ -262,8 +321,16 @@ hipError_t launch_compact(const DevPtrs& d, int64_t max_tiles, int n_cu, hipStre
     // strides over the tiles
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(max_tiles, (int64_t)n_cu * 8));
     hipLaunchKernelGGL(compact_count_kernel, dim3(grid), dim3(kCT), 0, st, d);
-    hipLaunchKernelGGL(compact_scan_kernel, dim3((unsigned)NS), dim3(1024), 0, st, d);
-    hipLaunchKernelGGL(compact_scatter_kernel, dim3(grid), dim3(kCT), 0, st, d);
+    // up to kAddTiles tiles a workgroup adds up the counts before its tile
+    // itself (at most 32 a thread, one round of reads in flight together),
+    // which is less than a launch of the scan (5 us and its gap)
+    constexpr int64_t kAddTiles = 8192;
+    if (max_tiles <= kAddTiles) {
+        hipLaunchKernelGGL(compact_scatter_kernel<false>, dim3(grid), dim3(kCT), 0, st, d);
+    } else {
+        hipLaunchKernelGGL(compact_scan_kernel, dim3((unsigned)NS), dim3(1024), 0, st, d);
+        hipLaunchKernelGGL(compact_scatter_kernel<true>, dim3(grid), dim3(kCT), 0, st, d);
+    }
     hipLaunchKernelGGL(compact_finish_kernel, dim3((unsigned)((NS + 255) / 256)), dim3(256), 0, st, d);
     return hipGetLastError();
 }
