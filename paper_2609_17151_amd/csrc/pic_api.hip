@@ -96,6 +96,7 @@ void* dev_alloc(pic_ctx* c, size_t bytes)
         p = c->alloc.alloc(bytes, c->alloc.user);
     } else if (hipMalloc(&p, bytes) != hipSuccess) {
         p = nullptr;
+        (void)hipGetLastError();                    // else the next launch would report it
     }
     if (p) c->blocks.push_back(p);
     return p;
@@ -108,6 +109,42 @@ void dev_release(pic_ctx* c, void* p)
     if (it != c->blocks.end()) c->blocks.erase(it);
     if (c->has_alloc) c->alloc.free(p, c->alloc.user);
     else (void)hipFree(p);
+}
+
+// whether particles of the segment can be absorbed, collide or be renewed: a
+// step then has events, and births
+bool has_events(const SegConst& sc) { return sc.compacts || sc.nch > 0 || sc.emits || sc.renew_lz > 0.0; }
+
+int64_t context_slots(const pic_ctx* c)
+{
+    int64_t n = 0;
+    for (int64_t v : c->grid_cap) n += v;
+    return n;
+}
+
+bool dense_births(const pic_ctx* c) { return context_slots(c) <= kDenseSlots; }
+
+// The storage of a step's events and births, once: at pic_init where the
+// configuration has them, else with the first collision table (a periodic box
+// without either holds none of these 41 bytes per slot).  PIC_ENOMEM leaves
+// the context as it was.
+pic_status alloc_events(pic_ctx* c)
+{
+    DevPtrs& d = c->d;
+    if (d.births) return PIC_OK;
+    const int64_t slots = context_slots(c);
+    const int64_t staged = slots / kTileMax * births_per_tile(kTileMax, false);      // every tile size's without `dense`
+    void* births = dev_alloc(c, sizeof(Birth) * (size_t)(dense_births(c) ? slots / 4 : staged));
+    void* evr = dev_alloc(c, 16ull * slots);
+    void* evq = dev_alloc(c, 16ull * slots);
+    if (!births || !evr || !evq) {
+        for (void* p : {births, evr, evq}) dev_release(c, p);
+        return PIC_ENOMEM;
+    }
+    d.births = (Birth*)births;
+    d.evr = (uint4*)evr;
+    d.evq = (uint4*)evq;
+    return PIC_OK;
 }
 
 bool valid_species(const pic_species_cfg& s)
@@ -668,11 +705,8 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
             zero_ptr = block + zero_from;
             zero_bytes = bytes - zero_from;
         }
-        int64_t slots = 0;
-        for (int s = 0; s < S; ++s) slots += ctx->grid_cap[s];
-        d.births = (Birth*)A(sizeof(Birth) * (size_t)(slots / kBirthSlots + (int64_t)B * S * births_per_tile(kTileMax)));
-        d.evr = (uint4*)A(16ull * slots);
-        d.evq = (uint4*)A(16ull * slots);
+        for (const SegConst& sc : ctx->segc)
+            if (rc == PIC_OK && has_events(sc)) rc = alloc_events(ctx);
     }
     if (rc == PIC_OK) {
         // the largest readback: the power sums of a discharge, or its wall
@@ -763,6 +797,7 @@ pic_status pic_load_xsec(pic_ctx* ctx, int32_t batch, int32_t species, int32_t k
         if (!h.tabs.empty() && electron_kind(h.tabs[0].kind) != electron_kind(kind)) return PIC_EINVAL;
     }
     pic_status rc = hip_st(hipStreamSynchronize(ctx->stream));
+    if (rc == PIC_OK) rc = alloc_events(ctx);
     for (int b = b0; b < b1 && rc == PIC_OK; ++b) {
         SegHost& h = ctx->segh[b * ctx->S + species];
         Table t;
@@ -876,13 +911,15 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
         const SegConst& sc = ctx->segc[g];
         p.vm |= sc.vuse;
         p.holes = p.holes || sc.compacts;
-        if (sc.compacts || sc.nch > 0 || sc.emits || sc.renew_lz > 0.0) p.general = true;
+        if (has_events(sc)) p.general = true;
     }
     int events_in_push = ctx->events_in_push;
-    if (!ctx->schedule_set && p.general) {
+    const bool dense = dense_births(ctx);
+    if (!ctx->schedule_set && p.general && dense) {
         // Nobody chose a schedule: small tiles whose workgroups do their own
         // events up to kFuseParticles particles, as one launch and the tiles'
-        // number count there; large tiles and the events kernel above.
+        // number count there; large tiles and the events kernel above, and
+        // where small tiles would not stage the births of large ones.
         // Measured, us per step, 4 x 1024 with the events kernel / 4 x 256
         // with its own events: one argon discharge of 2e4 particles 26.6 /
         // 16.5, 4e5 28.4 / 21.8 (sampled 44.7 / 35.1), 1.5e6 37.7 / 33.5, 4e6
@@ -916,6 +953,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     pa.nodes_max_dyn = nn_max;
     pa.cells_max_dyn = nc_max;
     pa.acc = ctx->d.acc;
+    pa.births_per_tile = (uint32_t)births_per_tile(T, dense);
     uint64_t key = 1469598103934665603ull;
     auto mix = [&](uint64_t v) { key = (key ^ v) * 1099511628211ull; };
     mix((uint64_t)ctx->diag);
@@ -936,11 +974,11 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     p.fa.only_b = -1;
     p.fa.steps = 1;
     p.fa.acc = ctx->d.acc;
-    p.fa.births_per_tile = p.general ? births_per_tile(T) : 0;
+    p.fa.births_per_tile = p.general ? births_per_tile(T, dense) : 0;
     p.ea.d = ctx->d;
     p.ea.T = T;
     p.ea.push_grid = (int32_t)p.grid;
-    p.ea.births_per_tile = births_per_tile(T);
+    p.ea.births_per_tile = births_per_tile(T, dense);
     p.ea.diag = ctx->diag;
     p.ea.eepf_inv_bin = pa.eepf_inv_bin;
     p.ea.vm = ctx->diag ? (kUseY | kUseZ) : p.vm;

@@ -23,11 +23,18 @@ constexpr int kWindowRing = PIC_WINDOW_RING;
 constexpr int kMaxSeg = PIC_MAX_BATCH * PIC_MAX_SPECIES;   // (discharge, species) segments of a context
 constexpr int64_t kMaxTiles = 1ll << 30;                    // tile numbers fit in int32
 constexpr int kTileMin = 256;                               // smallest tile of the push (particles)
-// Births a tile of T particles stages per step: a quarter of the particles up
-// to 256, T / 16 in larger tiles.  Tiles of 1024 to 4096 stage the same number,
-// so the default of 1024 takes whatever births a tile of 4096 would.
-__host__ __device__ constexpr int births_per_tile(int T) { return T / 4 < 256 ? T / 4 : (T / 16 > 256 ? T / 16 : 256); }
-constexpr int kBirthSlots = 4;                              // staging: one birth per 4 slots holds every tile size's
+// Births a tile of T particles stages per step.  Contexts of up to kDenseSlots
+// particle slots stage a quarter of the particles up to 256, T / 16 in larger
+// tiles: tiles of 1024 to 4096 stage the same number, so the default of 1024
+// takes whatever births a tile of 4096 would.  That is 9 bytes of staging per
+// slot, 0.6 GB at most.  Larger contexts stage T / 16, 2.25 bytes per slot of
+// 82: with 9 a GPU would hold 8 % fewer particles; the default keeps tiles of
+// 4096 there.
+constexpr int64_t kDenseSlots = 1ll << 26;
+constexpr int births_per_tile(int T, bool dense)
+{
+    return !dense || T / 16 > 256 ? T / 16 : (T / 4 < 256 ? T / 4 : 256);
+}
 constexpr int kMaxPushGrid = 4096;                          // workgroups of a push launch
 constexpr int kPow = 5;                                     // power time sums per species and node
 
@@ -249,7 +256,8 @@ struct DevPtrs {
     unsigned long long* eepf;    // [B][2][bins]
     double* wring;               // [B][kWindowRing][1 + (S+2) nodes_max] completed windows: samples, sums as avg
     unsigned long long* wedf;    // [B][S][2][bins] impact energies at each wall
-    Birth* births;               // [slots / kBirthSlots] births staged by tile, in any order
+    Birth* births;               // [slots / 4 or / 16] births staged by tile, in any order (see births_per_tile); this and
+                                 // the events' records only where the context can have events
     int32_t* bcnt;               // [tiles_max] births staged by each tile
     uint4* evr;                  // [slots] events of the step, packed per push workgroup from the first slot
                                  // of its tile range, in any order: (slot in tile | event bits, id, vx, vy)

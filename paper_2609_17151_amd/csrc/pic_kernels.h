@@ -10,6 +10,7 @@ struct PushArgs {
     DevPtrs d;
     int32_t diag;                 // accumulate electron energy deposit and EEPF
     float eepf_inv_bin;           // 1 / bin width (eV)
+    uint32_t births_per_tile;     // staging slots of a tile
     int32_t nodes_max_dyn, cells_max_dyn;
     unsigned long long* acc;      // deposit sums of this step ([B][S][kRep][nodes_max])
     // a streaming step that solves for its field itself (SOLVE): the sums of
