@@ -436,7 +436,9 @@ pic_status pic_use_graphs(pic_ctx* ctx, int32_t enable);
  * to fill the GPU; this applies to tiles of 256 threads with one to four
  * particles each (other shapes keep the events kernel).  Until this call or
  * pic_config_tiles sets a schedule, the library chooses place and tile shape
- * by the number of particles.  The results are the same
+ * by the number of particles of the running discharges, as the last call that
+ * set or read them left it (pic_init, pic_set_particles, pic_load_profiles;
+ * pic_sync, pic_get_particles, and pic_diag's COUNTS, ENERGY and CHARGE).  The results are the same
  * either way, bit for bit.  PIC_EINVAL for another value.  Synchronous;
  * takes effect at the next pic_step. */
 pic_status pic_config_events(pic_ctx* ctx, int32_t in_push);

@@ -56,7 +56,9 @@ struct pic_ctx {
     int compact_every = 16;              // steps between compactions of the holes
     int events_in_push = 0;              // 256-thread general pushes do their own events
     bool schedule_set = false;           // by pic_config_tiles or pic_config_events; else plan_step's rule
-    std::vector<int64_t> known;          // particles per segment when the host last set them
+    std::vector<int64_t> known;          // particles per segment when the host last set or read them
+    std::vector<uint8_t> retired;        // per discharge
+    int small_tiles = -1;                // what the rule last chose (-1: not yet for the particles the host set)
     int64_t steps_since_compact = 0;
     int64_t compact_tiles = 0;           // grid of the compaction passes
     int diag = 0;
@@ -568,6 +570,7 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
     ctx->segh.assign((size_t)B * S, SegHost{});
     ctx->disc.assign(B, DisConst{});
     ctx->known.assign((size_t)B * S, 0);
+    ctx->retired.assign(B, 0);
     DevPtrs& d = ctx->d;
     d.B = B;
     d.S = S;
@@ -710,10 +713,11 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
     }
     if (rc == PIC_OK) {
         // the largest readback: the power sums of a discharge, or its wall
-        // distributions, with its state and counters
+        // distributions, with its state and counters; or every discharge's
+        // and segment's state
         ctx->host_words = std::max<size_t>({(size_t)S * kPow * nodes_max, (size_t)(S + 2) * nodes_max + 1,
                                             (size_t)3 * nodes_max, (size_t)S * 2 * kEepfBins,
-                                            sizeof(DisState) / 8 * (size_t)B}) +
+                                            (sizeof(DisState) + S * sizeof(SegState)) / 8 * (size_t)B}) +
                           (sizeof(DisState) + S * sizeof(SegState)) / 8 + (size_t)S * kRep * C_N;
         if (hipHostMalloc((void**)&ctx->host, ctx->host_words * 8, hipHostMallocDefault) != hipSuccess) {
             ctx->host = nullptr;
@@ -926,10 +930,18 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
         // 56.1 / 55.7; 16 of 3.2e6 in all 58.6 / 53.0, 64 of 4e6 70.0 / 62.6; a
         // renewing box of 8e6 82.6 / 84.0, 64 discharges of 1.77e7 184 / 201
         // (sampled 309 / 302).
+        // The particles are those of the running discharges, by the counts that
+        // the last call which set or read them left (a step does not bring any
+        // to the host).  A run that falls below the line again takes small
+        // tiles at half of it, so that a swarm thinned at every read does not
+        // capture its graph anew each time.
         constexpr int64_t kFuseParticles = 6000000;
         int64_t n = 0;
-        for (int64_t v : ctx->known) n += v;
-        if (n <= kFuseParticles) {
+        for (int g = 0; g < B * S; ++g)
+            if (!ctx->retired[g / S]) n += ctx->known[g];
+        const int64_t line = ctx->small_tiles == 0 ? kFuseParticles / 2 : kFuseParticles;
+        ctx->small_tiles = n <= line ? 1 : 0;
+        if (ctx->small_tiles) {
             p.ppt = 4;
             p.threads = 256;
             events_in_push = 1;
@@ -1148,7 +1160,9 @@ pic_status pic_retire(pic_ctx* ctx, int32_t batch, int32_t retired)
     if (!ctx || batch < 0 || batch >= ctx->B) return PIC_EINVAL;
     const int32_t v = retired ? 1 : 0;
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return PIC_EHIP;
-    return hip_st(hipMemcpy(&ctx->d.diss[batch].retired, &v, sizeof(v), hipMemcpyHostToDevice));
+    const pic_status rc = hip_st(hipMemcpy(&ctx->d.diss[batch].retired, &v, sizeof(v), hipMemcpyHostToDevice));
+    if (rc == PIC_OK) ctx->retired[batch] = (uint8_t)v;
+    return rc;
 }
 
 pic_status pic_thin(pic_ctx* ctx, int32_t species, int64_t above, int64_t keep)
@@ -1227,8 +1241,10 @@ pic_status pic_sync(pic_ctx* ctx)
     if (!ctx) return PIC_EINVAL;
     Readback rb(ctx);
     const DisState* ds = rb.add(ctx->d.diss, (size_t)ctx->B);
+    const SegState* ss = rb.add(ctx->d.segs, (size_t)ctx->B * ctx->S);
     const pic_status rc = rb.go();
     if (rc != PIC_OK) return rc;
+    for (int g = 0; g < ctx->B * ctx->S; ++g) ctx->known[g] = ss[g].live;
     uint32_t f = 0;
     for (int b = 0; b < ctx->B; ++b) f |= ds[b].flags;
     return flags_status(f);
@@ -1399,6 +1415,7 @@ pic_status pic_get_particles(pic_ctx* ctx, int32_t batch, int32_t species, int64
     const int idx = batch * ctx->S + species;
     SegState ss;
     if (hipMemcpy(&ss, ctx->d.segs + idx, sizeof(SegState), hipMemcpyDeviceToHost) != hipSuccess) return PIC_EHIP;
+    ctx->known[idx] = ss.live;
     if (n_out) *n_out = ss.live;
     if (next_id) *next_id = ss.next_id;
     if (!cell && !off && !vx && !vy && !vz && !id) return PIC_OK;
@@ -1454,6 +1471,7 @@ pic_status pic_set_particles(pic_ctx* ctx, int32_t batch, int32_t species, int64
         if (sc.z[p]) ok = ok && hipMemset(sc.z[p], 0, 2 * nb) == hipSuccess;
     }
     ctx->known[idx] = n;
+    ctx->small_tiles = -1;
     ss.count = n;
     ss.live = n;
     ss.dead = 0;
@@ -1528,6 +1546,7 @@ pic_status pic_load_profiles(pic_ctx* ctx, int32_t batch, int32_t m, const doubl
         if (ok && zc.z[ss[s].parity] && n[s] > 0)
             ok = hipMemsetAsync(zc.z[ss[s].parity], 0, 8ull * n[s], st) == hipSuccess;
         ctx->known[(size_t)batch * S + s] = n[s];
+        ctx->small_tiles = -1;
         ss[s].count = ss[s].live = n[s];
         ss[s].dead = 0;
         ss[s].staged = 0;
@@ -1613,6 +1632,7 @@ pic_status pic_diag(pic_ctx* ctx, int32_t batch, int32_t what, void* out, size_t
     for (int r = 0; r < rows; ++r) got[r] = rb.add((const unsigned long long*)row[r].p, row[r].words);
     const pic_status rc = rb.go();
     if (rc != PIC_OK) return rc;
+    for (int s = 0; states && s < S; ++s) ctx->known[(size_t)batch * S + s] = ss[s].live;
     if (!found || (need && (!out || out_bytes < need))) return PIC_EINVAL;
     DisState ds = *dsp;
     std::vector<unsigned long long> ev(counters ? (size_t)S * C_N : 0, 0ull);   // counters summed over copies
