@@ -590,11 +590,12 @@ hipError_t launch_chain(const pic_mlp* n, ChainArgs& g, int* parts)
     g.ld = k + kPad;
     const int rows = TRAIN ? g.ldb : g.M;          // training fills its rows of 32
     // 16 samples per workgroup until the batch fills 256 compute units, then
-    // more, which share each weight fragment: the weights cross the L2 ports
-    // once per workgroup
-    const int most = TRAIN ? 2 : 4;
-    int mt = 1;
-    while (mt < most && rows > 16 * mt * 256 && chain_lds(2 * mt, k) <= (size_t)kChainLds) mt *= 2;
+    // 32, which share each weight fragment: the weights cross the L2 ports
+    // once per workgroup.  Prediction of 4112 / 16384 samples by
+    // 5-200-200-200-300: 18.9 / 39.4 us with 16, 14.1 / 29.0 with 32; training
+    // there 72.9 / 176 and 61.3 / 155.  Not 64: its instance spilled
+    // registers (16384 samples of 5-200-200-200-768: 51 us, 34 with 32).
+    const int mt = rows > 16 * 256 && chain_lds(2, k) <= (size_t)kChainLds ? 2 : 1;
     g.rows_wg = (rows + 16 * mt - 1) / (16 * mt);
     g.weights = n->weights;
     g.n_weights = (int32_t)(n->weight_bytes / 16);
@@ -603,8 +604,7 @@ hipError_t launch_chain(const pic_mlp* n, ChainArgs& g, int* parts)
     if (TRAIN && g.rows_wg <= kWarmRows) grid = ((grid + kXcd - 1) / kXcd + kWarmers) * kXcd;
     const size_t lds = chain_lds(mt, k);
     if (mt == 1) hipLaunchKernelGGL((chain_kernel<1, TRAIN>), dim3(grid), dim3(kChainThreads), lds, n->stream, g);
-    else if (mt == 2) hipLaunchKernelGGL((chain_kernel<2, TRAIN>), dim3(grid), dim3(kChainThreads), lds, n->stream, g);
-    else hipLaunchKernelGGL((chain_kernel<TRAIN ? 2 : 4, TRAIN>), dim3(grid), dim3(kChainThreads), lds, n->stream, g);
+    else hipLaunchKernelGGL((chain_kernel<2, TRAIN>), dim3(grid), dim3(kChainThreads), lds, n->stream, g);
     if (parts) *parts = g.rows_wg;
     return hipGetLastError();
 }
