@@ -609,6 +609,14 @@ hipError_t launch_chain(const pic_mlp* n, ChainArgs& g, int* parts)
     return hipGetLastError();
 }
 
+// Tiles of 16 x 16 outputs up to which a layer takes a wave for each: many
+// waves for a product that a few workgroups of 64 x 64 would do one after the
+// other; above, each operand fragment has to serve more outputs.  Prediction by
+// 5-1024-1024-1024-768, wave / workgroup tiles: 1024 of them 26.4 / 40.7 us,
+// 2048 32.8 / 42.9, 4096 49.1 / 50.4, 8192 79.2 / 67.3; three layers of 2048:
+// 4096 71.8 / 75.9, 8192 125 / 96.
+constexpr int kSmallTiles = 4096;
+
 // the layers one launch each, for networks too wide for the chain
 hipError_t run_layers(pic_mlp* n, int batch, const float* x, float* y, const float* t, float scale, int ldb, int* parts)
 {
@@ -626,7 +634,7 @@ hipError_t run_layers(pic_mlp* n, int batch, const float* x, float* y, const flo
         a.ldb = ldb;
         a.a = n->rows[cur];
         dim3 grid((unsigned)((cols + 15) / 16), (unsigned)(rows / 16));
-        const bool small = (int64_t)grid.x * grid.y <= 1024;
+        const bool small = (int64_t)grid.x * grid.y <= kSmallTiles;
         if (!small) grid = dim3((unsigned)((cols + 63) / 64), (unsigned)(rows / 64));
         if (a.epi == LAYER_LOSS && parts) *parts = (int)(grid.x * grid.y);
         if (small) hipLaunchKernelGGL((layer_kernel<1, 1, 1>), grid, dim3(64), 0, n->stream, a);
@@ -789,7 +797,7 @@ pic_status pic_mlp_create(const int32_t* widths, int32_t n_widths, int32_t max_b
         n->k_max = std::max(n->k_max, std::max(y.kf, y.kb));
     }
     n->chain = chain_lds(1, n->k_max) <= (size_t)kChainLds;
-    n->max_parts = std::max<int64_t>({1024, pad32(max_batch) / 16,
+    n->max_parts = std::max<int64_t>({kSmallTiles, pad32(max_batch) / 16,
                                       pad64(max_batch) / 64 * ((n->net.l[L - 1].kb + 63) / 64)});
     bool ok = true;
     auto A = [&](size_t bytes) {
