@@ -29,10 +29,10 @@
 // cycle), and the launch of two kernels.  Measured there: 33 us per training
 // step (chain 25, gradients and Adam 9), 313 us with one tiled kernel per
 // product that gathered its operands element by element; prediction of 4096
-// samples 15 us instead of 122.  Networks whose layers do not fit the chain's
-// LDS take one layer_kernel per product (operands straight from the cache);
-// for the others that is slower at every batch above a few rows (training,
-// batch 64: 41 us and five times the host's launches; 4096: 110 against 60).
+// samples 15 us instead of 122.  Networks with more weights, on batches too
+// small for the chain to fill the GPU, and those whose layers do not fit the
+// chain's LDS take one layer_kernel per product (operands straight from the
+// cache); the rule and both sides' figures are at use_chain.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -51,7 +51,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMaxL = PIC_MLP_MAX_LAYERS;
 constexpr int kChainThreads = 1024;
 constexpr int kChainWaves = kChainThreads / 64;
-constexpr int kChainLds = 64 * 1024;       // activations of the chain's rows
+constexpr int kChainLds = 64 * 1024;       // activations of the chain's rows (no more: use_chain)
 constexpr int kPad = 8;                    // LDS row padding: rows land on different banks
 constexpr int kAhead = 12;                 // weight fragments in flight per wave
 
@@ -558,9 +558,10 @@ struct pic_mlp {
     float *w = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
     uint4* weights = nullptr;      // every layer's wf and wt, one block
     size_t weight_bytes = 0;
+    size_t forward_bytes = 0, train_bytes = 0;   // of them read by a prediction, by a training step
     bool chain = true;             // the layers of 16 samples fit the chain's LDS
     int kf_max = 0, k_max = 0;     // longest padded k: forward, training
-    __bf16* rows[2] = {nullptr, nullptr};   // without the chain: rows of the current and the next product
+    __bf16* rows[2] = {nullptr, nullptr};   // where the chain is not taken: rows of the current and the next product
     float* loss_part = nullptr;
     float* loss = nullptr;         // [1]
     int64_t max_parts = 0;
@@ -582,6 +583,36 @@ void* net_alloc(pic_mlp* n, size_t bytes)
 int64_t pad64(int64_t n) { return (n + 63) & ~(int64_t)63; }
 
 size_t chain_lds(int mt, int k) { return (size_t)2 * 16 * mt * (k + kPad) * 2; }
+
+// Whether a call takes the chain.  Its time is that of the weights through one
+// compute unit's L2 port, whatever the batch up to 16 samples per compute unit:
+// 11 us per MB.  A launch per product takes 5 us for each (6 when training) as
+// long as the batch gives it few tiles.  So the chain is left for networks with
+// more than kChainBytes of weights in an average product on batches of up to
+// kLayerRows samples, and to kHeavyRows above kHeavyBytes.  Measured, us, chain /
+// launch per product, hidden layers of h between 5 inputs and 768 outputs,
+// batch 64: prediction h = 256 13.0 / 19.8, 448 (0.41 MB per product) 19.7 /
+// 19.3, 512 23.3 / 20.2, 960 61.8 / 21.2; training 256 33.4 / 42.2, 384 (0.34
+// MB) 48.6 / 45.2, 448 55.6 / 47.8, 512 63.4 / 49.4, 960 145 / 63.7.  By batch:
+// h = 512 (0.5 MB), 256 samples 23.6 / 20.3 and 67.4 / 53.5, 1024 24.2 / 29.0 and
+// 76.3 / 77.3; seven layers of 512, 256 samples 38.3 / 38.3, 512 38.3 / 41.9; h =
+// 640 (0.68 MB), 768 samples 29.6 / 28.4 and 89.7 / 80.0, 1024 29.9 / 33.4.
+// Layers that need more than 64 KiB of the compute unit's 160 would only gain
+// from the chain above 2048 samples (h = 1024, 512 samples: 65 / 44 and 166 /
+// 126; 4096: 72 / 102 and 277 / 337), so they do without.
+constexpr size_t kChainBytes = 420000, kHeavyBytes = 600000;
+constexpr int kLayerRows = 256, kHeavyRows = 768;
+
+// the batches up to which a launch per product is taken
+int layer_rows(const pic_mlp* n, bool train)
+{
+    if (!n->chain) return n->max_batch;
+    const size_t products = train ? 2 * (size_t)n->net.L - 1 : (size_t)n->net.L;
+    const size_t bytes = (train ? n->train_bytes : n->forward_bytes) / products;
+    return bytes > kHeavyBytes ? kHeavyRows : (bytes > kChainBytes ? kLayerRows : 0);
+}
+
+bool use_chain(const pic_mlp* n, int batch, bool train) { return batch > layer_rows(n, train); }
 
 template <bool TRAIN>
 hipError_t launch_chain(const pic_mlp* n, ChainArgs& g, int* parts)
@@ -617,7 +648,7 @@ hipError_t launch_chain(const pic_mlp* n, ChainArgs& g, int* parts)
 // 4096 71.8 / 75.9, 8192 125 / 96.
 constexpr int kSmallTiles = 4096;
 
-// the layers one launch each, for networks too wide for the chain
+// the layers one launch each (see use_chain)
 hipError_t run_layers(pic_mlp* n, int batch, const float* x, float* y, const float* t, float scale, int ldb, int* parts)
 {
     const Net& net = n->net;
@@ -690,7 +721,7 @@ hipError_t run_layers(pic_mlp* n, int batch, const float* x, float* y, const flo
 
 hipError_t run_forward(pic_mlp* n, int batch, const float* x, float* y)
 {
-    if (!n->chain) return run_layers(n, batch, x, y, nullptr, 0.0f, pad32(batch), nullptr);
+    if (!use_chain(n, batch, false)) return run_layers(n, batch, x, y, nullptr, 0.0f, pad32(batch), nullptr);
     ChainArgs g{};
     g.net = n->net;
     g.M = batch;
@@ -713,7 +744,7 @@ hipError_t run_grad(pic_mlp* n, int batch, const float* x, const float* t, float
     const int ldb = pad32(batch);
     int parts = 0;
     hipError_t e;
-    if (n->chain) {
+    if (use_chain(n, batch, true)) {
         ChainArgs c{};
         c.net = n->net;
         c.M = batch;
@@ -812,7 +843,10 @@ pic_status pic_mlp_create(const int32_t* widths, int32_t n_widths, int32_t max_b
     // the BF16 weights in the order of their use: forward, then back
     auto wf_bytes = [&](int l) { return 2ull * pad16(n->net.l[l].no) * n->net.l[l].kf; };
     auto wt_bytes = [&](int l) { return 2ull * pad16(n->net.l[l].ni) * n->net.l[l].kb; };
-    for (int l = 0; l < L; ++l) n->weight_bytes += wf_bytes(l) + wt_bytes(l);
+    for (int l = 0; l < L; ++l) n->forward_bytes += wf_bytes(l);
+    n->train_bytes = n->forward_bytes;
+    for (int l = 1; l < L; ++l) n->train_bytes += wt_bytes(l);
+    n->weight_bytes = n->train_bytes + wt_bytes(0);
     n->weights = (uint4*)A(n->weight_bytes);
     {
         char* q = (char*)n->weights;
@@ -832,7 +866,8 @@ pic_status pic_mlp_create(const int32_t* widths, int32_t n_widths, int32_t max_b
         y.dzt = (__bf16*)A(2ull * pad16(y.no) * ldb);
         if (l < L - 1) y.z = (float*)A(4ull * max_batch * y.no);
     }
-    for (auto& r : n->rows) r = (__bf16*)A(2ull * pad64(max_batch) * n->k_max);
+    if (const int64_t rows = std::min(max_batch, std::max(layer_rows(n, false), layer_rows(n, true))))
+        for (auto& r : n->rows) r = (__bf16*)A(2ull * pad64(rows) * n->k_max);
     n->loss_part = (float*)A(4ull * n->max_parts);
     n->loss = (float*)A(4);
     if (ok) {

@@ -1,5 +1,7 @@
 """Device memory of a context per particle slot, and the storage of the step's
 events in contexts that get their first collision table after a run."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -92,3 +94,23 @@ def test_collisions_from_a_later_step_on(pic):
     # a table that is there from the start gives the candidates of the id draws
     other = pic.Sim(cfg, [one])
     assert other.numax(0) == late.numax(0)
+
+
+def test_a_network_of_the_chain_holds_no_rows_for_other_kernels(pic):
+    # per sample: every layer's input with its ones and output gradient in BF16
+    # (rows of 32 and 16), the hidden layers' pre-activations in FP32
+    widths, batch = (5, 64, 64, 48), 65536
+    pairs = list(zip(widths[:-1], widths[1:]))
+    row = sum(2 * ((a + 32) // 32 * 32 + (b + 15) // 16 * 16) for a, b in pairs) + 4 * sum(widths[1:-1])
+    lib, h, asked = pic.load_library(), C.c_void_p(), []
+
+    def alloc(n, user):
+        asked.append(n)
+        return torch.cuda.caching_allocator_alloc(int(n))
+
+    hooks = pic.ALLOC_FN(alloc), pic.FREE_FN(lambda p, user: torch.cuda.caching_allocator_delete(p))
+    a = pic.PicAllocator(*hooks, None)
+    w = (C.c_int32 * len(widths))(*widths)
+    assert lib.pic_mlp_create(w, len(widths), batch, C.byref(a), None, C.byref(h)) == pic.OK
+    assert sum(asked) <= row * batch + (4 << 20)
+    lib.pic_mlp_free(h)

@@ -24,9 +24,10 @@ def _net(P, widths, batch, seed=5):
 
 
 @pytest.mark.parametrize("widths,batches", [
-    # layers of 1024 outputs, 64 tiles of 16 across: 4096 tiles at 1024 samples
-    ((7, 1024, 1024), (64, 1009, 1024, 1025, 1088)),
-    # the last layer's padded row of 1216, 76 across: 4104 tiles at 864 samples
+    # 66 tiles across the first layer's padded rows, 64 across the outputs: 4096
+    # tiles are passed from 960 to 1009 samples (padded to 1024) and from 1024 to 1025
+    ((7, 1024, 1024), (64, 960, 1009, 1024, 1025, 1088)),
+    # 76 across: 3952 tiles at 832 samples, 4256 at 833 (padded to 896)
     ((3, 1200, 1210), (800, 832, 833)),
 ])
 def test_tiles_of_a_wave_and_of_a_workgroup(P, widths, batches):
@@ -41,4 +42,32 @@ def test_tiles_of_a_wave_and_of_a_workgroup(P, widths, batches):
         assert _rel(y[:m], y_ref) <= 2e-2
         assert loss == pytest.approx(loss_ref, rel=2e-2)
         assert _rel(g.astype(np.float64), g_ref) <= 2e-2
+    net.close()
+
+
+@pytest.mark.parametrize("widths", [(5, 448, 448, 448, 768), (5, 512, 512, 512, 768), (900, 900), (3, 31, 940, 700, 33)])
+@pytest.mark.parametrize("max_batch", [40, 800])
+def test_the_chain_and_a_launch_per_product(P, widths, max_batch):
+    # networks of more than 0.42 MB of weights per product take a launch per
+    # product up to 256 samples (0.6 MB: 768), the chain above.  448 wide:
+    # prediction by the chain, training of few samples by a launch per product;
+    # (900, 900) is past 0.6 MB
+    x, t = W.mlp_batch(max_batch, widths[0], widths[-1], seed=4)
+    net, p = _net(P, widths, max_batch)
+    y = net.forward(x).cpu().numpy()
+    for m in (1, 40, 256, 257, 768, 769):
+        if m > max_batch:
+            continue
+        assert np.array_equal(net.forward(x[:m]).cpu().numpy(), y[:m]), m
+        y_ref, loss_ref, g_ref = _reference(p, widths, x[:m].astype(np.float32), t[:m])
+        loss, g = net.grad(x[:m], t[:m])
+        assert _rel(y[:m], y_ref) <= 2e-2
+        assert loss == pytest.approx(loss_ref, rel=2e-2)
+        assert _rel(g.astype(np.float64), g_ref) <= 2e-2
+        g64, before = g.astype(np.float64), net.params().astype(np.float64)
+        net.set_params(p)                               # clears the moments
+        net.train_step(x[:m], t[:m], lr=1e-3)
+        expect = before - 1e-3 * g64 / (np.abs(g64) + 1e-8)
+        assert np.abs(net.params() - expect).max() <= 1e-6 * 1e-3 + 2e-7 * np.abs(p).max()
+        net.set_params(p)
     net.close()
