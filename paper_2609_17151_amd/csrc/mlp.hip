@@ -425,12 +425,12 @@ __global__ __launch_bounds__(64 * WAVES) void layer_kernel(LayerArgs g)
 __global__ __launch_bounds__(256) void input_kernel(const float* x, int M, int rows, int ni, int kf, __bf16* out,
                                                     __bf16* at, int ldb)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)rows * kf) return;
-    const int m = (int)(i / kf), c = (int)(i - (int64_t)m * kf);
-    const float v = c < ni ? (m < M ? x[(int64_t)m * ni + c] : 0.0f) : (c == ni ? 1.0f : 0.0f);
-    out[frag_at(m, c, kf / 32)] = (__bf16)v;
-    if (at && m < ldb && c <= ni) at[frag_at(c, m, ldb / 32)] = (__bf16)v;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (int64_t)rows * kf; i += (int64_t)gridDim.x * 256) {
+        const int m = (int)(i / kf), c = (int)(i - (int64_t)m * kf);
+        const float v = c < ni ? (m < M ? x[(int64_t)m * ni + c] : 0.0f) : (c == ni ? 1.0f : 0.0f);
+        out[frag_at(m, c, kf / 32)] = (__bf16)v;
+        if (at && m < ldb && c <= ni) at[frag_at(c, m, ldb / 32)] = (__bf16)v;
+    }
 }
 
 struct GradArgs {
@@ -655,7 +655,9 @@ hipError_t run_layers(pic_mlp* n, int batch, const float* x, float* y, const flo
     const int L = net.L;
     const int64_t rows = pad64(batch);
     const Layer& l0 = net.l[0];
-    hipLaunchKernelGGL(input_kernel, dim3((unsigned)((rows * l0.kf + 255) / 256)), dim3(256), 0, n->stream, x, batch,
+    // a launch has fewer than 2^32 threads
+    const int64_t input_wg = std::min<int64_t>((rows * l0.kf + 255) / 256, 1 << 23);
+    hipLaunchKernelGGL(input_kernel, dim3((unsigned)input_wg), dim3(256), 0, n->stream, x, batch,
                        (int)rows, l0.ni, l0.kf, n->rows[0], t ? l0.at : nullptr, ldb);
     hipError_t e = hipGetLastError();
     int cur = 0;

@@ -3,6 +3,7 @@ widths and batch: a sample's outputs do not depend on which kernel formed them,
 and gradients match the products of the same BF16 operands."""
 import numpy as np
 import pytest
+import torch
 
 import workloads as W
 from test_gpu_mlp_shapes import _reference, _rel
@@ -71,3 +72,17 @@ def test_the_chain_and_a_launch_per_product(P, widths, max_batch):
         assert np.abs(net.params() - expect).max() <= 1e-6 * 1e-3 + 2e-7 * np.abs(p).max()
         net.set_params(p)
     net.close()
+
+
+def test_more_input_elements_than_a_launch_has_threads(P):
+    # 2^20 samples (the most a network takes) of 4096 inputs and their ones are
+    # more than 2^32 elements; the last rows give the same bits on their own
+    n, widths = 1 << 20, (4096, 3)
+    net, _ = _net(P, widths, n)
+    x = torch.randn((n, widths[0]), device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    y = net.forward(x)
+    for at in (0, n // 2 - 20, n - 40):
+        assert bool(torch.equal(y[at:at + 40], net.forward(x[at:at + 40]))), at
+    net.close()
+    del x, y
+    torch.cuda.empty_cache()
