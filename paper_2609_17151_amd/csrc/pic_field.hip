@@ -783,7 +783,8 @@ __global__ __launch_bounds__(256) void deposit_kernel(DevPtrs d, int only_b)
         if (k >= st.count) break;
         int c = sc.cell[p][k];
         const float f = sc.off[p][k];
-        if ((unsigned)c >= (unsigned)nc) {
+        if (c < 0) continue;                              // a hole: absorbed, not compacted away yet
+        if (c >= nc) {
             atomicOr(&d.diss[b].flags, kFlagCell);
             continue;
         }
