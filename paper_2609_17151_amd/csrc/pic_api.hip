@@ -450,8 +450,24 @@ void drop_graph(pic_ctx* ctx);
 
 static_assert(sizeof(DisState) % 8 == 0 && sizeof(SegState) % 8 == 0, "read in 8-byte words");
 
+// The context's GPU is the current one while this lives: a kernel on the null
+// stream runs on the current GPU, and could not reach another's memory.
+struct OnDevice {
+    int before = -1;
+    explicit OnDevice(int dev)
+    {
+        int now = dev;
+        if (hipGetDevice(&now) == hipSuccess && now != dev && hipSetDevice(dev) == hipSuccess) before = now;
+    }
+    ~OnDevice()
+    {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
 // A readback in stream order: pieces of device memory to pinned host memory in
-// one kernel, then a wait.  add() says where a piece will be.
+// one kernel, then a wait.  add() says where a piece will be.  As good from a
+// thread whose current GPU is another one as a copy through the runtime is.
 struct Readback {
     pic_ctx* ctx;
     ReadArgs a{};
@@ -467,6 +483,7 @@ struct Readback {
     pic_status go()
     {
         if (a.n > ReadArgs::kMax || a.first[a.n] > ctx->host_words) return PIC_EINVAL;
+        const OnDevice on(ctx->device);
         if (launch_read(a, ctx->stream) != hipSuccess) return PIC_EHIP;
         return hip_st(hipStreamSynchronize(ctx->stream));
     }
@@ -721,6 +738,7 @@ pic_status pic_init(const pic_config* cfg, int32_t n_batch, const pic_allocator*
                           (sizeof(DisState) + S * sizeof(SegState)) / 8 + (size_t)S * kRep * C_N;
         if (hipHostMalloc((void**)&ctx->host, ctx->host_words * 8, hipHostMallocDefault) != hipSuccess) {
             ctx->host = nullptr;
+            (void)hipGetLastError();
             rc = PIC_ENOMEM;
         }
     }

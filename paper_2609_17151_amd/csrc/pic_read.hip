@@ -26,11 +26,14 @@ __global__ __launch_bounds__(kRT) void read_kernel(ReadArgs a)
 
 }  // namespace
 
+// by the launch's own status: an error that some other call of the program has
+// left behind is not this one's
 hipError_t launch_read(const ReadArgs& a, hipStream_t st)
 {
     const unsigned grid = std::max(1u, std::min((a.first[a.n] + kRT - 1) / kRT, 64u));
-    hipLaunchKernelGGL(read_kernel, dim3(grid), dim3(kRT), 0, st, a);
-    return hipGetLastError();
+    ReadArgs copy = a;
+    void* args[] = {&copy};
+    return hipLaunchKernel(reinterpret_cast<const void*>(read_kernel), dim3(grid), dim3(kRT), args, 0, st);
 }
 
 }  // namespace pic
