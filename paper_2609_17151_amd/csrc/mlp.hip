@@ -40,9 +40,15 @@
 #include <cmath>
 #include <vector>
 
+#include "pic_device.h"
 #include "pic_mlp.h"
 
 namespace {
+
+// between layers: what goes to global memory there is read by no other wave of
+// the kernel (the transposed copies), or back by the lane that wrote it (the
+// pre-activations)
+using pic::lds_barrier;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -122,16 +128,6 @@ __device__ __forceinline__ void product(const __bf16* a, int lda, const __bf16* 
         PIC_REST(7) PIC_REST(8) PIC_REST(9) PIC_REST(10) PIC_REST(11) default: break;
     }
 #undef PIC_REST
-}
-
-// a workgroup barrier that orders LDS only: __syncthreads also waits for every
-// store to global memory, here the transposed copies no wave of the kernel
-// reads and the pre-activations each lane reads back itself
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 struct ChainArgs {

@@ -1,5 +1,5 @@
 // Device helpers of the MI355X PIC-MCC library: counter-based random numbers,
-// Box-Muller, scattering rotation, wave/block scans.
+// Box-Muller, scattering rotation, wave/block scans, a barrier of the LDS.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -76,6 +76,15 @@ __device__ __forceinline__ void scatter_dir_d(double dx, double dy, double dz, d
     ox = alt ? nc : na;
     oy = alt ? na : nb;
     oz = alt ? nb : nc;
+}
+
+// a workgroup barrier that orders LDS only: __syncthreads also waits for the
+// wave's outstanding accesses to global memory
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // inclusive scan of one 32-bit value over a 64-wide wave

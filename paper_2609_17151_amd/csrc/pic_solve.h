@@ -4,16 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace pic {
+#include "pic_device.h"
 
-// a workgroup barrier that orders LDS only: __syncthreads also waits for the
-// wave's outstanding accesses to global memory
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
+namespace pic {
 
 // Prefix state of a run of nodes for the nested sums of the solve: n nodes,
 // S = sum of g, P = sum over the run of the running sums of g, Q = sum over
