@@ -1014,7 +1014,6 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     p.ea.vm = ctx->diag ? (kUseY | kUseZ) : p.vm;
     p.ev_grid = std::max<int64_t>(1, std::min(tiles, (int64_t)events_occupancy() * ctx->n_cu));
     mix((uint64_t)p.ev_grid);
-    p.fa.eepf_inv_bin = pa.eepf_inv_bin;
     mix((uint64_t)ctx->sort_every);
     mix((uint64_t)ctx->compact_every);
     p.key = key;

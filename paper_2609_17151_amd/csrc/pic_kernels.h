@@ -43,7 +43,6 @@ struct FinArgs {
     int32_t diag;
     int32_t only_b;               // -1: all discharges (grid = B), else this one (grid = 1)
     int32_t births_per_tile;      // staging slots of a push tile (0: the step cannot have births)
-    float eepf_inv_bin;           // 1 / bin width (eV) of the bulk electron energy distribution
     int32_t steps;                // steps since the last finalize
     unsigned long long* acc;      // deposit sums to solve for (cleared)
     unsigned long long* acc_clear;   // another set to clear, or null
