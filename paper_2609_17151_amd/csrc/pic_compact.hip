@@ -4,14 +4,15 @@
 // particles were absorbed).
 //
 // Tiles of 1024 slots (256 threads, 4 slots each), numbered over
-// the segments that have holes.  Four plain passes, no waiting between
-// workgroups (the two tile passes run on persistent grids):
+// the segments that have holes.  Four plain passes (three in contexts of few
+// tiles), no waiting between workgroups (the two tile passes run on persistent
+// grids):
 //   count:   live particles of every tile
 //   scan:    per segment, exclusive scan of its tiles' counts (first slot of
 //            every tile), checked against the segment's live count (contexts
 //            of few tiles: part of the scatter)
 //   scatter: every live particle written to its tile's first slot + its rank
-//            in the tile (four rounds of 256 neighbouring slots)
+//            in the tile (four groups of 256 neighbouring slots, all in flight)
 //   finish:  copies swap, count = live
 #include "pic_device.h"
 #include "pic_internal.h"
@@ -152,8 +153,8 @@ __global__ __launch_bounds__(1024) void compact_scan_kernel(DevPtrs d)
 // other, took 13 us for one discharge of 4e5 particles), a large one wants the
 // bytes in flight.  Per step, compaction every 16 or 32 steps, before and now: 64
 // discharges of 4.9e7 particles 450 and 443 us, of 1.77e7 sampled 262 and 256;
-// one of 4e5 20.5 and 20.3, sampled 31.2 and 30.9.  SCANNED: the scan kernel has turned the counts into first
-// slots; otherwise the workgroup adds up the counts of the tiles before its own.
+// one of 4e5 20.5 and 20.3, sampled 31.2 and 30.9.  SCANNED: the scan kernel has
+// turned the counts into first slots; otherwise the workgroup adds up the counts of the tiles before its own.
 template <bool SCANNED>
 __global__ __launch_bounds__(kCT) void compact_scatter_kernel(DevPtrs d)
 {
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(kCT) void compact_scatter_kernel(DevPtrs d)
         const int32_t t0 = pref[g];
         const int64_t base = (int64_t)(t - t0) * kCTile;
         const PIC_GLOBAL int32_t* cell = (const PIC_GLOBAL int32_t*)sc.cell[in];
-        // rounds of 256 consecutive slots: lanes read and write neighbours
+        // groups of 256 consecutive slots: lanes read and write neighbours
         int32_t c[kCP];
 #pragma unroll
         for (int r = 0; r < kCP; ++r) {
@@ -321,9 +322,14 @@ hipError_t launch_compact(const DevPtrs& d, int64_t max_tiles, int n_cu, hipStre
     // strides over the tiles
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(max_tiles, (int64_t)n_cu * 8));
     hipLaunchKernelGGL(compact_count_kernel, dim3(grid), dim3(kCT), 0, st, d);
-    // up to kAddTiles tiles a workgroup adds up the counts before its tile
-    // itself (at most 32 a thread, one round of reads in flight together),
-    // which is less than a launch of the scan (5 us and its gap)
+    // up to kAddTiles tiles a workgroup adds up the counts before each of its
+    // tiles itself (at most 32 a thread and tile, one round of reads in flight
+    // together, out of the L2), which is less than a launch of the scan and its
+    // gap.  Measured, us per compaction, adding / scanning, one discharge (two
+    // segments) of 512 tiles 14.6 / 16.8, 2048 27.0 / 29.9, 4096 38.9 / 43.3,
+    // 8192 85 to 89 / 91 to 99; 64 discharges of 2048 tiles in all 18.7 / 24.1,
+    // 8192 49.4 / 52.4.  Adding still wins at 32768 (346 / 366), but its reads
+    // grow with the square of a segment's tiles, so the line lies well inside.
     constexpr int64_t kAddTiles = 8192;
     if (max_tiles <= kAddTiles) {
         hipLaunchKernelGGL(compact_scatter_kernel<false>, dim3(grid), dim3(kCT), 0, st, d);

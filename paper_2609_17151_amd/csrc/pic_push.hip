@@ -3,14 +3,14 @@
 namespace pic {
 
 // The events of a step, after the push: chunks of 64 consecutive events of
-// one push workgroup's range (in unit order: tiles, waves, slots), fully
-// packed but for the last of each range, strided over all the waves of the
-// grid.  Each lane one event: the renewal
-// (a fresh velocity from the species' initial distribution, call 6), the
-// collision of a candidate, or the secondary-emission test of an absorbed
-// ion, all in FP64, with the new velocity rounded to binary32 once and
-// written to the particle's slot, and the diagnostics of the particle's
-// final velocity.  A birth (ionization pair, secondary electron) claims a
+// one push workgroup's list (in any order: its waves claim places as they go),
+// fully packed but for the last of each list, strided over all the waves of
+// the grid.  Each lane one event: the renewal (a fresh velocity from the
+// species' initial distribution, call 6), the collision of a candidate, or the
+// secondary-emission test of an absorbed ion, all in FP64, with the new
+// velocity rounded to binary32 once and written to the particle's slot.  The
+// push has sampled the particle with the velocity of the record; a sampled
+// step adds what the new one changes.  A birth (ionization pair, secondary electron) claims a
 // slot of its tile's staging area with an atomic and carries its parent's
 // slot, by which the finalize orders the tile's births; its charge goes
 // straight into the discharge's fixed-point sums.  Counters come from
