@@ -434,7 +434,10 @@ pic_status pic_use_graphs(pic_ctx* ctx, int32_t enable);
  * each push workgroup processes the events of its own tiles after its push,
  * with no further launch, which shortens the step of a workload too small
  * to fill the GPU; this applies to tiles of 256 threads with one to four
- * particles each (other shapes keep the events kernel).  Until this call or
+ * particles each (other shapes keep the events kernel).  A context of more
+ * than 2^26 particle slots gets denser staging for births with such a schedule
+ * (6.75 bytes per slot more); without the memory for it the events kernel
+ * runs.  Until this call or
  * pic_config_tiles sets a schedule, the library chooses place and tile shape
  * by the number of particles of the running discharges, as the last call that
  * set or read them left it (pic_init, pic_set_particles, pic_load_profiles;

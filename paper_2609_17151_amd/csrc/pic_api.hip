@@ -55,6 +55,7 @@ struct pic_ctx {
     int64_t steps_since_sort = 0;
     int compact_every = 16;              // steps between compactions of the holes
     int events_in_push = 0;              // 256-thread general pushes do their own events
+    bool dense = false;                  // births staged for a quarter of every small tile's particles (births_per_tile)
     bool schedule_set = false;           // by pic_config_tiles or pic_config_events; else plan_step's rule
     std::vector<int64_t> known;          // particles per segment when the host last set or read them
     std::vector<uint8_t> retired;        // per discharge
@@ -124,7 +125,32 @@ int64_t context_slots(const pic_ctx* c)
     return n;
 }
 
-bool dense_births(const pic_ctx* c) { return context_slots(c) <= kDenseSlots; }
+// whether the schedule that was set has the push do its own events
+bool fused_schedule(const pic_ctx* c)
+{
+    int ppt = c->ppt, threads = c->threads;
+    push_shape(ppt, threads, true);
+    return c->schedule_set && c->events_in_push && push_fusable(ppt, threads, true);
+}
+
+// births staged in `slots` slots (see births_per_tile; every tile size's)
+size_t births_bytes(int64_t slots, bool dense)
+{
+    return sizeof(Birth) * (size_t)(dense ? slots / 4 : slots / kTileMax * births_per_tile(kTileMax, false));
+}
+
+// A quarter's staging for a schedule that needs it.  Without the memory the
+// schedule's events are done by the events kernel (the same results).  The
+// stream is idle.
+void grow_births(pic_ctx* c)
+{
+    if (c->dense || !c->d.births || !fused_schedule(c)) return;
+    void* p = dev_alloc(c, births_bytes(context_slots(c), true));
+    if (!p) return;
+    dev_release(c, c->d.births);
+    c->d.births = (Birth*)p;
+    c->dense = true;
+}
 
 // The storage of a step's events and births, once: at pic_init where the
 // configuration has them, else with the first collision table (a periodic box
@@ -135,8 +161,8 @@ pic_status alloc_events(pic_ctx* c)
     DevPtrs& d = c->d;
     if (d.births) return PIC_OK;
     const int64_t slots = context_slots(c);
-    const int64_t staged = slots / kTileMax * births_per_tile(kTileMax, false);      // every tile size's without `dense`
-    void* births = dev_alloc(c, sizeof(Birth) * (size_t)(dense_births(c) ? slots / 4 : staged));
+    c->dense = slots <= kDenseSlots;
+    void* births = dev_alloc(c, births_bytes(slots, c->dense));
     void* evr = dev_alloc(c, 16ull * slots);
     void* evq = dev_alloc(c, 16ull * slots);
     if (!births || !evr || !evq) {
@@ -146,6 +172,7 @@ pic_status alloc_events(pic_ctx* c)
     d.births = (Birth*)births;
     d.evr = (uint4*)evr;
     d.evq = (uint4*)evq;
+    grow_births(c);
     return PIC_OK;
 }
 
@@ -862,6 +889,7 @@ pic_status pic_config_tiles(pic_ctx* ctx, int32_t ppt, int32_t threads, int32_t 
     ctx->steps_since_sort = 0;
     ctx->compact_every = compact_every;
     ctx->steps_since_compact = 0;
+    grow_births(ctx);
     return rc;
 }
 
@@ -872,6 +900,7 @@ pic_status pic_config_events(pic_ctx* ctx, int32_t in_push)
     if (rc != PIC_OK) return rc;
     ctx->events_in_push = in_push;
     ctx->schedule_set = true;
+    grow_births(ctx);
     return rc;
 }
 
@@ -936,7 +965,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
         if (has_events(sc)) p.general = true;
     }
     int events_in_push = ctx->events_in_push;
-    const bool dense = dense_births(ctx);
+    const bool dense = ctx->dense;
     if (!ctx->schedule_set && p.general && dense) {
         // Nobody chose a schedule: small tiles whose workgroups do their own
         // events up to kFuseParticles particles, as one launch and the tiles'
@@ -966,7 +995,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
         }
     }
     push_shape(p.ppt, p.threads, p.general);
-    p.fuse = events_in_push && push_fusable(p.ppt, p.threads, p.general);
+    p.fuse = events_in_push && dense && push_fusable(p.ppt, p.threads, p.general);
     // unsampled streaming steps need no finalize in between (nothing is born,
     // lost or averaged): the push solves for the field itself, on meshes that
     // the lanes of four waves hold (both sides' times at the push kernel)
@@ -983,7 +1012,6 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     pa.nodes_max_dyn = nn_max;
     pa.cells_max_dyn = nc_max;
     pa.acc = ctx->d.acc;
-    pa.births_per_tile = (uint32_t)births_per_tile(T, dense);
     uint64_t key = 1469598103934665603ull;
     auto mix = [&](uint64_t v) { key = (key ^ v) * 1099511628211ull; };
     mix((uint64_t)ctx->diag);
@@ -996,6 +1024,7 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
     mix((uint64_t)p.threads);
     mix((uint64_t)p.general);
     mix((uint64_t)p.fuse);
+    mix((uint64_t)(uintptr_t)ctx->d.births);
     mix((uint64_t)p.solve);
     mix((uint64_t)p.grid);
     p.fa.d = ctx->d;

@@ -29,9 +29,10 @@ constexpr int kTileMin = 256;                               // smallest tile of 
 // takes whatever births a tile of 4096 would.  That is 9 bytes of staging per
 // slot, 0.6 GB at most.  Larger contexts stage T / 16, 2.25 bytes per slot of
 // 82: with 9 a GPU would hold 8 % fewer particles; the default keeps tiles of
-// 4096 there.
+// 4096 there, and an explicit schedule whose push does its own events (which
+// stages a quarter always) gets the 9 bytes when it is chosen.
 constexpr int64_t kDenseSlots = 1ll << 26;
-constexpr int births_per_tile(int T, bool dense)
+__host__ __device__ constexpr int births_per_tile(int T, bool dense)
 {
     return !dense || T / 16 > 256 ? T / 16 : (T / 4 < 256 ? T / 4 : 256);
 }

@@ -10,7 +10,6 @@ struct PushArgs {
     DevPtrs d;
     int32_t diag;                 // accumulate electron energy deposit and EEPF
     float eepf_inv_bin;           // 1 / bin width (eV)
-    uint32_t births_per_tile;     // staging slots of a tile
     int32_t nodes_max_dyn, cells_max_dyn;
     unsigned long long* acc;      // deposit sums of this step ([B][S][kRep][nodes_max])
     // a streaming step that solves for its field itself (SOLVE): the sums of
@@ -43,13 +42,14 @@ struct FinArgs {
     int32_t diag;
     int32_t only_b;               // -1: all discharges (grid = B), else this one (grid = 1)
     int32_t births_per_tile;      // staging slots of a push tile (0: the step cannot have births)
-    int32_t steps;                // steps since the last finalize
     unsigned long long* acc;      // deposit sums to solve for (cleared)
     unsigned long long* acc_clear;   // another set to clear, or null
     double t_ext;
     const double* rho_ext;
     double* phi_out;
     double* e_out;
+    int32_t steps;                // steps since the last finalize (last: the place in the argument block moves a
+                                  // field solve of 21.5 us by 0.4)
 };
 
 struct LoadArgs {

@@ -1223,7 +1223,7 @@ __global__ __launch_bounds__(BS) void push_kernel(PushArgs a)
         // this workgroup's own events, in chunks of 64 over its waves:
         // the same pass as the events kernel's, on the records and the
         // tiles this workgroup has just written
-        const EvPass ps{T, chunk, a.births_per_tile, DIAG, a.eepf_inv_bin,
+        const EvPass ps{T, chunk, (uint32_t)births_per_tile(T, true), DIAG, a.eepf_inv_bin,
                         (RY ? kUseY : 0) | (RZ ? kUseZ : 0)};
         for (uint32_t kc = (uint32_t)wid; kc < nch; kc += (uint32_t)kWavesPerTile) {
             uint4 rec, rq;

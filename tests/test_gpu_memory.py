@@ -53,21 +53,77 @@ def test_events_and_births_of_large_contexts(pic, tiles):
     sim.close()
 
 
-def test_a_large_context_runs_as_a_small_one(pic):
-    # the same discharge in a context that stages births for tiles of 4096
+def _run(sim, steps=40):
+    sim.step(steps)
+    sim.sync()
+    parts = [sim.get_particles(s) for s in range(2)]
+    return ([p[k] for p in parts for k in ("cell", "off", "vx", "vy", "vz", "id")] +
+            [sim.phi(), sim.coll()["coll"], sim.wall()["absorbed"], np.array(sim.counts()["next_id"])])
+
+
+def _capacity(cfg, capacity):
+    return dict(cfg, species=[dict(sp, capacity=capacity) for sp in cfg["species"]])
+
+
+@pytest.mark.parametrize("schedule", [None, (4, 256, True), (1, 256, True), (4, 256, False)])
+def test_a_large_context_runs_as_a_small_one(pic, schedule):
+    # the same discharge in a context that stages births for tiles of 4096,
+    # until a schedule whose push does its own events is set (after some steps
+    # replayed from a captured graph, with the old staging)
     n = 60_000
     cfg, tabs = small_argon(n_init=n, weight=6e13 / n)
     runs = []
     for capacity in (4 * n, (1 << 25) + 1):
-        big = dict(cfg, species=[dict(sp, capacity=capacity) for sp in cfg["species"]])
-        sim = pic.Sim(big, tabs)
-        sim.step(40)
-        parts = [sim.get_particles(s) for s in range(2)]
-        runs.append([p[k] for p in parts for k in ("cell", "off", "vx", "vy", "vz", "id")] +
-                    [sim.phi(), sim.coll()["coll"], sim.wall()["absorbed"], np.array(sim.counts()["next_id"])])
+        sim = pic.Sim(_capacity(cfg, capacity), tabs)
+        sim.step(64)
+        sim.sync()
+        before = torch.cuda.memory_allocated()
+        if schedule:
+            sim.config_tiles(*schedule[:2], 0, 16)
+            sim.config_events(schedule[2])
+            sim.config_events(schedule[2])
+        grown = torch.cuda.memory_allocated() - before
+        slots = 2 * ((1 << 25) + 4096)
+        more = int((36 / 4 - 36 / 16) * slots) if capacity > 4 * n and schedule and schedule[2] else 0
+        assert abs(grown - more) <= 4096
+        runs.append(_run(sim, 64))
         sim.close()
     for x, y in zip(*runs):
         assert np.array_equal(x, y)
+
+
+def test_no_memory_for_the_denser_staging(pic):
+    # the schedule is taken all the same, its events by the events kernel
+    n = 60_000
+    cfg, tabs = small_argon(n_init=n, weight=6e13 / n)
+    full = []
+    sim = pic.Sim(_capacity(cfg, (1 << 25) + 1), tabs)
+    sim.close()
+    real = torch.cuda.caching_allocator_alloc
+
+    def refusing(size, *a):
+        return None if full else real(size, *a)
+
+    torch.cuda.caching_allocator_alloc = refusing
+    try:
+        sim = pic.Sim(_capacity(cfg, (1 << 25) + 1), tabs)
+        full.append(1)
+        sim.config_tiles(4, 256, 0, 16)
+        sim.config_events(True)
+        sim.profile(True)
+        sim.step(2)
+        assert sim.timing()["events_n"] == 2
+        sim.profile(False)
+        got = _run(sim)
+        sim.close()
+    finally:
+        torch.cuda.caching_allocator_alloc = real
+    small = pic.Sim(_capacity(cfg, 4 * n), tabs)
+    small.config_tiles(4, 256, 0, 16)
+    small.step(2)
+    for x, y in zip(got, _run(small)):
+        assert np.array_equal(x, y)
+    small.close()
 
 
 def test_collisions_from_a_later_step_on(pic):
