@@ -907,6 +907,7 @@ pic_status pic_config_events(pic_ctx* ctx, int32_t in_push)
 pic_status pic_set_diag(pic_ctx* ctx, int32_t enable, double eepf_emax_eV)
 {
     if (!ctx || !(eepf_emax_eV > 0.0) || !std::isfinite(eepf_emax_eV)) return PIC_EINVAL;
+    if (ctx->diag != (enable ? 1 : 0)) ctx->small_tiles = -1;     // another line
     ctx->diag = enable ? 1 : 0;
     ctx->eepf_emax = eepf_emax_eV;
     return PIC_OK;
@@ -970,24 +971,38 @@ pic_status plan_step(pic_ctx* ctx, StepPlan& p)
         // Nobody chose a schedule: small tiles whose workgroups do their own
         // events up to kFuseParticles particles, as one launch and the tiles'
         // number count there; large tiles and the events kernel above, and
-        // where small tiles would not stage the births of large ones.
-        // Measured, us per step, 4 x 1024 with the events kernel / 4 x 256
-        // with its own events: one argon discharge of 2e4 particles 26.6 /
-        // 16.5, 4e5 28.4 / 21.8 (sampled 44.7 / 35.1), 1.5e6 37.7 / 33.5, 4e6
-        // 56.1 / 55.7; 16 of 3.2e6 in all 58.6 / 53.0, 64 of 4e6 70.0 / 62.6; a
-        // renewing box of 8e6 82.6 / 84.0, 64 discharges of 1.77e7 184 / 201
-        // (sampled 309 / 302).
+        // where small tiles would not stage the births of large ones.  In
+        // sampled steps of a single discharge all workgroups add to the same
+        // nodes' sums, three times as many with small tiles: large ones from
+        // kFuseSampledOne on.  Measured, us per step, 4 x 1024 with the events
+        // kernel / 4 x 256 with its own events:
+        //   one argon discharge, 2e4 particles 21.2 / 15.6, 4e5 25.1 / 20.2, 1.5e6
+        //     32.5 / 29.1, 4e6 50.8 / 46.5, 6e6 67.6 / 59.4, 1.2e7 118 / 103;
+        //     sampled 2e4 31.0 / 23.1, 4e5 35.8 / 30.6, 1.5e6 47.8 / 47.4, 2e6 47 /
+        //     49 to 86 / 84 (10 to 200 mTorr), 3e6 57 / 65 to 113 / 112, 6e6 84 / 93
+        //     to 198 / 191;
+        //   two of them, sampled, 3e6 in all 57.5 / 55.4, 6e6 131 / 120; 16 of 3.2e6
+        //     51.4 / 45.8 (sampled 82.1 / 72.2), 9e6 107 / 96 (161 / 155); 64 of 4e6
+        //     62.8 / 56.4 (85.4 / 79.8), 9e6 98.0 / 94.3 (134 / 129), 1.77e7 166 /
+        //     170 (225 / 224); 4.9e7 as the long run leaves them 414 / 466;
+        //   a renewing box of 2e6 31.0 / 30.7, 4e6 48.7 / 51.2, 6e6 66.7 / 64.7, 8e6
+        //     82.7 / 84.0; sampled 1e6 36.7 / 36.7, 4e6 65.7 / 69.4, 6e6 84.5 / 91.4;
+        //   forty swarms of 4e6 60.0 / 58.6, 8e6 94.9 / 93.0; five of 5e6 85.8 / 109.
         // The particles are those of the running discharges, by the counts that
         // the last call which set or read them left (a step does not bring any
         // to the host).  A run that falls below the line again takes small
         // tiles at half of it, so that a swarm thinned at every read does not
         // capture its graph anew each time.
-        constexpr int64_t kFuseParticles = 6000000;
+        constexpr int64_t kFuseParticles = 6000000, kFuseSampledOne = 2000000;
         int64_t n = 0;
-        for (int g = 0; g < B * S; ++g)
-            if (!ctx->retired[g / S]) n += ctx->known[g];
-        const int64_t line = ctx->small_tiles == 0 ? kFuseParticles / 2 : kFuseParticles;
-        ctx->small_tiles = n <= line ? 1 : 0;
+        int running = 0;
+        for (int b = 0; b < B; ++b) {
+            if (ctx->retired[b]) continue;
+            ++running;
+            for (int s = 0; s < S; ++s) n += ctx->known[(size_t)b * S + s];
+        }
+        const int64_t line = ctx->diag && running == 1 ? kFuseSampledOne : kFuseParticles;
+        ctx->small_tiles = n <= (ctx->small_tiles == 0 ? line / 2 : line) ? 1 : 0;
         if (ctx->small_tiles) {
             p.ppt = 4;
             p.threads = 256;

@@ -42,6 +42,20 @@ def test_both_sides_of_the_line(pic, n, large):
     sim.close()
 
 
+@pytest.mark.parametrize("batch,n,large", [(1, 2_000_000, False), (1, 2_000_002, True), (2, 2_000_004, False)])
+def test_sampled_steps_of_one_discharge(pic, batch, n, large):
+    cfg, tabs = small_argon(n_init=n // 2 // batch, weight=6e13 / n)
+    for sp in cfg["species"]:
+        sp["capacity"] = n
+    sim = pic.Sim([cfg] * batch, tabs)
+    assert _events_launches(sim) == 0                    # unsampled: far below the line
+    sim.set_diag(True)
+    assert _events_launches(sim) == (2 if large else 0)
+    sim.set_diag(False)
+    assert _events_launches(sim) == 0
+    sim.close()
+
+
 def _ionizing(pic, n, hot):
     # `hot` of n electrons at 20 eV, every one a candidate that ionizes with
     # probability 1 / 1.05 (a constant collision frequency far above 1 / dt);
