@@ -96,11 +96,13 @@ __device__ __forceinline__ void global_deposit(unsigned long long* acc, int c, f
 }
 
 // NT: non-temporal (streaming) accesses, which leave the caches to the rest
-// of the step.  Measured on the 64-discharge argon sweep (4.7e7 particles):
-// the general push 541 -> 461 us (each at its fastest tile shape) and the
-// events kernel after it 97 -> 80 us.  The streaming push on the E x B box,
-// whose particle arrays fit the Infinity Cache between steps, is 11 % slower
-// with them and does not use them.
+// of the step.  The general push takes them: us per step without / with, 64
+// argon discharges of 4.9e7 particles 462 / 396, of 1.77e7 sampled 249 / 231,
+// one of 4e5 19.8 / 19.9.  Where the particles would stay in the Infinity Cache
+// from step to step they cost: 1.77e7 unsampled 157 / 166, a renewing box of 8e6
+// 75.0 / 82.4, forty swarms of 4e6 54.5 / 56.7.  The streaming push, which does
+// nothing else with the caches, is 11 % slower with them on an E x B box of 8e6
+// and does without.
 template <int N, typename V, bool NT = false, typename S>
 __device__ __forceinline__ void vload(const PIC_GLOBAL S* p, S* out)
 {
