@@ -12,7 +12,7 @@ from gpu_helpers import small_argon
 pytestmark = pytest.mark.gpu
 
 SMALL = 32 << 20         # what does not grow with the slots: sums and fields of up to 400 nodes, the windows' ring
-TILES = 16.0 / 256       # four arrays of 4 bytes (one of 8 among them) per 256 slots
+TILES = 16.0 / 256       # two arrays of 4 bytes and one of 8 per 256 slots
 
 
 @pytest.fixture(scope="module")
